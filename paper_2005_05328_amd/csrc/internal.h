@@ -68,6 +68,8 @@ struct lc_args {
     int n_cheb;
     double cchi[DZS_CHEB_MAX];
     double cdrift[DZS_CHEB_MAX];
+    // bounds over the drift (dzs_make_lc_args): max |D|, max |dD/dt|, min chi |dchi/dt|
+    double drift_max, drift_slope, chi_fall;
 };
 
 // the factors of one batched step, in a device block (and its pinned host staging): a

@@ -301,3 +301,54 @@ def test_batched_step_of_coarsened_boxes_with_records(dz, fp32):
             dp = out[k][o] - getattr(ref, k)[r] - fac["K2"] * (g[a] - rg[a])
             assert np.abs(dp).max() <= 1e-9 * np.abs(getattr(ref, k)).max()
     assert with_records >= 2
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1025, 4099])
+@pytest.mark.parametrize("fast", [False, True])
+def test_crossing_queue_edges_and_both_solvers(dz, n, fast):
+    """Counts around the 1024 particles of one workgroup of the crossing test, every particle
+    just inside the sphere (all of a workgroup's slots queued) or one in seven; momenta for
+    which the sphere outruns the particle (the secant solver) or not (bisection).  The
+    selection is the oracle's; each record's offset is d0 + p D(a) and lies on the sphere of
+    its crossing time.  Bound: the series of chi and D are good to 1e-12 relative, and t is
+    found to the rounding of F, some 1e-13 of the sphere's radius in |d| - chi."""
+    a0, a1, L = 0.90, 0.91, 2000.0
+    sp = dz.step_factors(a0, a1, 0.3)
+    lc = sp.lc
+    g = dzs_ics.rng(31 + n)
+    chi0, chi1 = math.sqrt(lc.chi2_0), math.sqrt(lc.chi2_1)
+    u = g.standard_normal((3, n))
+    u /= np.sqrt((u ** 2).sum(0))
+    r = chi1 + (chi0 - chi1) * (0.02 + 0.96 * g.random(n))
+    if n > 1100:
+        r = np.where(np.arange(n) % 7 == 0, r, 0.3 * r)
+    ps = dzs_ics.uniform_random(n, L, seed=5, vel=2e5 if fast else 500.0)
+    ps.x, ps.y, ps.z = 1000.0 + r * u
+    ps.id = np.arange(n, dtype=np.uint32)
+    x_obs = [1000.0] * 3
+    for d in range(3):
+        lc.x_obs[d] = x_obs[d]
+    box = dz.make_box(L, 1.0, 1.0)
+    ctx = dz.Context(n, 0)
+    st = dz.State.from_host(ps)
+    ring = dz.LCRing(n)
+    ring.reset()
+    ctx.lightcone_emit(box, st, lc, ring)
+    rec = ring.records()
+    ctx.close()
+    mask, d0, _, _ = oracle.lightcone_select(ps.x, ps.y, ps.z, ps.px, ps.py, ps.pz, L, x_obs,
+                                             lc.D, lc.chi2_0, lc.chi2_1)
+    assert rec["overflow"] == 0 and rec["count"] == int(mask.sum())
+    if not fast:
+        assert rec["count"] == (n if n <= 1100 else (n + 6) // 7)
+    i = rec["id"].astype(np.int64)
+    assert np.array_equal(np.sort(i), np.nonzero(mask)[0])
+    for k in np.linspace(0, len(i) - 1, min(len(i), 25)).astype(int):
+        a, p = float(rec["a_cross"][k]), rec["p"][k]
+        assert a0 <= a <= a1
+        D = oracle.drift_factor(a0, a) if a > a0 else 0.0
+        ref = d0[:, i[k]] + p * D
+        assert np.abs(rec["d"][k] - ref).max() <= 1e-11 * chi0 + 1e-11 * np.abs(p * lc.D).max()
+        # on the sphere, unless the drifted particle left it only through the periodic image
+        if np.linalg.norm(d0[:, i[k]] + p * lc.D) > chi1 * (1 + 1e-9):
+            assert abs(np.linalg.norm(rec["d"][k]) - oracle.chi(a)) <= 1e-10 * chi0

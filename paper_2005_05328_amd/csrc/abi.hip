@@ -251,7 +251,8 @@ static dzs_status create(dzs_ctx *c, const dzs_capacity *cap) {
     c->walk_stack_slots = 4096;
     c->walk_stack_depth = 8192;
     DZS_TRY(alloc(c, &c->walk_stack, c->walk_stack_slots * c->walk_stack_depth));
-    DZS_TRY(alloc(c, &c->walk_counter, 64));
+    DZS_TRY(alloc(c, &c->walk_counter, 64 + 4 * DZS_WALK_FT_N));
+    c->walk_ftab = (float *)(c->walk_counter + 64);
     DZS_HIP(c, hipMemset(c->walk_counter, 0, 64 * sizeof(uint32_t)));
     DZS_TRY(alloc(c, &c->cell_node, 1ull << (3 * DZS_CELL_K_MAX)));
     // the relative criterion's |g|, the time-step bins and the walk's target flags

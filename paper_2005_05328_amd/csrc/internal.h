@@ -19,6 +19,7 @@
 #define DZS_TREE_FIRST_PASS 2  // radix passes of 8 bits skipped by that sort
 #define DZS_CELL_K_MAX 7  // deepest level of the walk start cells (8^7 cells, 10 MB)
 #define DZS_KEY_SIDE 2097152.0
+#define DZS_WALK_FT_N 512  // cubics of the walk's FP32 force table
 
 // ---------------------------------------------------------------------------------------
 // kernel classes timed by dzs_timing
@@ -147,7 +148,9 @@ struct dzs_ctx {
     uint32_t *grp_flag = nullptr, *grp_scan = nullptr, *grp_first = nullptr;
     uint32_t *walk_stack = nullptr;
     uint64_t walk_stack_slots = 0, walk_stack_depth = 0;
-    uint32_t *walk_counter = nullptr;  // [0] work counter, [1] overflow flag, [8..9] pair count
+    uint32_t *walk_counter = nullptr;  // [0] work counter, [2] overflow flag, [8..9] pair count
+    float *walk_ftab = nullptr;        // the precision form's table of F(w), 4 DZS_WALK_FT_N
+                                       // floats behind the counters
     double q_coef[32] = {0};           // split-factor polynomial (see tree.hip)
     double q_wmax = -1.0;
     double q_err = 1.0;

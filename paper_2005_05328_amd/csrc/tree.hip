@@ -658,22 +658,35 @@ dzs_status dzs_check_order(dzs_ctx *ctx, uint64_t n, hipStream_t s) {
 // ---------------------------------------------------------------------------------------
 #define WALK_QN 18  // split-factor polynomial coefficients (Horner, fully unrolled): worst
                     // relative error in S 1.3e-13 at r_cut = 4.5 r_s, 7e-12 at 5 r_s
-// FP32: S(u) from a table of cubics, one per interval of u = r / r_s on [0, r_cut / r_s]:
-// Hermite interpolation of S and dS/du at both ends of each interval (worst absolute error
-// in S below 1e-7 at 64 intervals, FP32 coefficients included; checked on the host), plus
-// an entry past the cutoff that extends the last one linearly (a pair within rounding of
-// r_cut).  The table rides in the kernel arguments and each workgroup stages it in LDS.
+// FP32, outside the spline supports: F(w) = S(sqrt(w) / r_s) / w^1.5 from a table of cubics in
+// w = r^2, one per interval of 1/32 of an octave of w (the interval is the exponent and the top
+// five mantissa bits of w, so finding it takes no square root), over the 16 octaves up to the
+// interval of r_cut^2, i.e. r from r_cut / 256.  The cubic of interval j sits in slot j mod 512,
+// so any w finds a slot with one shift and one mask.  Cubics through the four Chebyshev nodes of the
+// interval: worst error 2e-8 of F at small w, 1e-8 of the unsplit force near r_cut, before the
+// FP32 rounding of the coefficients (the S table below with r^-3 from the hardware 1/sqrt:
+// 8.5e-8 in S and four more roundings).  The walk's set-up kernel computes it for each call.
+#define WALK_FT_BITS 5
+#define WALK_FT_OCT 16
+#define WALK_FT_N (WALK_FT_OCT << WALK_FT_BITS)
+#define WALK_FT_SHIFT (23 - WALK_FT_BITS)
+// FP32, close pairs (inside a spline support, or below the table of F): S(u) from a table of
+// cubics, one per interval of u = r / r_s on [0, r_cut / r_s]: Hermite interpolation of S and
+// dS/du at both ends of each interval (worst absolute error in S below 1e-7 at 64 intervals,
+// FP32 coefficients included; checked on the host), plus an entry past the cutoff that extends
+// the last one linearly.  The table rides in the kernel arguments; each workgroup stages both
+// tables in LDS.
 #define WALK_TAB_N 64
-// list region / cutoff sphere below which a group evaluates densely: in FP32 the one-pass loop
+// list region / cutoff sphere below which an FP32 group evaluates densely: the one-pass loop
 // wins even for wide groups (512^3 walk: 300 ms masked, 285 ms at 2.5, 282 ms at 3-4, 281 ms
-// dense everywhere), in FP64 the masked loop wins everywhere (128^3 walk: 2.38 ms masked,
-// 2.40 at 2.0, 2.81 dense everywhere)
-#ifndef WALK_DENSE_E_F32
-#define WALK_DENSE_E_F32 6.0
-#endif
-#ifndef WALK_DENSE_E_F64
-#define WALK_DENSE_E_F64 0.0
-#endif
+// dense everywhere).  In FP64 the masked loop wins everywhere (128^3 walk: 2.38 ms masked, 2.40
+// at 2.0, 2.81 dense everywhere), so the FP64 walk has no dense form.
+#define WALK_DENSE_E 6.0
+// waves of a walk workgroup: the FP32 form shares its tables among 8 waves (two workgroups of
+// 67 KB fill a CU's 16 wave slots at 128 VGPRs); the waves work on their own groups and meet
+// only once, when the tables are staged
+template <typename T> struct walk_waves { static constexpr int N = 1; };
+template <> struct walk_waves<float> { static constexpr int N = 8; };
 
 struct walk_args {
     const uint32_t *grp_first;
@@ -692,6 +705,8 @@ struct walk_args {
     double q[WALK_QN];
     float4 stab[WALK_TAB_N + 1];  // FP32 form: the cubics of S(u), coefficients of f^0..f^3
     double stab_scale;            // intervals per unit of u (WALK_TAB_N r_s / r_cut)
+    const float4 *ftab;           // FP32 form: the cubics of F(w), [WALK_FT_N] (device)
+    float ft_lo;                  // the low end of the table, in its unit of w
     // start cells: the walk of a group begins at the level-K nodes (and shallower leaves) of
     // the cells that meet its bounding box grown by r_cut, instead of at the root
     const uint32_t *cell_node;  // [8^K] node covering each level-K cell (Morton order)
@@ -808,23 +823,50 @@ template <typename T> __device__ __forceinline__ T gsoft_inner(T r, T h) {
                  T(1.0) / (T(15.0) * u * u * u));
 }
 
-// One interaction-list entry in LDS: pm = position (shifted to the image nearest the group;
-// in FP32 relative to the group centre) and mass; hh = (hm2, h): the entry's spline support h
-// and hm2 = max(h^2, the largest h_i^2 of the group's targets), an upper bound of the pair's
-// squared support that decides, with one comparison, whether the exact spline test is
-// needed.  FP32: 32 bytes, one 16-byte read for pm and one 4-byte read for hm2.
+// The interaction list in LDS: pm = position (shifted to the image nearest the group; in FP32
+// relative to the group centre) and mass; hh = (hm2, h): the entry's spline support h and hm2 =
+// max(h^2, the largest h_i^2 of the group's targets, the low end of the table of F), an upper
+// bound of the pair's squared support that decides, with one comparison, whether the exact
+// spline test is needed.  FP32: two arrays, one 16-byte and one 4-byte read per entry.
 template <typename T> struct vec4_of;
 template <> struct vec4_of<float> { typedef float4 type; typedef float2 half; };
-struct dvec4 { double x, y, z, w; };   // 8-byte aligned: a 48-byte FP64 entry
+struct dvec4 { double x, y, z, w; };
 struct dvec2 { double x, y; };
 template <> struct vec4_of<double> { typedef dvec4 type; typedef dvec2 half; };
-template <typename T> struct src_entry {
-    typename vec4_of<T>::type pm;
-    typename vec4_of<T>::half hh;
+struct dentry {   // 48 bytes: the masked loop's gathers spread over 16 bank offsets (8 at 32)
+    dvec4 pm;
+    dvec2 hh;
 };
-template <typename T> struct src_list {
-    src_entry<T> *e;
+template <typename T> struct src_list;
+template <> struct src_list<float> {
+    float4 *p;
+    float2 *h;
+    __device__ __forceinline__ float4 &pm(uint32_t i) const { return p[i]; }
+    __device__ __forceinline__ float2 &hh(uint32_t i) const { return h[i]; }
 };
+template <> struct src_list<double> {
+    dentry *e;
+    __device__ __forceinline__ dvec4 &pm(uint32_t i) const { return e[i].pm; }
+    __device__ __forceinline__ dvec2 &hh(uint32_t i) const { return e[i].hh; }
+};
+template <typename T> struct list_lds;
+template <> struct list_lds<float> {
+    float4 p[WALK_LIST + 64];
+    float2 h[WALK_LIST + 64];
+    __device__ __forceinline__ src_list<float> list() { return {p, h}; }
+};
+template <> struct list_lds<double> {
+    dentry e[WALK_LIST + 16];
+    __device__ __forceinline__ src_list<double> list() { return {e}; }
+};
+
+// Ordering of LDS and stack accesses between the lanes of one wave (its LDS operations complete
+// in order; only the compiler must keep them in place).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
 
 template <typename T> struct split_coef;
 template <> struct split_coef<double> {
@@ -888,13 +930,12 @@ __device__ __forceinline__ T pair_factor(const walk_args &A, T r2, T eh, T hm2, 
     return g;
 }
 
-// FP32 pair force factor g_soft(r) S(r/r_s) with S from the LDS table: x = u WALK_TAB_N /
-// u_cut = r tscale, interval k = floor(x) (at most WALK_TAB_N, the entry past the cutoff), the
-// cubic at f = x - k.  r2 = 0 (the target itself) gives a finite g: its separation is zero.
-//
+// FP32 pair force factor g_soft(r) S(r/r_s) with S from the LDS table: x = u WALK_TAB_N / u_cut
+// = r tscale, interval k = floor(x) (at most WALK_TAB_N, the entry past the cutoff), the cubic
+// at f = x - k; in the spline only where r2 < hm2 (the entry's bound) and the exact test holds.
 // x in [WALK_TAB_N, ...) (r at or past r_cut: only a pair within rounding of the cutoff is
 // kept) takes the last entry at the fraction of x, a linear continuation from S(r_cut).
-// r2 = 0 (the target itself) makes g NaN: the caller masks the pair out by r2 > 0.
+// r2 = 0 (the target itself) makes the factor NaN: the caller leaves the pair out.
 __device__ __forceinline__ float pair_factor_tab(const float4 *__restrict__ tab, float r2,
                                                 float hm2, const float *eh_ptr, float hi,
                                                 float hi2, float tscale) {
@@ -915,8 +956,8 @@ __device__ __forceinline__ float pair_factor_tab(const float4 *__restrict__ tab,
     return g;
 }
 
-template <typename T> struct pair_eval;
-template <> struct pair_eval<double> {
+template <typename T, bool FT> struct pair_eval;
+template <> struct pair_eval<double, false> {
     const walk_args *A;
     double rs_inv2, rs_inv3, t_scale;
     // hh: the entry's (hm2, h)
@@ -926,12 +967,37 @@ template <> struct pair_eval<double> {
         return pair_factor<double>(*A, r2, v.y, v.x, hi, hi2, rs_inv2, rs_inv3, t_scale);
     }
 };
-template <> struct pair_eval<float> {
+template <> struct pair_eval<float, false> {
     const float4 *tab;
     float tscale;
     __device__ __forceinline__ float operator()(float r2, const float2 *hh, float hi,
                                                 float hi2) const {
         return pair_factor_tab(tab, r2, hh->x, &hh->y, hi, hi2, tscale);
+    }
+};
+// FP32 with far pairs' F from its table at w = r2.  The slot of a w outside the table holds
+// another interval's cubic: such a w belongs to a close pair, a pair past the cutoff or a
+// sentinel, whose F is not used.
+template <> struct pair_eval<float, true> {
+    const float4 *tab, *ftab;
+    float tscale;
+    __device__ __forceinline__ float far(float w) const {
+        const uint32_t bits = __float_as_uint(w);
+        const float4 c = ftab[(bits >> WALK_FT_SHIFT) & (uint32_t)(WALK_FT_N - 1)];
+        const float d = w - __uint_as_float(bits & ~((1u << WALK_FT_SHIFT) - 1u));
+        return __builtin_fmaf(__builtin_fmaf(__builtin_fmaf(c.w, d, c.z), d, c.y), d, c.x);
+    }
+    // r2 = 0 (the target itself): any finite factor, its separation is zero
+    __device__ __forceinline__ float close(float r2, const float *eh, float hi, float hi2) const {
+        return r2 == 0.0f ? 0.0f
+                          : pair_factor_tab(tab, r2, __builtin_inff(), eh, hi, hi2, tscale);
+    }
+    __device__ __forceinline__ float operator()(float r2, const float2 *hh, float hi,
+                                                float hi2) const {
+        float g = far(r2);
+        if (r2 < hh->x)   // rare
+            g = close(r2, &hh->y, hi, hi2);
+        return g;
     }
 };
 
@@ -942,11 +1008,11 @@ template <> struct pair_eval<float> {
 // times more entries than any one target's cutoff sphere; without the mask the whole wave
 // would step through the force arithmetic for every entry some lane accepts.  The caller
 // fills the P entries past the list with far-away sentinels, so the block bound is uniform.
-template <typename T, bool MINIMG>
-__device__ __forceinline__ void pair_loop(const pair_eval<T> &ev, const walk_geom &W,
+template <typename T, bool MINIMG, typename Ev>
+__device__ __forceinline__ void pair_loop(const Ev &ev, const walk_geom &W,
                                           const src_list<T> src, uint32_t nlist, uint32_t s,
                                           uint32_t P, T xi, T yi, T zi, T hi, T hi2, T &ax,
-                                          T &ay, T &az, uint32_t &n_pairs) {
+                                          T &ay, T &az, bool active, uint32_t &n_pairs) {
     const T rcut2 = T(W.rcut2), L = T(W.L);
     // entries per lane: uniform, so the block loops run on the scalar unit
     const uint32_t n_max = (uint32_t)__builtin_amdgcn_readfirstlane((int)((nlist + P - 1) / P));
@@ -957,18 +1023,18 @@ __device__ __forceinline__ void pair_loop(const pair_eval<T> &ev, const walk_geo
         uint32_t mask = 0;
         for (uint32_t k = 0; k < kmax; ++k) {
             T dx, dy, dz;
-            const T r2 = pair_sep<T, MINIMG>(src.e[blk + k * P].pm, xi, yi, zi, L, dx, dy, dz);
+            const T r2 = pair_sep<T, MINIMG>(src.pm(blk + k * P), xi, yi, zi, L, dx, dy, dz);
             mask = mask + mask + ((r2 < rcut2 && r2 > T(0.0)) ? 1u : 0u);
         }
-        mask <<= 32u - kmax;
+        mask = active ? mask << (32u - kmax) : 0u;   // targets nobody asked for: no pairs
         n_pairs += (uint32_t)__popc(mask);
         while (mask) {
             const uint32_t k = (uint32_t)__builtin_clz(mask);
             mask ^= 0x80000000u >> k;
-            const auto e = src.e[blk + k * P].pm;
+            const auto e = src.pm(blk + k * P);
             T dx, dy, dz;
             const T r2 = pair_sep<T, MINIMG>(e, xi, yi, zi, L, dx, dy, dz);
-            const T f = e.w * ev(r2, &src.e[blk + k * P].hh, hi, hi2);
+            const T f = e.w * ev(r2, &src.hh(blk + k * P), hi, hi2);
             ax = wfma(f, dx, ax);
             ay = wfma(f, dy, ay);
             az = wfma(f, dz, az);
@@ -976,39 +1042,33 @@ __device__ __forceinline__ void pair_loop(const pair_eval<T> &ev, const walk_geo
     }
 }
 
-// The lane's share of the list in one pass: every entry is evaluated and the pairs outside
-// r_cut (and the target itself) are multiplied by zero.  All lanes of a phase read the same
-// entry and every lane works on every iteration, so when most of the list lies inside most
-// targets' cutoff spheres (a compact group) this costs less than the masked two-pass loop.
-// 0 < r2 < rcut2: in FP32 one unsigned comparison of the bit patterns (r2 is a sum of
-// squares: +0, positive, or +inf for the far sentinels), so the result is a single mask
+// 0 < r2 < rcut2 by one unsigned comparison of the bit patterns (r2 is a sum of squares: +0,
+// positive, or +inf for the far sentinels), so the result is a single mask
 __device__ __forceinline__ bool pair_inside(float r2, float rcut2) {
     return __float_as_uint(r2) - 1u < __float_as_uint(rcut2) - 1u;
 }
-__device__ __forceinline__ bool pair_inside(double r2, double rcut2) {
-    return r2 < rcut2 && r2 > 0.0;
-}
 
-template <typename T, bool MINIMG>
-__device__ __forceinline__ void pair_dense(const pair_eval<T> &ev, const walk_geom &W,
-                                           const src_list<T> src, uint32_t nlist, uint32_t s,
-                                           uint32_t P, T xi, T yi, T zi, T hi, T hi2, T &ax,
-                                           T &ay, T &az, uint64_t act_mask, uint32_t &np_wave) {
-    const T rcut2 = T(W.rcut2), L = T(W.L);
+// The dense loop with S and 1/sqrt for every pair, and minimum-image pairs: phase s takes the
+// entries s, s + P, ...
+template <bool MINIMG>
+__device__ __forceinline__ void pair_dense_s(const pair_eval<float, false> &ev, float rcut2,
+                                             float L, const src_list<float> src, uint32_t nlist,
+                                             uint32_t s, uint32_t P, float xi, float yi, float zi,
+                                             float hi, float hi2, float &ax, float &ay, float &az,
+                                             uint64_t act_mask, uint32_t &np_wave) {
     const uint32_t n_max = (uint32_t)__builtin_amdgcn_readfirstlane((int)((nlist + P - 1) / P));
     uint32_t cnt = 0;   // wave-uniform, kept on the scalar unit
     for (uint32_t k = 0; k < n_max; ++k) {
-        const src_entry<T> *q = src.e + s + k * P;
-        const auto e = q->pm;
-        T dx, dy, dz;
-        const T r2 = pair_sep<T, MINIMG>(e, xi, yi, zi, L, dx, dy, dz);
+        const float4 e = src.pm(s + k * P);
+        float dx, dy, dz;
+        const float r2 = pair_sep<float, MINIMG>(e, xi, yi, zi, L, dx, dy, dz);
         const bool in = pair_inside(r2, rcut2);
         // pairs of the flagged targets, counted on the scalar unit
         cnt = (uint32_t)__builtin_amdgcn_readfirstlane(
             (int)(cnt + (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in) & act_mask)));
-        const T g = ev(r2, &q->hh, hi, hi2);
+        const float g = ev(r2, &src.hh(s + k * P), hi, hi2);
         // the factor of a pair outside (or of the target itself: r = 0) is not used
-        const T f = in ? e.w * g : T(0.0);
+        const float f = in ? e.w * g : 0.0f;
         ax = wfma(f, dx, ax);
         ay = wfma(f, dy, ay);
         az = wfma(f, dz, az);
@@ -1016,42 +1076,144 @@ __device__ __forceinline__ void pair_dense(const pair_eval<T> &ev, const walk_ge
     np_wave += cnt;
 }
 
-// one wave per workgroup; the FP32 walk fits 4 waves per SIMD (128 VGPRs), the FP64 one 3
-template <typename T, bool CELLS, bool BATCH>
-__global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_args A) {
-    static_assert(!(CELLS && BATCH), "a batch walk starts at the box nodes");
-    constexpr int KBL = BATCH ? DZS_BATCH_LEVELS : 0;  // tree levels above a box
-    __shared__ src_entry<T> s_list[WALK_LIST + 64];
-    const src_list<T> src{s_list};
-    __shared__ uint32_t q_first[64];
-    __shared__ uint32_t q_pref[65];
-    __shared__ double q_org[3][64];   // a queued leaf's origin in the list frame (image shift)
-    __shared__ uint32_t q_wide[64];
-    __shared__ uint32_t q_mark[64];
-    __shared__ uint32_t s_g;
-    __shared__ float s_hbox[12];
-    __shared__ float4 s_tab[sizeof(T) == 4 ? WALK_TAB_N + 1 : 1];
+// The lane's share of the list (FP32) in one pass: every entry is evaluated and the pairs
+// outside r_cut are multiplied by zero.  Phase s takes the entries s K .. s K + K - 1, K even,
+// two per iteration; all lanes of a phase read the same entry and every lane works on every
+// iteration, so when most of the list lies inside most targets' cutoff spheres (a compact group)
+// this costs less than the masked two-pass loop.  The caller puts sentinels, or entries outside
+// every target's cutoff, in the up to 2 P slots past the list.
+//
+// VALU-issue bound (the vector units of every SIMD are busy throughout), so its instructions
+// per entry are its cost: 21 (6 separation, 2 slot, 2 offset in the interval, 3 cubic, 1 cutoff
+// test, 1 close test, 5 mass, select and accumulation, the address) against 28 and a 1/sqrt at
+// a quarter of the rate with S from a table of r.  With the list flushed at one place (the pair
+// loops are in the kernel once, not three times) and short groups on fewer lanes: 256^3 walk
+// 28.0 -> 22.2 ms, 512^3 193 -> 153 ms.
+//
+// The pairs inside r_cut are counted on the scalar unit; a pair at zero separation (the target
+// itself) counts there too, always is a close pair and is taken off there (n_zero).
+__device__ __forceinline__ void pair_dense(const pair_eval<float, true> &ev, float rcut2,
+                                           const src_list<float> src, uint32_t nlist, uint32_t s,
+                                           uint32_t P, float xi, float yi, float zi, float hi,
+                                           float hi2, float &ax, float &ay, float &az,
+                                           uint64_t act_mask, uint32_t &np_wave,
+                                           uint32_t &n_zero) {
+    const uint32_t K = ((nlist + P - 1) / P + 1u) & ~1u;
+    const uint32_t n_max = (uint32_t)__builtin_amdgcn_readfirstlane((int)K);
+    const float4 *pm = src.p + s * K;
+    const float2 *hh = src.h + s * K;
+    uint32_t cnt = 0;   // wave-uniform, kept on the scalar unit
+    for (uint32_t k = 0; k < n_max; k += 2u, pm += 2, hh += 2) {
+        const float4 e0 = pm[0], e1 = pm[1];
+        const float b0 = hh[0].x, b1 = hh[1].x;
+        float dx0, dy0, dz0, dx1, dy1, dz1;
+        const float r0 = pair_sep<float, false>(e0, xi, yi, zi, 0.0f, dx0, dy0, dz0);
+        const float r1 = pair_sep<float, false>(e1, xi, yi, zi, 0.0f, dx1, dy1, dz1);
+        float g0 = ev.far(r0), g1 = ev.far(r1);
+        const bool in0 = r0 < rcut2, in1 = r1 < rcut2;
+        // pairs of the flagged targets
+        cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in0) & act_mask) +
+               (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in1) & act_mask);
+        const bool c0 = r0 < b0, c1 = r1 < b1;
+        if (c0 || c1) {   // rare
+            const uint32_t one = (uint32_t)(act_mask >> (threadIdx.x & 63u)) & 1u;
+            if (c0) {
+                g0 = ev.close(r0, &hh[0].y, hi, hi2);
+                n_zero += r0 == 0.0f ? one : 0u;
+            }
+            if (c1) {
+                g1 = ev.close(r1, &hh[1].y, hi, hi2);
+                n_zero += r1 == 0.0f ? one : 0u;
+            }
+        }
+        // the factor of a pair outside is not used
+        const float f0 = in0 ? e0.w * g0 : 0.0f, f1 = in1 ? e1.w * g1 : 0.0f;
+        ax = wfma(f0, dx0, ax);
+        ay = wfma(f0, dy0, ay);
+        az = wfma(f0, dz0, az);
+        ax = wfma(f1, dx1, ax);
+        ay = wfma(f1, dy1, ay);
+        az = wfma(f1, dz1, az);
+    }
+    np_wave += (uint32_t)__builtin_amdgcn_readfirstlane((int)cnt);
+}
 
-    const uint32_t lane = threadIdx.x;
-    const uint32_t G = (uint32_t)A.G_lanes;
-    const uint32_t P = 64u / G;
-    const uint32_t tl = lane % G, ph = lane / G;
+// 4 waves per SIMD (128 VGPRs).
+//
+// TEAM > 1: the workgroup's TEAM waves take every group together.  Each walks the tree and fills
+// its own list (the same one), evaluates every TEAM-th of its entries, and the first adds the
+// partial sums, wave by wave.  The walk proper is done TEAM times over, the pairs once: for the
+// case that the groups are too few to keep every wave busy to the end, where one group of a
+// dense clump can take as long as the whole launch.
+//
+// FT (FP32): far pairs from the table of F.  Not for a batch: its boxes' r_s differ, so F would
+// need another scaling per pair; it keeps S, the order of its sums and with them the bits of
+// its forces.
+template <typename T, bool CELLS, bool BATCH, int TEAM, bool FT>
+__global__ __launch_bounds__(64 * (TEAM > 1 ? TEAM : walk_waves<T>::N), 4) void k_tree_walk(
+    walk_args A) {
+    static_assert(!(CELLS && BATCH), "a batch walk starts at the box nodes");
+    static_assert(sizeof(T) == 4 || !FT, "the table of F is FP32");
+    static_assert(sizeof(T) == 8 || FT || TEAM == 1, "the order of the sums is kept");
+    constexpr int KBL = BATCH ? DZS_BATCH_LEVELS : 0;  // tree levels above a box
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr bool COOP = TEAM > 1;
+    constexpr int WAVES = COOP ? TEAM : walk_waves<T>::N;
+    // each wave's own list, leaf queue and half boxes
+    struct wave_lds {
+        list_lds<T> list;
+        double q_org[3][64];   // a queued leaf's origin in the list frame (image shift)
+        uint32_t q_first[64], q_wide[64], q_mark[64], q_pref[64];
+        uint32_t g;
+        float hbox[F32 ? 12 : 1];
+    };
+    __shared__ float4 s_ftab[FT ? WALK_FT_N : 1];
+    __shared__ float4 s_tab[F32 ? WALK_TAB_N + 1 : 1];
+    __shared__ wave_lds s_wave[WAVES];
+
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    wave_lds &S = s_wave[wave];
+    const src_list<T> src = S.list.list();
+    uint32_t *const q_first = S.q_first, *const q_pref = S.q_pref, *const q_wide = S.q_wide,
+                    *const q_mark = S.q_mark;
+    double(*const q_org)[64] = S.q_org;
+    float *const s_hbox = S.hbox;
+    const uint32_t team = (uint32_t)TEAM, member = COOP ? wave : 0u;
     const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    uint32_t *stk = A.stack + (uint64_t)blockIdx.x * A.depth;
+    uint32_t *stk = A.stack + ((uint64_t)blockIdx.x * WAVES + wave) * A.depth;
     if (A.bad && *A.bad)
         return;
-    if (sizeof(T) == 4) {
-        for (uint32_t k = lane; k <= WALK_TAB_N; k += 64)
+    if (F32) {
+        for (uint32_t k = threadIdx.x; k <= WALK_TAB_N; k += 64 * WAVES)
             s_tab[k] = A.stab[k];
+        if (FT)
+            for (uint32_t k = threadIdx.x; k < WALK_FT_N; k += 64 * WAVES)
+                s_ftab[k] = A.ftab[k];
         __syncthreads();
     }
 
-    for (;;) {
-        if (lane == 0)
-            s_g = atomicAdd(&A.counter[0], 1u);
-        __syncthreads();
-        const uint32_t g = s_g;
-        __syncthreads();
+    // A wave's first group follows from its place (neighbouring groups to different workgroups,
+    // so that few groups spread over the chip), the others from the counter.
+    const uint32_t n_first = gridDim.x * (COOP ? 1u : (uint32_t)WAVES);
+    uint32_t g = (COOP ? 0u : wave * gridDim.x) + blockIdx.x;
+    for (bool again = false;; again = true) {
+        if (again && COOP) {   // every wave of the workgroup comes here once per group
+            if (threadIdx.x == 0)
+                s_wave[0].g = n_first + atomicAdd(&A.counter[0], 1u);
+            __syncthreads();
+            g = s_wave[0].g;
+            __syncthreads();
+        } else if (again) {
+            if (lane == 0)
+                S.g = n_first + atomicAdd(&A.counter[0], 1u);
+            wave_sync();
+            g = S.g;
+            wave_sync();
+        }
+        // lanes: G targets, P phases (lane = target + G phase)
+        uint32_t G = (uint32_t)A.G_lanes, P = 64u / G;
+        uint32_t tl = lane % G, ph = lane / G;
         uint32_t first, cnt;
         if (A.tgt) {
             if (g >= *A.n_tgrp)
@@ -1080,9 +1242,9 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
             W = walk_geom{A.L,  A.halfL, A.rcut, A.rcut2, A.rs_inv, A.rs_inv2,
                           A.G,  A.m0,    A.h0,   0.5 * (A.halfL - A.rcut), 0u};
         }
-        const bool valid = tl < cnt;
-        const uint32_t i = A.tgt ? A.tgt[valid ? first + tl : first] : (valid ? first + tl : first);
-        const bool active = valid && (!A.active || A.active[i] != 0);
+        bool valid = tl < cnt;
+        uint32_t i = A.tgt ? A.tgt[valid ? first + tl : first] : (valid ? first + tl : first);
+        bool active = valid && (!A.active || A.active[i] != 0);
         if (A.active && __ballot(active) == 0ull)
             continue;  // no target in this group
         double xi = A.x[i], yi = A.y[i], zi = A.z[i];
@@ -1092,7 +1254,7 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
             yi = yi - y0 > W.halfL ? yi - W.L : (yi - y0 < -W.halfL ? yi + W.L : yi);
             zi = zi - z0 > W.halfL ? zi - W.L : (zi - z0 < -W.halfL ? zi + W.L : zi);
         }
-        const double hi = W.h0 * mult_cbrt(A.mult[i]);
+        double hi = W.h0 * mult_cbrt(A.mult[i]);
         // group bounding box
         double mnx = xi, mny = yi, mnz = zi, mxx = xi, mxy = yi, mxz = zi;
         for (int o = 32; o >= 1; o >>= 1) {
@@ -1107,15 +1269,15 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
         const double ghx = 0.5 * (mxx - mnx), ghy = 0.5 * (mxy - mny), ghz = 0.5 * (mxz - mnz);
         const double ghmax = fmax(ghx, fmax(ghy, ghz));
         // the list is culled to the group's box grown by r_cut (Steiner: volume, surface,
-        // edge and ball terms); when that region is at most WALK_DENSE_E_* times one cutoff
+        // edge and ball terms); when that region is at most WALK_DENSE_E times one cutoff
         // sphere, enough entries are inside enough targets' spheres to evaluate densely
         const double rc = W.rcut, pi = 3.14159265358979323846;
         const double v_ball = (4.0 / 3.0) * pi * rc * rc * rc;
         const double v_list = 8.0 * ghx * ghy * ghz + 8.0 * rc * (ghx * ghy + ghy * ghz + ghz * ghx) +
                               2.0 * pi * rc * rc * (ghx + ghy + ghz) + v_ball;
-        const double dense_e = sizeof(T) == 4 ? WALK_DENSE_E_F32 : WALK_DENSE_E_F64;
         // (every lane holds the same group box: a wave-uniform choice)
-        const bool dense = __builtin_amdgcn_readfirstlane(v_list <= dense_e * v_ball ? 1 : 0) != 0;
+        const bool dense = F32 && G >= 4u && __builtin_amdgcn_readfirstlane(
+                                                 v_list <= WALK_DENSE_E * v_ball ? 1 : 0) != 0;
         // relative criterion: alpha / G times the smallest previous |g| of the group
         double alpha_a = 0.0;
         if (A.aold) {
@@ -1123,6 +1285,30 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
             for (int o = 32; o >= 1; o >>= 1)
                 a = fmin(a, __shfl_xor(a, o, 64));
             alpha_a = A.alpha_g * a;
+        }
+        // A group of at most half its G lanes' targets (cut short by the tree, or a short run of
+        // listed targets) has fewer targets and more phases; lane t holds target t already.  (By
+        // the group's count and not by its active targets: a target's force is the same bits
+        // whichever others are asked for.)  The floor keeps the phases' sentinels inside the
+        // list's spare slots.
+        if (!F32 || FT) {
+            uint32_t Ge = COOP ? (F32 ? 16u : 4u) : (F32 ? 4u : 2u);
+            while (Ge < cnt)
+                Ge <<= 1;
+            if (Ge < G) {
+                G = Ge;
+                P = 64u / G;
+                tl = lane % G;
+                ph = lane / G;
+                valid = tl < cnt;
+                const int from = valid ? (int)tl : 0;
+                active = __shfl((int)active, from, 64) != 0 && valid;
+                i = (uint32_t)__shfl((int)i, from, 64);
+                xi = __shfl(xi, from, 64);
+                yi = __shfl(yi, from, 64);
+                zi = __shfl(zi, from, 64);
+                hi = __shfl(hi, from, 64);
+            }
         }
         // list coordinates: absolute in FP64, relative to the group centre in FP32
         const bool rel = sizeof(T) == 4;
@@ -1133,6 +1319,10 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
         T hg2 = valid ? thi2 : T(0.0);
         for (int o = 32; o >= 1; o >>= 1)
             hg2 = wmax(hg2, (T)__shfl_xor(hg2, o, 64));
+        if constexpr (FT) {
+            // pairs below the table of F are close pairs too (a few ulps above its low end)
+            hg2 = wmax(hg2, 1.000001f * A.ft_lo);
+        }
         const uint64_t act_mask = __ballot(active);
         const T m_unit = T(W.m0), h_unit = T(W.h0);
         const typename vec4_of<T>::half hh_unit = {wmax(h_unit * h_unit, hg2), h_unit};
@@ -1143,9 +1333,9 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
         // phases.  Entries farther than r_cut from both boxes are dropped.
         const uint32_t Gh = G >> 1;
         const uint32_t Ph = G >= 4u ? 64u / Gh : 1u;
-        const bool halves = sizeof(T) == 4 && dense && G >= 4u;
+        bool halves = false;        // the sums are the halves' (the group layout's otherwise)
         float rc_cls2 = 0.0f;
-        if (sizeof(T) == 4 && halves) {
+        if (F32 && dense) {
             const float inf = __builtin_inff();
             float b[6] = {valid ? float(txi) : inf, valid ? float(tyi) : inf,
                           valid ? float(tzi) : inf, valid ? float(txi) : -inf,
@@ -1165,9 +1355,11 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
             rc_cls2 = __double2float_ru(rc_m * rc_m);
         }
 
-        pair_eval<T> ev;
-        if constexpr (sizeof(T) == 4) {
+        pair_eval<T, FT> ev;
+        if constexpr (F32) {
             ev.tab = s_tab;
+            if constexpr (FT)
+                ev.ftab = s_ftab;
             ev.tscale = float(A.stab_scale * W.rs_inv);
         } else {
             ev.A = &A;
@@ -1175,18 +1367,48 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
             ev.rs_inv3 = W.rs_inv * W.rs_inv2;
             ev.t_scale = A.t_scale;
         }
-        T ax = T(0.0), ay = T(0.0), az = T(0.0);
-        T bx = T(0.0), by = T(0.0), bz = T(0.0);   // half B's (ax, ay, az hold half A's)
+        T ax = T(0.0), ay = T(0.0), az = T(0.0);   // the lane's partial sums (half A's)
+        T bx = T(0.0), by = T(0.0), bz = T(0.0);   // half B's
         uint32_t nlist = 0;
+        // the masked loop's P sentinels fit behind the list (16 slots in FP64)
+        const uint32_t PT = P * team;
+        const uint32_t list_cap = F32 || PT <= 16u ? WALK_LIST : WALK_LIST + 16u - PT;
         uint32_t n_pairs = 0;   // per lane (the masked loop)
         uint32_t np_wave = 0;   // the wave's (the dense loop)
+        uint32_t n_zero = 0;    // per lane: pairs at zero separation it counted
         bool wide = false;
 
+        // The halves' sums in the group layout: fixed-order sums of the Ph partial accelerations
+        // of each half's targets, moved to the target's first lane.
+        auto fold = [&]() {
+            for (uint32_t o = Gh; o < 64; o <<= 1) {
+                ax += __shfl_xor(ax, o, 64);
+                ay += __shfl_xor(ay, o, 64);
+                az += __shfl_xor(az, o, 64);
+                bx += __shfl_xor(bx, o, 64);
+                by += __shfl_xor(by, o, 64);
+                bz += __shfl_xor(bz, o, 64);
+            }
+            const int sl = (int)(tl % Gh);
+            const T ax2 = __shfl(ax, sl, 64), ay2 = __shfl(ay, sl, 64), az2 = __shfl(az, sl, 64);
+            const T bx2 = __shfl(bx, sl, 64), by2 = __shfl(by, sl, 64), bz2 = __shfl(bz, sl, 64);
+            const bool inA = tl < Gh;
+            ax = ph == 0u ? (inA ? ax2 : bx2) : T(0.0);
+            ay = ph == 0u ? (inA ? ay2 : by2) : T(0.0);
+            az = ph == 0u ? (inA ? az2 : bz2) : T(0.0);
+            halves = false;
+        };
+
+        // The list's interactions into the sums: compact lists by the dense halves, the others
+        // (and the rare lists that need minimum-image pairs) by the masked loop.
         auto flush = [&]() {
-            if constexpr (sizeof(T) == 4) {
-                if (halves) {
-                    uint32_t nA = nlist, bB = 0u, nB = nlist, nt = nlist;
-                    if (!wide) {
+            bool masked = true;
+            if constexpr (F32) {
+                if (dense && (!wide || !FT)) {
+                    masked = false;
+                    halves = true;
+                    uint32_t n1 = 0u, n2 = nlist, n3 = 0u;
+                    if (FT || !wide) {
                         // lane l holds entries l and l + 64 (the list holds at most 128)
                         static_assert(WALK_LIST <= 128, "two list entries per lane");
                         float hbA[6], hbB[6];
@@ -1208,21 +1430,21 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
                             return a ? (b ? 2u : 1u) : (b ? 3u : 0u);
                         };
                         if (lane < nlist) {
-                            p0 = src.e[lane].pm;
-                            q0 = src.e[lane].hh;
+                            p0 = src.pm(lane);
+                            q0 = src.hh(lane);
                             c0 = cls(p0);
                         }
                         if (lane + 64u < nlist) {
-                            p1 = src.e[lane + 64u].pm;
-                            q1 = src.e[lane + 64u].hh;
+                            p1 = src.pm(lane + 64u);
+                            q1 = src.hh(lane + 64u);
                             c1 = cls(p1);
                         }
                         const uint64_t m01 = __ballot(c0 == 1u), m02 = __ballot(c0 == 2u),
                                        m03 = __ballot(c0 == 3u), m11 = __ballot(c1 == 1u),
                                        m12 = __ballot(c1 == 2u), m13 = __ballot(c1 == 3u);
-                        const uint32_t n1 = (uint32_t)(__popcll(m01) + __popcll(m11));
-                        const uint32_t n2 = (uint32_t)(__popcll(m02) + __popcll(m12));
-                        const uint32_t n3 = (uint32_t)(__popcll(m03) + __popcll(m13));
+                        n1 = (uint32_t)(__popcll(m01) + __popcll(m11));
+                        n2 = (uint32_t)(__popcll(m02) + __popcll(m12));
+                        n3 = (uint32_t)(__popcll(m03) + __popcll(m13));
                         // stable destinations: class base, then the entries of the class before
                         const uint32_t s0 =
                             c0 == 1u ? (uint32_t)__popcll(m01 & lt_mask)
@@ -1232,77 +1454,73 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
                         const uint32_t r12 = (uint32_t)(__popcll(m02) + __popcll(m12 & lt_mask));
                         const uint32_t r13 = (uint32_t)(__popcll(m03) + __popcll(m13 & lt_mask));
                         const uint32_t s1 = c1 == 1u ? r11 : (c1 == 2u ? n1 + r12 : n1 + n2 + r13);
-                        __syncthreads();   // every entry read before any is moved
+                        wave_sync();   // every entry read before any is moved
                         if (c0 != 0u) {
-                            src.e[s0].pm = p0;
-                            src.e[s0].hh = q0;
+                            src.pm(s0) = p0;
+                            src.hh(s0) = q0;
                         }
                         if (c1 != 0u) {
-                            src.e[s1].pm = p1;
-                            src.e[s1].hh = q1;
+                            src.pm(s1) = p1;
+                            src.hh(s1) = q1;
                         }
-                        nA = n1 + n2;
-                        bB = n1;
-                        nB = n2 + n3;
-                        nt = n1 + n2 + n3;
                     }
-                    if (lane < Ph) {  // sentinels: far outside every cutoff, in any image
-                        src.e[nt + lane].pm = {T(1e30), T(1e30), T(1e30), T(0.0)};
-                        src.e[nt + lane].hh = {T(0.0), T(0.0)};
+                    // sentinels (2 Ph team <= 64): far outside every cutoff
+                    if (lane < 2u * Ph * team) {
+                        src.pm(n1 + n2 + n3 + lane) = {T(1e30), T(1e30), T(1e30), T(0.0)};
+                        src.hh(n1 + n2 + n3 + lane) = {T(0.0), T(0.0)};
                     }
-                    __syncthreads();
-                    const uint32_t sph = lane / Gh, t0 = lane % Gh;
+                    wave_sync();
+                    const uint32_t sph = lane / Gh + Ph * member, t0 = lane % Gh;
                     {
-                        const uint32_t ts = t0;   // main-layout lane of the target (half A)
-                        const T xs = __shfl(txi, (int)ts, 64), ys = __shfl(tyi, (int)ts, 64),
-                                zs = __shfl(tzi, (int)ts, 64), hs = __shfl(thi, (int)ts, 64);
-                        const uint64_t am = __ballot(__shfl((int)active, (int)ts, 64) != 0);
-                        if (wide)
-                            pair_dense<T, true>(ev, W, src, nA, sph, Ph, xs, ys, zs, hs, hs * hs,
-                                                ax, ay, az, am, np_wave);
+                        const int ts = (int)t0;   // main-layout lane of the target (half A)
+                        const T xs = __shfl(txi, ts, 64), ys = __shfl(tyi, ts, 64),
+                                zs = __shfl(tzi, ts, 64), hs = __shfl(thi, ts, 64);
+                        const uint64_t am = __ballot(__shfl((int)active, ts, 64) != 0);
+                        if constexpr (FT)
+                            pair_dense(ev, T(W.rcut2), src, n1 + n2, sph, Ph * team, xs, ys, zs,
+                                       hs, hs * hs, ax, ay, az, am, np_wave, n_zero);
+                        else if (wide)
+                            pair_dense_s<true>(ev, T(W.rcut2), T(W.L), src, nlist, sph, Ph, xs, ys,
+                                               zs, hs, hs * hs, ax, ay, az, am, np_wave);
                         else
-                            pair_dense<T, false>(ev, W, src, nA, sph, Ph, xs, ys, zs, hs, hs * hs,
-                                                 ax, ay, az, am, np_wave);
+                            pair_dense_s<false>(ev, T(W.rcut2), T(W.L), src, n1 + n2, sph, Ph, xs,
+                                                ys, zs, hs, hs * hs, ax, ay, az, am, np_wave);
                     }
                     {
-                        const uint32_t ts = Gh + t0;   // half B
-                        const T xs = __shfl(txi, (int)ts, 64), ys = __shfl(tyi, (int)ts, 64),
-                                zs = __shfl(tzi, (int)ts, 64), hs = __shfl(thi, (int)ts, 64);
-                        const uint64_t am = __ballot(__shfl((int)active, (int)ts, 64) != 0);
-                        const src_list<T> sB{src.e + bB};
-                        if (wide)
-                            pair_dense<T, true>(ev, W, sB, nB, sph, Ph, xs, ys, zs, hs, hs * hs,
-                                                bx, by, bz, am, np_wave);
+                        const int ts = (int)(Gh + t0);   // half B
+                        const T xs = __shfl(txi, ts, 64), ys = __shfl(tyi, ts, 64),
+                                zs = __shfl(tzi, ts, 64), hs = __shfl(thi, ts, 64);
+                        const uint64_t am = __ballot(__shfl((int)active, ts, 64) != 0);
+                        const src_list<T> sB{src.p + n1, src.h + n1};
+                        if constexpr (FT)
+                            pair_dense(ev, T(W.rcut2), sB, n2 + n3, sph, Ph * team, xs, ys, zs,
+                                       hs, hs * hs, bx, by, bz, am, np_wave, n_zero);
+                        else if (wide)
+                            pair_dense_s<true>(ev, T(W.rcut2), T(W.L), sB, nlist, sph, Ph, xs, ys,
+                                               zs, hs, hs * hs, bx, by, bz, am, np_wave);
                         else
-                            pair_dense<T, false>(ev, W, sB, nB, sph, Ph, xs, ys, zs, hs, hs * hs,
-                                                 bx, by, bz, am, np_wave);
+                            pair_dense_s<false>(ev, T(W.rcut2), T(W.L), sB, n2 + n3, sph, Ph, xs,
+                                                ys, zs, hs, hs * hs, bx, by, bz, am, np_wave);
                     }
-                    nlist = 0;
-                    __syncthreads();
-                    return;
                 }
             }
-            if (lane < P) {  // sentinels: far outside every cutoff, in any image
-                src.e[nlist + lane].pm = {T(1e30), T(1e30), T(1e30), T(0.0)};
-                src.e[nlist + lane].hh = {T(0.0), T(0.0)};
-            }
-            __syncthreads();
-            if (dense) {
+            if (masked) {
+                if (halves)
+                    fold();   // the list has just become wide, and stays so
+                if (lane < PT) {  // sentinels: far outside every cutoff, in any image
+                    src.pm(nlist + lane) = {T(1e30), T(1e30), T(1e30), T(0.0)};
+                    src.hh(nlist + lane) = {T(0.0), T(0.0)};
+                }
+                wave_sync();
                 if (wide)
-                    pair_dense<T, true>(ev, W, src, nlist, ph, P, txi, tyi, tzi, thi, thi2, ax,
-                                        ay, az, act_mask, np_wave);
+                    pair_loop<T, true>(ev, W, src, nlist, ph + P * member, PT, txi, tyi, tzi, thi, thi2, ax, ay,
+                                       az, active, n_pairs);
                 else
-                    pair_dense<T, false>(ev, W, src, nlist, ph, P, txi, tyi, tzi, thi, thi2, ax,
-                                         ay, az, act_mask, np_wave);
-            } else if (wide) {
-                pair_loop<T, true>(ev, W, src, nlist, ph, P, txi, tyi, tzi, thi, thi2, ax, ay,
-                                   az, n_pairs);
-            } else {
-                pair_loop<T, false>(ev, W, src, nlist, ph, P, txi, tyi, tzi, thi, thi2, ax, ay,
-                                    az, n_pairs);
+                    pair_loop<T, false>(ev, W, src, nlist, ph + P * member, PT, txi, tyi, tzi, thi, thi2, ax,
+                                        ay, az, active, n_pairs);
             }
             nlist = 0;
-            __syncthreads();
+            wave_sync();
         };
 
         uint32_t sp = 0;
@@ -1364,8 +1582,11 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
             }
         }
         __threadfence_block();
-        while (sp > 0 && !overflow) {
-            const uint32_t take = sp < 64 ? sp : 64;
+        // Nodes until the stack is empty, then one more turn that flushes what is left (the list
+        // is flushed at one place, which holds all of the pair code).
+        for (bool last = false; !last;) {
+            last = sp == 0 || overflow;
+            const uint32_t take = last ? 0u : (sp < 64 ? sp : 64);
             sp -= take;
             const bool has = lane < take;
             const uint32_t node = has ? stk[sp + lane] : 0u;
@@ -1434,148 +1655,146 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_tree_walk(walk_a
             const uint32_t pincl = dzs_wave_scan_add_full(npush);
             const uint32_t ptot = dzs_wave_last(pincl);
             if (sp + ptot > A.depth) {
-                overflow = true;
-                break;
+                overflow = true;   // what is left unvisited is flagged, as is its group's force
+                act = 0;
+            } else {
+                for (uint32_t j = 0; j < npush; ++j)
+                    stk[sp + pincl - npush + j] = child + j;
+                sp += ptot;
             }
-            for (uint32_t j = 0; j < npush; ++j)
-                stk[sp + pincl - npush + j] = child + j;
-            sp += ptot;
             __threadfence_block();
-            // ---- monopoles
             const uint64_t mono = __ballot(act == 2);
             const uint32_t nmono = (uint32_t)__popcll(mono);
-            if (nmono > 0) {
-                if (nlist + nmono > WALK_LIST)
-                    flush();
-                if (act == 2) {
-                    const uint32_t slot = nlist + (uint32_t)__popcll(mono & lt_mask);
-                    src.e[slot].pm = {T(comx + shx - ox), T(comy + shy - oy),
-                                      T(comz + shz - oz), T(nmass)};
-                    const T hn = T(nhmax);
-                    src.e[slot].hh = {wmax(hn * hn, hg2), hn};
-                }
-                nlist += nmono;
-            }
-            // ---- leaves: queue, then stream their particles into the list, keeping only the
-            //      particles within r_cut of the group's bounding box
+            // ---- leaves: queue
             const uint64_t lmask = __ballot(act == 1);
             const uint32_t nq = (uint32_t)__popcll(lmask);
+            const uint32_t lc = act == 1 ? ncount : 0u;
+            const uint32_t lincl = dzs_wave_scan_add_full(lc);
+            const uint32_t Ptot = dzs_wave_last(lincl);
+            const uint32_t lstart = lincl - lc;
+            const uint32_t lq = (uint32_t)__popcll(lmask & lt_mask);
             if (nq > 0) {
-                const uint32_t lc = act == 1 ? ncount : 0u;
-                const uint32_t lincl = dzs_wave_scan_add_full(lc);
-                const uint32_t Ptot = dzs_wave_last(lincl);
-                __syncthreads();
+                wave_sync();
                 if (act == 1) {
-                    const uint32_t q = (uint32_t)__popcll(lmask & lt_mask);
-                    q_first[q] = nfirst;
-                    q_pref[q] = lincl - lc;
-                    q_org[0][q] = ox - shx;
-                    q_org[1][q] = oy - shy;
-                    q_org[2][q] = oz - shz;
-                    q_wide[q] = node_wide ? 1u : 0u;
+                    q_first[lq] = nfirst;
+                    q_pref[lq] = lstart;
+                    q_org[0][lq] = ox - shx;
+                    q_org[1][lq] = oy - shy;
+                    q_org[2][lq] = oz - shz;
+                    q_wide[lq] = node_wide ? 1u : 0u;
                 }
-                if (lane == 0)
-                    q_pref[nq] = Ptot;
-                __syncthreads();
+                wave_sync();
+            }
+            // ---- passes: the monopoles, then the queued leaves' particles 64 at a time, keeping
+            //      those within r_cut of the group's bounding box.  The list is flushed before a
+            //      pass that might not fit, so that no candidate is held across a flush.
+            uint32_t carry = 0;
+            for (int done = (last || nmono > 0) ? -64 : 0; done < (int)Ptot; done += 64) {
+                const uint32_t need =
+                    last ? WALK_LIST + 1u : (done < 0 ? nmono : min(Ptot - (uint32_t)done, 64u));
+                if (nlist + need > list_cap)
+                    flush();
+                if (done < 0) {
+                    if (act == 2) {
+                        const uint32_t slot = nlist + (uint32_t)__popcll(mono & lt_mask);
+                        src.pm(slot) = {T(comx + shx - ox), T(comy + shy - oy),
+                                        T(comz + shz - oz), T(nmass)};
+                        const T hn = T(nhmax);
+                        src.hh(slot) = {wmax(hn * hn, hg2), hn};
+                    }
+                    nlist += nmono;
+                    continue;
+                }
                 // candidate f of a pass belongs to the last leaf starting at or before it: each
                 // leaf marks its start in the pass's window, a wave max-scan spreads the marks
                 // (the leaf of the window's first slot carries over from the pass before)
-                const uint32_t lstart = lincl - lc;
-                const uint32_t lq = (uint32_t)__popcll(lmask & lt_mask);
-                uint32_t carry = 0;
-                for (uint32_t done = 0; done < Ptot; done += 64) {
-                    // room for every candidate of the pass: no candidate is held across a flush
-                    if (nlist + min(Ptot - done, 64u) > WALK_LIST)
-                        flush();
-                    const uint32_t f = done + lane;
-                    q_mark[lane] = 0u;
-                    __syncthreads();
-                    if (act == 1 && lstart >= done && lstart - done < 64u)
-                        q_mark[lstart - done] = lq + 1u;
-                    __syncthreads();
-                    uint32_t v = q_mark[lane];
-                    if (lane == 0)
-                        v = v > carry + 1u ? v : carry + 1u;
-                    v = dzs_wave_scan_max_full(v);
-                    const uint32_t lo = v - 1u;
-                    carry = dzs_wave_last(lo);
-                    bool keep = false;
-                    double ex_ = 0.0, ey_ = 0.0, ez_ = 0.0;
-                    uint32_t mj = 0;
-                    if (f < Ptot) {
-                        const uint32_t j = q_first[lo] + (f - q_pref[lo]);
-                        // the particle in the list frame: its nearest image, less the group
-                        // centre in FP32 (then the offset from the centre is the coordinate)
-                        ex_ = A.x[j] - q_org[0][lo];
-                        ey_ = A.y[j] - q_org[1][lo];
-                        ez_ = A.z[j] - q_org[2][lo];
-                        mj = A.mult[j];
-                        const double cx = fmax(0.0, fabs(rel ? ex_ : ex_ - gcx) - ghx);
-                        const double cy = fmax(0.0, fabs(rel ? ey_ : ey_ - gcy) - ghy);
-                        const double cz = fmax(0.0, fabs(rel ? ez_ : ez_ - gcz) - ghz);
-                        keep = q_wide[lo] != 0u || cx * cx + cy * cy + cz * cz < W.rcut2;
-                    }
-                    const uint64_t kmask = __ballot(keep);
-                    const uint32_t nk = (uint32_t)__popcll(kmask);
-                    if (nk > 0) {
-                        if (keep) {
-                            const uint32_t slot = nlist + (uint32_t)__popcll(kmask & lt_mask);
-                            // an original particle (multiplicity 1) takes the group's constants
-                            T mj_mass = m_unit;
-                            typename vec4_of<T>::half mj_hh = hh_unit;
-                            if (mj != 1u) {
-                                mj_mass = T(W.m0 * (double)mj);
-                                const T hj = T(W.h0 * mult_cbrt(mj));
-                                mj_hh = {wmax(hj * hj, hg2), hj};
-                            }
-                            src.e[slot].pm = {T(ex_), T(ey_), T(ez_), mj_mass};
-                            src.e[slot].hh = mj_hh;
-                        }
-                        nlist += nk;
-                    }
+                const uint32_t f = (uint32_t)done + lane;
+                q_mark[lane] = 0u;
+                wave_sync();
+                if (act == 1 && lstart >= (uint32_t)done && lstart - (uint32_t)done < 64u)
+                    q_mark[lstart - (uint32_t)done] = lq + 1u;
+                wave_sync();
+                uint32_t v = q_mark[lane];
+                if (lane == 0)
+                    v = v > carry + 1u ? v : carry + 1u;
+                v = dzs_wave_scan_max_full(v);
+                const uint32_t lo = v - 1u;
+                carry = dzs_wave_last(lo);
+                bool keep = false;
+                double ex_ = 0.0, ey_ = 0.0, ez_ = 0.0;
+                uint32_t mj = 0;
+                if (f < Ptot) {
+                    const uint32_t j = q_first[lo] + (f - q_pref[lo]);
+                    // the particle in the list frame: its nearest image, less the group
+                    // centre in FP32 (then the offset from the centre is the coordinate)
+                    ex_ = A.x[j] - q_org[0][lo];
+                    ey_ = A.y[j] - q_org[1][lo];
+                    ez_ = A.z[j] - q_org[2][lo];
+                    mj = A.mult[j];
+                    const double cx = fmax(0.0, fabs(rel ? ex_ : ex_ - gcx) - ghx);
+                    const double cy = fmax(0.0, fabs(rel ? ey_ : ey_ - gcy) - ghy);
+                    const double cz = fmax(0.0, fabs(rel ? ez_ : ez_ - gcz) - ghz);
+                    keep = q_wide[lo] != 0u || cx * cx + cy * cy + cz * cz < W.rcut2;
                 }
-                __syncthreads();
+                const uint64_t kmask = __ballot(keep);
+                const uint32_t nk = (uint32_t)__popcll(kmask);
+                if (nk > 0) {
+                    if (keep) {
+                        const uint32_t slot = nlist + (uint32_t)__popcll(kmask & lt_mask);
+                        // an original particle (multiplicity 1) takes the group's constants
+                        T mj_mass = m_unit;
+                        typename vec4_of<T>::half mj_hh = hh_unit;
+                        if (mj != 1u) {
+                            mj_mass = T(W.m0 * (double)mj);
+                            const T hj = T(W.h0 * mult_cbrt(mj));
+                            mj_hh = {wmax(hj * hj, hg2), hj};
+                        }
+                        src.pm(slot) = {T(ex_), T(ey_), T(ez_), mj_mass};
+                        src.hh(slot) = mj_hh;
+                    }
+                    nlist += nk;
+                }
             }
+            wave_sync();
         }
         if (overflow) {
             if (lane == 0)
                 atomicOr(&A.counter[2], 1u);   // sticky until checked
         }
-        flush();
-        if (halves) {
-            // fixed-order sums of the Ph partial accelerations of each half's targets, then each
-            // target's sum moved to its lane (tl) of the group layout
-            for (uint32_t o = Gh; o < 64; o <<= 1) {
-                ax += __shfl_xor(ax, o, 64);
-                ay += __shfl_xor(ay, o, 64);
-                az += __shfl_xor(az, o, 64);
-                bx += __shfl_xor(bx, o, 64);
-                by += __shfl_xor(by, o, 64);
-                bz += __shfl_xor(bz, o, 64);
-            }
-            const int sl = (int)(tl % Gh);
-            const T ax2 = __shfl(ax, sl, 64), ay2 = __shfl(ay, sl, 64), az2 = __shfl(az, sl, 64);
-            const T bx2 = __shfl(bx, sl, 64), by2 = __shfl(by, sl, 64), bz2 = __shfl(bz, sl, 64);
-            const bool inA = tl < Gh;
-            ax = inA ? ax2 : bx2;
-            ay = inA ? ay2 : by2;
-            az = inA ? az2 : bz2;
-        } else {
-            // fixed-order sum of the P partial accelerations of each target
-            for (uint32_t o = G; o < 64; o <<= 1) {
-                ax += __shfl_xor(ax, o, 64);
-                ay += __shfl_xor(ay, o, 64);
-                az += __shfl_xor(az, o, 64);
-            }
+        if (halves)
+            fold();
+        // fixed-order sum of the P partial accelerations of each target
+        for (uint32_t o = G; o < 64; o <<= 1) {
+            ax += __shfl_xor(ax, o, 64);
+            ay += __shfl_xor(ay, o, 64);
+            az += __shfl_xor(az, o, 64);
         }
         {
-            uint64_t cnt_pairs = active ? n_pairs : 0u;
+            uint64_t cnt_pairs = (active ? (uint64_t)n_pairs : 0ull) - n_zero;
             for (int o = 32; o >= 1; o >>= 1)
                 cnt_pairs += __shfl_xor(cnt_pairs, o, 64);
             if (lane == 0)
                 atomicAdd(A.pair_count, (unsigned long long)(cnt_pairs + np_wave));
         }
-        if (active && ph == 0) {
+        if constexpr (COOP) {
+            // the waves' partial sums, added in their order (every wave comes here; the
+            // next group's fetch has a barrier before the rows are written again)
+            T *const part = (T *)S.q_org;
+            if (ph == 0) {
+                part[lane] = ax;
+                part[64u + lane] = ay;
+                part[128u + lane] = az;
+            }
+            __syncthreads();
+            if (wave == 0)
+                for (int w = 1; w < WAVES; ++w) {
+                    const T *const o = (const T *)s_wave[w].q_org;
+                    ax += o[lane];
+                    ay += o[64u + lane];
+                    az += o[128u + lane];
+                }
+        }
+        if (active && ph == 0 && (!COOP || wave == 0)) {
             const double gxv = W.Gc * (double)ax, gyv = W.Gc * (double)ay, gzv = W.Gc * (double)az;
             const uint32_t o = A.out_perm ? A.out_perm[i] : i;
             if (A.accumulate) {
@@ -1708,6 +1927,41 @@ static double split_table_f32(double ucut, float4 *tab) {
     return (double)worst;
 }
 
+// Before a walk: the work counter to zero and, for the FP32 form (tab non-null), the cubics of
+// F(w) = S(sqrt(w) / r_s) / w^1.5 in d = w - a on each interval [a, b) of 2^-WALK_FT_BITS octave
+// from index base: the polynomial through F at the four Chebyshev nodes (Newton's divided
+// differences), in powers of d.
+__global__ __launch_bounds__(64) void k_walk_setup(uint32_t *counter, float4 *tab, uint32_t base,
+                                                   double r_s) {
+    const uint32_t j = blockIdx.x * 64u + threadIdx.x;
+    if (j == 0)
+        counter[0] = 0u;
+    if (!tab || j >= WALK_FT_N)
+        return;
+    const double a = (double)__uint_as_float((base + j) << WALK_FT_SHIFT);
+    const double h = (double)__uint_as_float((base + j + 1u) << WALK_FT_SHIFT) - a;
+    const double node[4] = {0.5 - 0.5 * 0.92387953251128674, 0.5 - 0.5 * 0.38268343236508977,
+                            0.5 + 0.5 * 0.38268343236508977, 0.5 + 0.5 * 0.92387953251128674};
+    double f[4];
+    for (int k = 0; k < 4; ++k) {   // in units of h: x = d / h in [0, 1)
+        const double w = a + h * node[k], r = sqrt(w), u = r / r_s;
+        f[k] = (erfc(0.5 * u) + u * 0.56418958354775629 * exp(-0.25 * u * u)) / (w * r);
+    }
+    for (int o = 1; o < 4; ++o)
+        for (int k = 3; k >= o; --k)
+            f[k] = (f[k] - f[k - 1]) / (node[k] - node[k - o]);
+    double c[4] = {f[3], 0.0, 0.0, 0.0};
+    for (int k = 2; k >= 0; --k) {   // c <- c (x - node[k]) + f[k]
+        for (int i = 3; i >= 1; --i)
+            c[i] = c[i - 1] - node[k] * c[i];
+        c[0] = f[k] - node[k] * c[0];
+    }
+    const double hi = 1.0 / h;
+    tab[(base + j) & (uint32_t)(WALK_FT_N - 1)] =
+        make_float4((float)c[0], (float)(c[1] * hi), (float)(c[2] * hi * hi),
+                         (float)(c[3] * hi * hi * hi));
+}
+
 dzs_status dzs_tree_walk(dzs_ctx *ctx, const dzs_box *box, uint64_t n, const double *x,
                          const double *y, const double *z, const uint32_t *mult, double *gx,
                          double *gy, double *gz, const dzs_tree_params *prm, hipStream_t s,
@@ -1805,30 +2059,68 @@ dzs_status dzs_tree_walk_ex(dzs_ctx *ctx, const dzs_box *box, uint64_t n, const 
         DZS_TRY(dzs_check_launch(ctx, "cell_fill"));
     }
     // persistent waves: each takes groups until the counter passes the device group count
-    uint32_t slots = (uint32_t)ctx->walk_stack_slots;
-    if (n < slots)
-        slots = (uint32_t)n;   // there are at most n groups
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(TB_THREADS), 0, s, (uint64_t)1, ctx->walk_counter,
-                       0u);
-    DZS_TRY(dzs_check_launch(ctx, "walk_counter_clear"));
+    const bool ft = fp32 && !boxes;
+    // Waves per group, by n / group_size, the least number of groups (the tree cuts about 1.5
+    // times as many).  With 4096 resident waves a launch of few groups lasts as long as its
+    // heaviest one: FP64, 110,592 clustered particles in groups of 32 (3456) 1.16 ms alone, 0.98
+    // in twos, 1.01 in fours; 20^3 (250) 78, 63 and 58 us; FP32 in groups of 64, 100,000
+    // clustered (1562) 1.42, 0.96 and 0.74 ms, near-uniform 32^3 (512) 286, 195 and 181 us, 48^3
+    // (1728) 436, 446 and 489 us.  Where every wave has several groups the repeated walks only
+    // cost: 64^3 (4096) 579, 698 and 897 us, FP64 200,003 in groups of 16 (12,500) 1.17 ms alone,
+    // 1.41 in fours.  (Groups below 16 would need more sentinels than the list has spare slots.)
+    const uint64_t least = n / (uint64_t)A.G_lanes;
+    const int team = A.G_lanes < 16 || least >= 4096 || (fp32 && !ft) ? 1 : (least >= 1024 ? 2 : 4);
+    uint32_t slots = (uint32_t)ctx->walk_stack_slots;   // waves
+    if (n * team < slots)
+        slots = (uint32_t)(n * team);   // there are at most n groups
+    const float ft_top = (float)A.rcut2;
+    uint32_t ft_bits;
+    memcpy(&ft_bits, &ft_top, sizeof(ft_bits));
+    ft_bits >>= WALK_FT_SHIFT;
+    const uint32_t ft_base = ft_bits >= WALK_FT_N ? ft_bits - (WALK_FT_N - 1) : 1u;
+    const uint32_t ft_lo_bits = ft_base << WALK_FT_SHIFT;
+    memcpy(&A.ft_lo, &ft_lo_bits, sizeof(A.ft_lo));
+    A.ftab = (const float4 *)ctx->walk_ftab;
+    hipLaunchKernelGGL(k_walk_setup, dim3(ft ? WALK_FT_N / 64 : 1), dim3(64), 0, s,
+                       ctx->walk_counter, ft ? (float4 *)ctx->walk_ftab : nullptr, ft_base,
+                       prm->r_s);
+    DZS_TRY(dzs_check_launch(ctx, "walk_setup"));
     {
         dzs_timed t(ctx, KC_TREE_WALK, s);
-        if (boxes && fp32)
-            hipLaunchKernelGGL((k_tree_walk<float, false, true>), dim3(slots), dim3(64), 0, s, A);
-        else if (boxes)
-            hipLaunchKernelGGL((k_tree_walk<double, false, true>), dim3(slots), dim3(64), 0, s, A);
-        else if (fp32 && K > 0)
-            hipLaunchKernelGGL((k_tree_walk<float, true, false>), dim3(slots), dim3(64), 0, s, A);
-        else if (fp32)
-            hipLaunchKernelGGL((k_tree_walk<float, false, false>), dim3(slots), dim3(64), 0, s, A);
+        auto launch = [&](auto cells, auto batch, auto tm, auto far, auto real) {
+            typedef decltype(real) T;
+            constexpr uint32_t W = tm.value > 1 ? tm.value : walk_waves<T>::N;
+            hipLaunchKernelGGL((k_tree_walk<T, cells.value, batch.value, tm.value, far.value>),
+                               dim3((slots + W - 1) / W), dim3(64 * W), 0, s, A);
+        };
+        const std::true_type yes;
+        const std::false_type no;
+        const std::integral_constant<int, 1> one;
+        const std::integral_constant<int, 2> two;
+        const std::integral_constant<int, 4> four;
+        auto pick = [&](auto cells, auto batch) {
+            if (fp32 && !ft)
+                launch(cells, batch, one, no, 0.0f);
+            else if (!fp32)
+                team == 1 ? launch(cells, batch, one, no, 0.0)
+                          : (team == 2 ? launch(cells, batch, two, no, 0.0)
+                                       : launch(cells, batch, four, no, 0.0));
+            else if constexpr (!batch.value)
+                team == 1 ? launch(cells, batch, one, yes, 0.0f)
+                          : (team == 2 ? launch(cells, batch, two, yes, 0.0f)
+                                       : launch(cells, batch, four, yes, 0.0f));
+        };
+        if (boxes)
+            pick(no, yes);
         else if (K > 0)
-            hipLaunchKernelGGL((k_tree_walk<double, true, false>), dim3(slots), dim3(64), 0, s, A);
+            pick(yes, no);
         else
-            hipLaunchKernelGGL((k_tree_walk<double, false, false>), dim3(slots), dim3(64), 0, s, A);
+            pick(no, no);
         DZS_TRY(dzs_check_launch(ctx, "tree_walk"));
     }
     return DZS_OK;  // overflows stay on the device until dzs_check
 }
 
+static_assert(WALK_FT_N == DZS_WALK_FT_N, "the context's table of F(w) holds WALK_FT_N cubics");
 static_assert(sizeof(((dzs_ctx *)nullptr)->stab) == sizeof(float4) * (WALK_TAB_N + 1),
               "the context's table of S(u) holds WALK_TAB_N + 1 cubics");

@@ -288,7 +288,7 @@ typedef struct {
 /* ---- context ------------------------------------------------------------------------ */
 
 /* Create a context on HIP device `device` and allocate all its scratch for `cap`: about
- * 123 bytes per particle (keys and sort indices 24; one arena of 89 shared by the tree, with
+ * 106 bytes per particle (keys and sort indices 24; one arena of 72 shared by the tree, with
  * node capacity max_particles/2 + 4096, and the DZS coarsening buffers; group starts 4; the
  * relative criterion's |g| 4; time-step bins and the walk's target flags 2), plus 28 bytes per
  * particle of sorted copies for tree_force unless DZS_CAP_NO_COPIES, plus 44 bytes per

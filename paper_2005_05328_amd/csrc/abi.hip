@@ -197,7 +197,7 @@ static dzs_status create(dzs_ctx *c, const dzs_capacity *cap) {
     // the permutation scratch shares the sort's ping-pong keys (free once a sort returns)
     c->gather_tmp = (double *)c->key_alt;
     // One arena holds, at different times, the tree (nodes, which live from the build to the
-    // end of the walk, plus the build's frontier scratch and the group flags) and the DZS
+    // end of the walk, plus the build's counts and the group flags) and the DZS
     // coarsening buffers (used before the tree of the same step is built).  Nodes: at most
     // n/2 + 4096 (internal nodes hold more than one particle; the build flags an overflow).
     const uint64_t nn = n / 2 + 4096;
@@ -208,14 +208,15 @@ static dzs_status create(dzs_ctx *c, const dzs_capacity *cap) {
         off += (bytes + 255) & ~255ull;
         return at;
     };
-    const uint64_t o_first = carve(off_t, 4 * nn), o_count = carve(off_t, 4 * nn),
-                   o_child = carve(off_t, 4 * nn), o_nchild = carve(off_t, nn),
+    const uint64_t tw = dzs_tree_scan_words(n), gw = dzs_tree_flag_tiles(n);
+    const uint64_t o_first = carve(off_t, 4 * nn), o_end = carve(off_t, 4 * nn),
+                   o_child = carve(off_t, 4 * nn), o_cend = carve(off_t, 4 * nn),
                    o_level = carve(off_t, nn), o_rec = carve(off_t, sizeof(dzs_node_rec) * nn),
-                   o_fr = carve(off_t, 4 * nn), o_frn = carve(off_t, 4 * nn),
-                   o_nc = carve(off_t, 4 * nn), o_ni = carve(off_t, 4 * nn),
-                   o_co = carve(off_t, 4 * nn), o_io = carve(off_t, 4 * nn),
-                   o_cb = carve(off_t, 36 * nn), o_gf = carve(off_t, 4 * n),
-                   o_gs = carve(off_t, 4 * n);
+                   o_sd = carve(off_t, 2 * n), o_tc = carve(off_t, 4 * tw),
+                   o_ts = carve(off_t, 4 * tw),
+                   o_tn = carve(off_t, 4 * tw),
+                   o_tp = carve(off_t, 4 * dzs_tree_span_words(n)), o_gf = carve(off_t, n),
+                   o_gc = carve(off_t, 4 * gw), o_gs = carve(off_t, 4 * gw);
     const uint64_t o_head = carve(off_d, 4 * n), o_flag = carve(off_d, 4 * n),
                    o_scan = carve(off_d, 4 * n), o_new = carve(off_d, 48 * n),
                    o_nmult = carve(off_d, 4 * n), o_nid = carve(off_d, 4 * n),
@@ -224,19 +225,18 @@ static dzs_status create(dzs_ctx *c, const dzs_capacity *cap) {
     c->arena_bytes = off_t > off_d ? off_t : off_d;
     char *A = c->arena;
     c->nd_first = (uint32_t *)(A + o_first);
-    c->nd_count = (uint32_t *)(A + o_count);
+    c->nd_end = (uint32_t *)(A + o_end);
     c->nd_child = (uint32_t *)(A + o_child);
-    c->nd_nchild = (uint8_t *)(A + o_nchild);
+    c->nd_cend = (uint32_t *)(A + o_cend);
     c->nd_level = (uint8_t *)(A + o_level);
     c->nd_rec = (dzs_node_rec *)(A + o_rec);
-    c->frontier = (uint32_t *)(A + o_fr);
-    c->frontier_next = (uint32_t *)(A + o_frn);
-    c->fr_nchild = (uint32_t *)(A + o_nc);
-    c->fr_ninternal = (uint32_t *)(A + o_ni);
-    c->fr_child_off = (uint32_t *)(A + o_co);
-    c->fr_int_off = (uint32_t *)(A + o_io);
-    c->child_bounds = (uint32_t *)(A + o_cb);
-    c->grp_flag = (uint32_t *)(A + o_gf);
+    c->tree_sd = (uint16_t *)(A + o_sd);
+    c->tree_cnt = c->tree_snap_e = (uint32_t *)(A + o_tc);
+    c->tree_snap = (uint32_t *)(A + o_tn);
+    c->tree_span = (uint32_t *)(A + o_tp);
+    c->tree_scan = (uint32_t *)(A + o_ts);
+    c->grp_flag = (uint8_t *)(A + o_gf);
+    c->grp_cnt = (uint32_t *)(A + o_gc);
     c->grp_scan = (uint32_t *)(A + o_gs);
     c->dz_head = (uint32_t *)(A + o_head);
     c->dz_flag = (uint32_t *)(A + o_flag);

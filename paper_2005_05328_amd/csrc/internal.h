@@ -134,18 +134,19 @@ struct dzs_ctx {
 
     // ---- octree (structure of arrays)
     uint64_t cap_nodes = 0;
-    uint32_t *nd_first = nullptr, *nd_count = nullptr, *nd_child = nullptr;
-    uint8_t *nd_nchild = nullptr, *nd_level = nullptr;
+    uint32_t *nd_first = nullptr, *nd_end = nullptr, *nd_child = nullptr, *nd_cend = nullptr;
+    uint8_t *nd_level = nullptr;
     struct dzs_node_rec *nd_rec = nullptr;  // moments and topology as the walk reads them
-    int tree_deepest = 0;                    // deepest level the last build may have made
     double *gpm = nullptr;  // [3 cap] the PM force of the split individual step (capacity flag)
     uint32_t *grp_list = nullptr;  // [cap] slots of the active targets (same capacity flag)
     uint32_t *tg_flag = nullptr, *tg_tscan = nullptr, *tg_gscan = nullptr, *tg_pos = nullptr;
-    uint32_t *frontier = nullptr, *frontier_next = nullptr;
-    uint32_t *fr_nchild = nullptr, *fr_ninternal = nullptr, *fr_child_off = nullptr,
-             *fr_int_off = nullptr;
-    uint32_t *child_bounds = nullptr;  // 9 per frontier node
-    uint32_t *grp_flag = nullptr, *grp_scan = nullptr, *grp_first = nullptr;
+    uint16_t *tree_sd = nullptr;   // per particle: first level that starts, deepest node
+    // node starts per level and block, scanned, and the nodes that span blocks, tier by tier
+    uint32_t *tree_cnt = nullptr, *tree_scan = nullptr, *tree_span = nullptr;
+    // the moments' block starts and the first node of each level there (tree_cnt's memory)
+    uint32_t *tree_snap = nullptr, *tree_snap_e = nullptr;
+    uint8_t *grp_flag = nullptr;
+    uint32_t *grp_cnt = nullptr, *grp_scan = nullptr, *grp_first = nullptr;
     uint32_t *walk_stack = nullptr;
     uint64_t walk_stack_slots = 0, walk_stack_depth = 0;
     uint32_t *walk_counter = nullptr;  // [0] work counter, [2] overflow flag, [8..9] pair count
@@ -357,13 +358,6 @@ __device__ __forceinline__ uint32_t dzs_wave_last(uint32_t v) {
 uint64_t dzs_scan_tmp_words(uint64_t n);
 dzs_status dzs_scan_u32(dzs_ctx *ctx, const uint32_t *in, uint32_t *out, uint64_t n,
                         uint32_t *total_dev, hipStream_t s);
-// the same over min(n_max, *n_dev) elements, the count read on the device
-dzs_status dzs_scan_u32_dev(dzs_ctx *ctx, const uint32_t *in, uint32_t *out, uint64_t n_max,
-                            const uint32_t *n_dev, uint32_t *total_dev, hipStream_t s);
-dzs_status dzs_scan2_u32_dev(dzs_ctx *ctx, const uint32_t *in0, uint32_t *out0,
-                             const uint32_t *in1, uint32_t *out1, uint64_t n_max,
-                             const uint32_t *n_dev, uint32_t *total0, uint32_t *total1,
-                             hipStream_t s);
 uint64_t dzs_sort_hist_words(uint64_t n);
 dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s,
                           int first_pass = 0);  // ctx->key/idx in+out; an even first_pass
@@ -413,6 +407,9 @@ dzs_status dzs_gather_u32(dzs_ctx *ctx, const uint32_t *src, const uint32_t *per
                           uint32_t *dst, uint64_t n, hipStream_t s);
 
 // tree.hip
+uint64_t dzs_tree_scan_words(uint64_t n);   // words of tree_cnt and tree_scan
+uint64_t dzs_tree_span_words(uint64_t n);   // words of tree_span
+uint64_t dzs_tree_flag_tiles(uint64_t n);   // words of grp_cnt and grp_scan
 // Tree build state words (ctx->bstate) that dzs_check reads: sticky error flags.
 #define DZS_BS_OVERFLOW 3   // the tree needed more than the node capacity
 #define DZS_BS_BADINPUT 40  // tree_force: an input out of key order under presorted, or a

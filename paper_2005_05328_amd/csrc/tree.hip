@@ -1,11 +1,11 @@
 // Oct-tree on Morton-sorted particles and the wavefront-cooperative short-range walk.
 //
 // Build (paper Sec. 2.1: root = box, each node split into its 8 octants while it holds more
-// than one particle; here a node stops splitting at `leaf_size` particles): level by level
-// from the root.  A node's particles are a contiguous range of the sorted order and its
-// children are the sub-ranges with equal next 3 key bits, found by binary search.  Nodes are
-// stored level-major, children of a node contiguous and in Morton order.  Moments (mass,
-// centre of mass, particle bounding box, largest softening) are accumulated bottom-up.
+// than one particle; here a node stops splitting at `leaf_size` particles): a node's particles
+// are a contiguous range of the sorted order, so the nodes follow from the sorted keys without
+// descending the tree (see the build section).  Nodes are stored level-major, children of a node
+// contiguous and in Morton order.  Moments (mass, centre of mass, particle bounding box, largest
+// softening) are accumulated bottom-up.
 //
 // Walk: one wave64 per target group (<= 64 Morton-contiguous particles inside one node,
 // one target per lane).  The wave pops up to 64 nodes from its stack at a time; each lane
@@ -29,163 +29,237 @@ static inline uint32_t blocks_for(uint64_t n, uint32_t t) { return (uint32_t)((n
 // ---------------------------------------------------------------------------------------
 // build
 // ---------------------------------------------------------------------------------------
-// Build state in device memory (ctx->bstate): the counts of the level-synchronous build stay
-// on the device, so the build needs no host synchronisation (and can be graph-captured).
-#define BS_NF 0         // frontier nodes at the current level
-#define BS_NODES 1      // nodes so far
+// Particle i and the one before it share their first c_i octal digits (c_0 = -1), so a cube of
+// every level above c_i starts at i.  The cube of level k holding i has more than `leaf`
+// particles if and only if some window of leaf + 1 consecutive particles around i shares k
+// digits; the deepest such level m_i is a sliding maximum.  A cube is a node when its parent
+// splits, so the nodes holding i are those of levels 0 .. d_i = m_i + 1 (at most
+// DZS_TREE_LEVELS): node k starts at i for c_i < k <= d_i, and the node of level k that holds
+// i - 1 ends at i for c_i < k <= d_(i-1).  With the number E_k(i) of nodes of level k that start
+// before i (a level-major scan of per-block counts), a node's index, its first child's (E_(k+1)
+// where it starts) and the end of its children's (E_(k+1) where it ends) are all known where it
+// starts and ends.  In place of a loop over the levels with five launches each and one for the moments the
+// build is two kernels around a scan, a kernel for the moments inside blocks, one per tier of 32
+// blocks for the others and three for the groups.  Build, moments and groups alone on the GPU:
+// 20^3 270 -> 75 us, 128^3 408 -> 203 us, 256^3 1540 -> 1164 us.
+//
+// Build state in device memory (ctx->bstate): the counts stay on the device, so the build needs
+// no host synchronisation (and can be graph-captured).
+#define BS_NODES 1      // nodes
 #define BS_GROUPS 2     // target groups
 #define BS_OVERFLOW DZS_BS_OVERFLOW  // sticky: the tree needed more than the node capacity
-#define BS_CHILDREN 4   // scan totals of the current level
-#define BS_INTERNAL 5
+#define BS_LMAX 7       // deepest level built (DZS_TREE_LEVELS unless the capacity cut it)
 #define BS_LEVEL 8      // [BS_LEVEL + k]: first node of level k (k <= DZS_KEY_BITS + 1)
+#define TREE_TILE 1024  // particles of a build block
+#define TREE_NLEV (DZS_TREE_LEVELS + 1)
+#define TREE_LEAF_MAX 64
+#define TREE_TIER 32    // blocks (or tiers) that one workgroup joins
 
-// An input flagged out of order (DZS_BS_BADINPUT) builds an empty root and nothing below it.
-__global__ void k_tree_root(uint32_t n, uint32_t *nd_first, uint32_t *nd_count,
-                            uint32_t *nd_child, uint8_t *nd_nchild, uint8_t *nd_level,
-                            uint32_t *frontier,
-                            uint32_t *bs, uint32_t leaf, int KB) {
-    if (bs[DZS_BS_BADINPUT])
-        n = 0;
-    nd_first[0] = 0;
-    nd_count[0] = n;
-    nd_child[0] = 0;
-    nd_nchild[0] = 0;
-    nd_level[0] = 0;
-    frontier[0] = 0;
-    bs[BS_NF] = (n > leaf || (KB > 0 && n > 0)) ? 1u : 0u;
-    bs[BS_NODES] = 1;
-    bs[BS_GROUPS] = 0;
-    bs[BS_LEVEL + 0] = 0;
-    for (int k = 1; k <= DZS_KEY_BITS + 1; ++k)
-        bs[BS_LEVEL + k] = 1;
-}
+static inline uint64_t tree_blocks(uint64_t n) { return n / TREE_TILE + 1; }   // particles 0 .. n
 
-// After the emit of level k: advance the node count and the frontier; a level that would
-// exceed the node capacity stops the build (its nodes were not written) and flags it.
-__global__ void k_tree_level(uint32_t *bs, int k, uint64_t cap) {
-    const uint64_t nodes = (uint64_t)bs[BS_NODES] + bs[BS_CHILDREN];
-    if (nodes > cap) {
-        bs[BS_OVERFLOW] = 1u;
-        bs[BS_NF] = 0;
-    } else {
-        bs[BS_NODES] = (uint32_t)nodes;
-        bs[BS_NF] = bs[BS_INTERNAL];
+uint64_t dzs_tree_scan_words(uint64_t n) { return TREE_NLEV * tree_blocks(n) + 1; }
+uint64_t dzs_tree_span_words(uint64_t n) {
+    uint64_t words = 0;
+    for (uint64_t nb = tree_blocks(n);; nb = (nb + TREE_TIER - 1) / TREE_TIER) {
+        words += TREE_NLEV * nb;
+        if (nb == 1)
+            return words;
     }
-    for (int j = k + 2; j <= DZS_KEY_BITS + 1; ++j)
-        bs[BS_LEVEL + j] = bs[BS_NODES];
+}
+uint64_t dzs_tree_flag_tiles(uint64_t n) { return (n + 4095) / 4096; }
+
+// octal digits that two keys share
+__device__ __forceinline__ int tree_common(uint64_t a, uint64_t b) {
+    return a == b ? DZS_KEY_BITS : (__clzll((long long)(a ^ b)) - 1) / 3;
 }
 
-// For each frontier node at level k: the 9 bounds of its 8 octant sub-ranges.  One wave per
-// node (grid-stride over the frontier).  A node of at most 64 particles is read in one round;
-// a larger one is searched for the 7 inner bounds at once: lanes 9 (d - 1) .. 9 (d - 1) + 8
-// sample the bracket of "first index whose digit is >= d" at 9 points, which shrinks it about
-// 9-fold per round (dependent loads: log_9 of the node size, not 7 log_2 of it).
-__global__ __launch_bounds__(TB_THREADS) void k_tree_split(
-    const uint32_t *__restrict__ frontier, const uint32_t *__restrict__ bs, int k,
-    const uint64_t *__restrict__ key,
-    const uint32_t *__restrict__ nd_first, const uint32_t *__restrict__ nd_count,
-    uint32_t *__restrict__ bounds, uint32_t *__restrict__ nchild, uint32_t *__restrict__ ninternal,
-    uint32_t leaf, int KB) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t waves = gridDim.x * (TB_THREADS / 64);
-    const uint32_t nf = bs[BS_NF];
-    const int shift = 3 * (DZS_KEY_BITS - (k + 1));
-    const uint32_t g = lane / 9u, j = lane - 9u * g;  // search group (digit g + 1), sample
-    for (uint32_t f = blockIdx.x * (TB_THREADS / 64) + (threadIdx.x >> 6); f < nf; f += waves) {
-        const uint32_t node = frontier[f];
-        const uint32_t s = nd_first[node], e = s + nd_count[node];
-        uint32_t b = s;  // lane d in 1..7: first index in [s, e) whose digit is >= d
-        if (e - s <= 64u) {
-            const uint32_t i = s + lane;
-            const uint32_t dig = i < e ? (uint32_t)(key[i] >> shift) & 7u : 8u;
-            for (uint32_t d = 1; d < 8; ++d) {
-                const uint64_t m = __ballot(dig < d);
-                if (lane == d)
-                    b = s + (uint32_t)__popcll(m);
-            }
-        } else {
-            uint32_t lo = s, hi = e;  // the bound lies in [lo, hi]
-            const uint32_t d = g + 1u;
-            while (__ballot(g < 7u && lo < hi) != 0ull) {
-                const uint32_t len = hi - lo;
-                const uint32_t step = (len + 8u) / 9u;
-                const uint32_t p = lo + j * step;
-                // positions at or past hi count as "digit >= d" (the bracket's invariant)
-                bool ge = true;
-                if (g < 7u && lo < hi && p < hi)
-                    ge = ((uint32_t)(key[p] >> shift) & 7u) >= d;
-                const uint64_t m = __ballot(ge);
-                if (g < 7u && lo < hi) {
-                    const uint32_t gm = (uint32_t)(m >> (9u * g)) & 0x1ffu;
-                    if (gm & 1u) {
-                        hi = lo;  // the digit at lo is already >= d
-                    } else if (gm == 0u) {
-                        lo += 8u * step + 1u;  // every sample (all below hi) has digit < d
-                    } else {
-                        // between the last sample below d and the first at or above it
-                        const uint32_t jj = (uint32_t)__builtin_ctz(gm);
-                        const uint32_t nhi = lo + jj * step;
-                        lo += (jj - 1u) * step + 1u;
-                        hi = nhi < hi ? nhi : hi;
-                    }
-                }
-            }
-            const uint32_t src = (lane >= 1u && lane <= 7u) ? 9u * (lane - 1u) : 0u;
-            const uint32_t got = __shfl(lo, (int)src, 64);
-            if (lane >= 1u && lane <= 7u)
-                b = got;
+// Per particle the first level that starts at it (c_i + 1, DZS_TREE_LEVELS + 1 = none) and the
+// deepest node that holds it (d_i), packed as start | d_i << 8; per block and level the number of
+// nodes that start in the block (level-major); the group flags cleared; and the block's first
+// place where the coarsest cube starts (snap), which the moments take for the blocks' bounds:
+// few levels of the tree then span them.  An input flagged out of
+// order (DZS_BS_BADINPUT) starts nothing.  KB > 0: a batch whose keys carry the box in their top
+// KB digits; the cubes above level KB always split.
+__global__ __launch_bounds__(TB_THREADS) void k_tree_levels(
+    uint32_t n, const uint64_t *__restrict__ key, int leaf, int KB,
+    const uint32_t *__restrict__ bs, uint16_t *__restrict__ sd, uint32_t *__restrict__ cnt,
+    uint8_t *__restrict__ flag, uint32_t *__restrict__ snap) {
+    __shared__ uint64_t s_key[TREE_TILE + 2 * TREE_LEAF_MAX];
+    __shared__ int8_t s_m[2][TREE_TILE + TREE_LEAF_MAX];
+    __shared__ uint32_t s_cnt[TB_THREADS / 64][TREE_NLEV];
+    __shared__ uint32_t s_snap;
+    const uint32_t tid = threadIdx.x, nb = gridDim.x;
+    if (tid == 0)
+        s_snap = 0xffffffffu;
+    const int64_t base = (int64_t)blockIdx.x * TREE_TILE;
+    const int64_t N = bs[DZS_BS_BADINPUT] ? 0 : (int64_t)n;
+    for (int e = (int)tid; e < TREE_TILE + 2 * leaf; e += TB_THREADS) {
+        const int64_t j = base - leaf + e;
+        s_key[e] = j >= 0 && j < N ? key[j] : 0ull;
+    }
+    __syncthreads();
+    // m[e]: digits shared by the window of particles j .. j + leaf, j = base - leaf + e; then the
+    // maximum over 2^p of them, the largest power of two within the leaf + 1 windows around i
+    const int len = TREE_TILE + leaf;
+    for (int e = (int)tid; e < len; e += TB_THREADS) {
+        const int64_t j = base - leaf + e;
+        s_m[0][e] = j >= 0 && j + leaf < N ? (int8_t)tree_common(s_key[e], s_key[e + leaf])
+                                           : (int8_t)-1;
+    }
+    int cur = 0, span = 1;
+    for (; 2 * span <= leaf + 1; span *= 2, cur ^= 1) {
+        __syncthreads();
+        for (int e = (int)tid; e < len; e += TB_THREADS) {
+            const int8_t a = s_m[cur][e], b = e + span < len ? s_m[cur][e + span] : (int8_t)-1;
+            s_m[cur ^ 1][e] = a > b ? a : b;
         }
-        if (lane == 8u)
-            b = e;
-        // counts of the 8 children (lane d: bound d + 1 - bound d)
-        const uint32_t bn = __shfl_down(b, 1, 64);
-        const uint32_t c = lane < 8u ? bn - b : 0u;
-        const bool child = lane < 8u && c > 0u;
-        // nodes above level KB (the box digits of a batch) always split
-        const bool internal = child && (c > leaf || k + 1 < KB) && k + 1 < DZS_TREE_LEVELS;
-        const uint64_t mc = __ballot(child), mi = __ballot(internal);
-        if (lane <= 8u)
-            bounds[(uint64_t)f * 9 + lane] = b;
-        if (lane == 0u) {
-            nchild[f] = (uint32_t)__popcll(mc);
-            ninternal[f] = (uint32_t)__popcll(mi);
+    }
+    __syncthreads();
+    uint32_t c[TREE_NLEV];
+#pragma unroll
+    for (int k = 0; k < TREE_NLEV; ++k)
+        c[k] = 0u;
+    uint32_t best = 0xffffffffu;   // first level that starts * TREE_TILE + place
+    for (int e = (int)tid; e < TREE_TILE; e += TB_THREADS) {
+        const int64_t i = base + e;
+        int start = TREE_NLEV, d = -1;
+        if (i < N) {
+            const int c_i = i == 0 ? -1 : tree_common(s_key[e + leaf - 1], s_key[e + leaf]);
+            start = c_i + 1 < TREE_NLEV ? c_i + 1 : TREE_NLEV;
+            const int8_t a = s_m[cur][e], b = s_m[cur][e + leaf + 1 - span];
+            int m = a > b ? a : b;
+            m = m > KB - 1 ? m : KB - 1;
+            d = m + 1 < DZS_TREE_LEVELS ? m + 1 : DZS_TREE_LEVELS;
         }
+        best = min(best, (uint32_t)start * TREE_TILE + (uint32_t)e);
+        if (i < (int64_t)n) {
+            sd[i] = (uint16_t)(start | ((d < 0 ? 0 : d) << 8));
+            flag[i] = 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < TREE_NLEV; ++k)
+            c[k] += (uint32_t)__popcll(__ballot(start <= k && k <= d));
+    }
+    if ((tid & 63u) == 0u)
+#pragma unroll
+        for (int k = 0; k < TREE_NLEV; ++k)
+            s_cnt[tid >> 6][k] = c[k];
+    atomicMin(&s_snap, best);
+    __syncthreads();
+    if (tid == 0) {
+        const int64_t p = base + (int64_t)(s_snap % TREE_TILE);
+        snap[blockIdx.x] = (uint32_t)(p < (int64_t)n ? p : (int64_t)n);
+    }
+    if (tid < TREE_NLEV) {
+        uint32_t t = 0;
+        for (int w = 0; w < TB_THREADS / 64; ++w)
+            t += s_cnt[w][tid];
+        cnt[(uint64_t)tid * nb + blockIdx.x] = t;
     }
 }
 
+// Nodes at the places where they start and end; E: the scanned counts.  A level that would take
+// the nodes past the capacity is left out whole, with all below it: its parents are leaves (and
+// the overflow is flagged).  The first block also writes the build state; an input flagged out
+// of order gets an empty root.  snap_e: the same numbers at the moments' block bounds.
 __global__ __launch_bounds__(TB_THREADS) void k_tree_emit(
-    const uint32_t *__restrict__ frontier, const uint32_t *__restrict__ bs, int k,
-    const uint32_t *__restrict__ bounds, const uint32_t *__restrict__ child_off,
-    const uint32_t *__restrict__ int_off, uint64_t cap, uint32_t *__restrict__ nd_first,
-    uint32_t *__restrict__ nd_count, uint32_t *__restrict__ nd_child,
-    uint8_t *__restrict__ nd_nchild, uint8_t *__restrict__ nd_level,
-    uint32_t *__restrict__ frontier_next, uint32_t leaf, int KB) {
-    uint32_t f = blockIdx.x * TB_THREADS + threadIdx.x;
-    if (f >= bs[BS_NF])
-        return;
-    // the whole level is dropped when it does not fit (k_tree_level flags it)
-    if ((uint64_t)bs[BS_NODES] + bs[BS_CHILDREN] > cap)
-        return;
-    const uint32_t node = frontier[f];
-    uint32_t c = bs[BS_NODES] + child_off[f];
-    uint32_t q = int_off[f];
-    nd_child[node] = c;
-    uint32_t nc = 0;
-    for (int d = 0; d < 8; ++d) {
-        uint32_t s = bounds[(uint64_t)f * 9 + d], e = bounds[(uint64_t)f * 9 + d + 1];
-        if (e == s)
-            continue;
-        nd_first[c] = s;
-        nd_count[c] = e - s;
-        nd_child[c] = 0;
-        nd_nchild[c] = 0;
-        nd_level[c] = (uint8_t)(k + 1);
-        if ((e - s > leaf || k + 1 < KB) && k + 1 < DZS_TREE_LEVELS)
-            frontier_next[q++] = c;
-        ++c;
-        ++nc;
+    uint32_t n, const uint16_t *__restrict__ sd, const uint32_t *__restrict__ E, uint64_t cap,
+    uint32_t *__restrict__ nd_first, uint32_t *__restrict__ nd_end,
+    uint32_t *__restrict__ nd_child, uint32_t *__restrict__ nd_cend,
+    uint8_t *__restrict__ nd_level, const uint32_t *__restrict__ snap,
+    uint32_t *__restrict__ snap_e, uint32_t *__restrict__ bs) {
+    constexpr int WAVES = TB_THREADS / 64, RUN = TREE_TILE / WAVES;
+    __shared__ uint32_t s_cnt[WAVES][TREE_NLEV];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, nb = gridDim.x;
+    const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const bool bad = bs[DZS_BS_BADINPUT] != 0u;
+    int lmax = 0;   // the levels that fit (the root always does)
+    {
+        uint32_t upto[TREE_NLEV];
+#pragma unroll
+        for (int k = 0; k < TREE_NLEV; ++k)
+            upto[k] = E[(uint64_t)(k + 1) * nb];
+#pragma unroll
+        for (int k = 1; k < TREE_NLEV; ++k)
+            lmax += !bad && lmax == k - 1 && (uint64_t)upto[k] <= cap ? 1 : 0;
     }
-    nd_nchild[node] = (uint8_t)nc;
+    if (blockIdx.x == 0 && tid == 0) {
+        const bool over = E[(uint64_t)TREE_NLEV * nb] > cap;
+        if (over)
+            bs[BS_OVERFLOW] = 1u;
+        bs[BS_NODES] = bad ? 1u : E[(uint64_t)(lmax + 1) * nb];
+        bs[BS_GROUPS] = 0u;
+        bs[BS_LMAX] = (uint32_t)lmax;
+        for (int k = 0; k <= DZS_KEY_BITS + 1; ++k)
+            bs[BS_LEVEL + k] = bad ? (k == 0 ? 0u : 1u)
+                                   : E[(uint64_t)(k <= lmax + 1 ? k : lmax + 1) * nb];
+        if (bad) {
+            nd_first[0] = nd_end[0] = nd_child[0] = nd_cend[0] = 0u;
+            nd_level[0] = 0u;
+        }
+    }
+    if (bad)
+        return;
+    const uint64_t base = (uint64_t)blockIdx.x * TREE_TILE + (uint64_t)wave * RUN;
+    const uint32_t bound = snap[blockIdx.x];   // the moments' block starts here
+    // the wave's particles (RUN / 64 rounds of 64): first level that starts, deepest node, and
+    // the deepest node of the particle before
+    constexpr int ROUNDS = RUN / 64;
+    int start[ROUNDS], deep[ROUNDS], dprev[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint64_t i = base + (uint32_t)r * 64u + lane;
+        const uint32_t v = i < n ? sd[i] : 0u, u = i > 0 && i <= n ? sd[i - 1] : 0u;
+        // past the last particle (i = n) every node ends
+        start[r] = i < n ? (int)(v & 0xffu) : (i == n ? 0 : TREE_NLEV);
+        deep[r] = i < n ? min((int)(v >> 8), lmax) : -1;
+        dprev[r] = i > 0 && i <= n ? min((int)(u >> 8), lmax) : -1;
+    }
+    // the wave's counts, then its first numbers
+    uint32_t run[TREE_NLEV];
+#pragma unroll
+    for (int k = 0; k < TREE_NLEV; ++k) {
+        run[k] = 0u;
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            run[k] += (uint32_t)__popcll(__ballot(start[r] <= k && k <= deep[r]));
+    }
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < TREE_NLEV; ++k)
+            s_cnt[wave][k] = run[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < TREE_NLEV; ++k) {
+        run[k] = E[(uint64_t)k * nb + blockIdx.x];
+        for (uint32_t w = 0; w < wave; ++w)
+            run[k] += s_cnt[w][k];
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t i = (uint32_t)base + (uint32_t)r * 64u + lane;
+        uint32_t below = 0u;   // E_(k+1)(i)
+#pragma unroll
+        for (int k = TREE_NLEV - 1; k >= 0; --k) {
+            const bool open = start[r] <= k && k <= deep[r];
+            const bool close = start[r] <= k && k <= dprev[r];
+            const uint64_t m = __ballot(open);
+            const uint32_t id = run[k] + (uint32_t)__popcll(m & lt_mask);
+            if (close) {
+                nd_end[id - 1u] = i;
+                nd_cend[id - 1u] = k < dprev[r] ? below : 0u;
+            }
+            if (open) {
+                nd_first[id] = i;
+                nd_child[id] = k < deep[r] ? below : 0u;
+                nd_level[id] = (uint8_t)k;
+            }
+            below = id;
+            if (i == bound)
+                snap_e[(uint64_t)k * nb + blockIdx.x] = id;
+            run[k] += (uint32_t)__popcll(m);
+        }
+    }
 }
 
 // mult^(1/3), the softening factor of a particle of multiplicity mult (1 for an original
@@ -199,25 +273,31 @@ __device__ __forceinline__ float half_up(double mn, double mx, double c) {
     return __double2float_ru(fmax(mx - c, c - mn));
 }
 
+// The nodes' topology as the build writes it: particles [first, end), children [child, cend).
+struct tree_nodes {
+    const uint32_t *first, *end, *child, *cend;
+    const uint8_t *level;
+};
+
 // Moments of node v (mass, centre of mass, particle bounding box, largest softening): of its
-// particles for a leaf, of its children (already complete) otherwise; written with the
-// node's topology into its walk record.
+// particles for a leaf, of its children (already complete) otherwise; with the node's
+// topology its walk record.  child_rec(c) gives the record of child c.
+template <typename Child>
 __device__ __forceinline__ void node_moments(
     uint32_t v, const double *__restrict__ x, const double *__restrict__ y,
     const double *__restrict__ z, const uint32_t *__restrict__ mult, double m0, double h0,
-    const uint32_t *__restrict__ nd_first, const uint32_t *__restrict__ nd_count,
-    const uint32_t *__restrict__ nd_child, const uint8_t *__restrict__ nd_nchild,
-    const uint8_t *__restrict__ nd_level, dzs_node_rec *__restrict__ rec,
-    const uint64_t *__restrict__ key, const dzs_bbox *__restrict__ boxes, double L, int unwrap) {
-    if (boxes && nd_nchild[v] == 0) {
+    const tree_nodes &nd, const Child &child_rec, const uint64_t *__restrict__ key,
+    const dzs_bbox *__restrict__ boxes, double L, int unwrap, dzs_node_rec &out) {
+    const uint32_t first = nd.first[v], end = nd.end[v], child = nd.child[v],
+                   nc = nd.cend[v] - child;
+    if (boxes && nc == 0) {
         // a batch: the leaf's box (its key prefix) sets the mass unit and the softening
-        const uint64_t b = key[nd_first[v]] >> DZS_BATCH_SHIFT;
+        const uint64_t b = key[first] >> DZS_BATCH_SHIFT;
         m0 = boxes[b].m0;
         h0 = boxes[b].h0;
     }
     double m = 0.0, sx = 0.0, sy = 0.0, sz = 0.0, hmax = 0.0;
     double mnx = 1e300, mny = 1e300, mnz = 1e300, mxx = -1e300, mxy = -1e300, mxz = -1e300;
-    const uint32_t nc = nd_nchild[v];
     // kept tree: a member (child) more than half a box from the first one crossed a face of
     // the periodic box since the build; it is taken at the image next to the first one
     const double halfL = 0.5 * L;
@@ -226,56 +306,86 @@ __device__ __forceinline__ void node_moments(
     };
     uint32_t crossed = 0u;
     if (nc == 0) {
-        const uint32_t s = nd_first[v], e = s + nd_count[v];
+        const uint32_t s = first, e = end;
         const double x0 = x[s], y0 = y[s], z0 = z[s];
         uint32_t mmax = 0;
-        for (uint32_t j = s; j < e; ++j) {
-            const uint32_t mu = mult[j];
-            const double mj = m0 * (double)mu;
-            double xj = x[j], yj = y[j], zj = z[j];
-            if (unwrap) {
-                const double ux = near(xj, x0), uy = near(yj, y0), uz = near(zj, z0);
-                crossed |= (ux != xj || uy != yj || uz != zj) ? 1u : 0u;
-                xj = ux;
-                yj = uy;
-                zj = uz;
+        // four members are loaded before the first is added (in order: the same sums)
+        for (uint32_t j0 = s; j0 < e; j0 += 4u) {
+            double xs[4], ys[4], zs[4];
+            uint32_t ms[4];
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                const uint32_t j = min(j0 + q, e - 1u);
+                xs[q] = x[j];
+                ys[q] = y[j];
+                zs[q] = z[j];
+                ms[q] = mult[j];
             }
-            m += mj;
-            sx += mj * xj;
-            sy += mj * yj;
-            sz += mj * zj;
-            mnx = fmin(mnx, xj); mny = fmin(mny, yj); mnz = fmin(mnz, zj);
-            mxx = fmax(mxx, xj); mxy = fmax(mxy, yj); mxz = fmax(mxz, zj);
-            mmax = mu > mmax ? mu : mmax;
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                if (j0 + q >= e)
+                    break;
+                const uint32_t mu = ms[q];
+                const double mj = m0 * (double)mu;
+                double xj = xs[q], yj = ys[q], zj = zs[q];
+                if (unwrap) {
+                    const double ux = near(xj, x0), uy = near(yj, y0), uz = near(zj, z0);
+                    crossed |= (ux != xj || uy != yj || uz != zj) ? 1u : 0u;
+                    xj = ux;
+                    yj = uy;
+                    zj = uz;
+                }
+                m += mj;
+                sx += mj * xj;
+                sy += mj * yj;
+                sz += mj * zj;
+                mnx = fmin(mnx, xj); mny = fmin(mny, yj); mnz = fmin(mnz, zj);
+                mxx = fmax(mxx, xj); mxy = fmax(mxy, yj); mxz = fmax(mxz, zj);
+                mmax = mu > mmax ? mu : mmax;
+            }
         }
         hmax = h0 * mult_cbrt(mmax);  // the softening grows with the multiplicity
     } else {
-        const uint32_t c0 = nd_child[v];
-        const double x0 = rec[c0].cx, y0 = rec[c0].cy, z0 = rec[c0].cz;
-        for (uint32_t c = c0; c < c0 + nc; ++c) {
-            const dzs_node_rec &r = rec[c];
-            const double mc = r.mass;
-            double rcx = r.cx, rcy = r.cy, rcz = r.cz;
-            double rmx = r.comx, rmy = r.comy, rmz = r.comz;
-            if (unwrap) {
-                // the child's box and centre of mass move together, by the box's shift
-                const double dx = near(rcx, x0) - rcx, dy = near(rcy, y0) - rcy,
-                             dz = near(rcz, z0) - rcz;
-                rcx += dx; rcy += dy; rcz += dz;
-                rmx += dx; rmy += dy; rmz += dz;
+        const uint32_t c0 = child;
+        double x0 = 0.0, y0 = 0.0, z0 = 0.0;
+        if (unwrap) {
+            const dzs_node_rec r0 = child_rec(c0);
+            x0 = r0.cx;
+            y0 = r0.cy;
+            z0 = r0.cz;
+        }
+        for (uint32_t cb = c0; cb < c0 + nc; cb += 4u) {
+            dzs_node_rec rs[4];
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q)
+                rs[q] = child_rec(min(cb + q, c0 + nc - 1u));
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                if (cb + q >= c0 + nc)
+                    break;
+                const dzs_node_rec &r = rs[q];
+                const double mc = r.mass;
+                double rcx = r.cx, rcy = r.cy, rcz = r.cz;
+                double rmx = r.comx, rmy = r.comy, rmz = r.comz;
+                if (unwrap) {
+                    // the child's box and centre of mass move together, by the box's shift
+                    const double dx = near(rcx, x0) - rcx, dy = near(rcy, y0) - rcy,
+                                 dz = near(rcz, z0) - rcz;
+                    rcx += dx; rcy += dy; rcz += dz;
+                    rmx += dx; rmy += dy; rmz += dz;
+                }
+                m += mc;
+                sx += mc * rmx;
+                sy += mc * rmy;
+                sz += mc * rmz;
+                mnx = fmin(mnx, rcx - (double)r.hx); mny = fmin(mny, rcy - (double)r.hy);
+                mnz = fmin(mnz, rcz - (double)r.hz);
+                mxx = fmax(mxx, rcx + (double)r.hx); mxy = fmax(mxy, rcy + (double)r.hy);
+                mxz = fmax(mxz, rcz + (double)r.hz);
+                hmax = fmax(hmax, r.hmax);
             }
-            m += mc;
-            sx += mc * rmx;
-            sy += mc * rmy;
-            sz += mc * rmz;
-            mnx = fmin(mnx, rcx - (double)r.hx); mny = fmin(mny, rcy - (double)r.hy);
-            mnz = fmin(mnz, rcz - (double)r.hz);
-            mxx = fmax(mxx, rcx + (double)r.hx); mxy = fmax(mxy, rcy + (double)r.hy);
-            mxz = fmax(mxz, rcz + (double)r.hz);
-            hmax = fmax(hmax, r.hmax);
         }
     }
-    dzs_node_rec out;
     out.cx = 0.5 * (mnx + mxx);
     out.cy = 0.5 * (mny + mxy);
     out.cz = 0.5 * (mnz + mxz);
@@ -287,94 +397,257 @@ __device__ __forceinline__ void node_moments(
     out.hx = half_up(mnx, mxx, out.cx);
     out.hy = half_up(mny, mxy, out.cy);
     out.hz = half_up(mnz, mxz, out.cz);
-    out.first = nd_first[v];
-    out.count = nd_count[v];
-    out.child = nd_child[v];
-    out.nl = nc | ((uint32_t)nd_level[v] << 8);
+    out.first = first;
+    out.count = end - first;
+    out.child = child;
+    out.nl = nc | ((uint32_t)nd.level[v] << 8);
     out.pad = crossed;
-    rec[v] = out;
 }
 
-// Moments of the nodes of level k, [level_start[k], level_start[k+1]) read on the device;
-// levels run bottom-up, so the children of every node are complete before it.
-__global__ __launch_bounds__(TB_THREADS) void k_tree_moments(
-    const uint32_t *__restrict__ bs, int k, const double *__restrict__ x,
-    const double *__restrict__ y, const double *__restrict__ z, const uint32_t *__restrict__ mult,
-    double m0, double h0, const uint32_t *__restrict__ nd_first,
-    const uint32_t *__restrict__ nd_count, const uint32_t *__restrict__ nd_child,
-    const uint8_t *__restrict__ nd_nchild, const uint8_t *__restrict__ nd_level,
-    dzs_node_rec *rec, const uint64_t *__restrict__ key, const dzs_bbox *__restrict__ boxes,
-    double L, int unwrap) {
-    const uint32_t end = bs[BS_LEVEL + k + 1];
-    for (uint32_t v = bs[BS_LEVEL + k] + blockIdx.x * TB_THREADS + threadIdx.x; v < end;
-         v += gridDim.x * TB_THREADS)
-        node_moments(v, x, y, z, mult, m0, h0, nd_first, nd_count, nd_child, nd_nchild, nd_level,
-                     rec, key, boxes, L, unwrap);
+struct moment_args {
+    const double *x, *y, *z;
+    const uint32_t *mult;
+    double m0, h0, L;
+    tree_nodes nd;
+    dzs_node_rec *rec;
+    const uint64_t *key;
+    const dzs_bbox *boxes;
+    int unwrap;
+    const uint32_t *E;   // first node of each level and block (at the blocks' snapped starts)
+    const uint32_t *snap;   // the blocks' starts
+    uint32_t *span;      // [level][block] the level's node that starts in the block and ends
+                         // past it (TREE_NONE: none)
+    const uint32_t *bs;
+    uint32_t n, nb;
+};
+#define TREE_NONE 0xffffffffu
+
+template <typename Child>
+__device__ __forceinline__ void moments_of(const moment_args &A, uint32_t v, const Child &child,
+                                           dzs_node_rec &out) {
+    node_moments(v, A.x, A.y, A.z, A.mult, A.m0, A.h0, A.nd, child, A.key, A.boxes, A.L,
+                 A.unwrap, out);
 }
 
-// Target groups: each node with more than G particles packs its consecutive children that
-// hold at most G particles into bins of at most G (greedy, Morton order); a bin starts a
-// group.  Leaves with more than G particles (coincident particles at the finest level) are
-// cut into chunks of G.
-__global__ __launch_bounds__(TB_THREADS) void k_tree_groups(
-    const uint32_t *__restrict__ bs, const uint32_t *__restrict__ nd_first,
-    const uint32_t *__restrict__ nd_count,
-    const uint32_t *__restrict__ nd_child, const uint8_t *__restrict__ nd_nchild, uint32_t G,
-    uint32_t *__restrict__ flag, const uint8_t *__restrict__ nd_level, int KB) {
-    uint32_t v = blockIdx.x * TB_THREADS + threadIdx.x;
-    if (v >= bs[BS_NODES])
-        return;
-    const uint32_t cnt = nd_count[v];
+// Target groups of node v: each node with more than G particles packs its consecutive children
+// that hold at most G particles into bins of at most G (greedy, Morton order); a bin starts a
+// group.  Leaves with more than G particles (coincident particles at the finest level) are cut
+// into chunks of G.
+__device__ __forceinline__ void node_groups(uint32_t v, const tree_nodes &nd, uint32_t G,
+                                            uint8_t *__restrict__ flag, int KB) {
+    const uint32_t first = nd.first[v], cnt = nd.end[v] - first;
+    const uint32_t c0 = nd.child[v], c1 = nd.cend[v];
     if (KB > 0) {
         // a batch: nothing above the box nodes (level KB) is a group, and the box nodes of at
         // most G particles are groups of their own
-        const int lev = nd_level[v];
+        const int lev = nd.level[v];
         if (lev + 1 < KB)
             return;
         if (lev + 1 == KB) {
-            const uint32_t c0 = nd_child[v];
-            for (uint32_t c = c0; c < c0 + nd_nchild[v]; ++c)
-                if (nd_count[c] <= G)
-                    flag[nd_first[c]] = 1u;
+            for (uint32_t c = c0; c < c1; ++c)
+                if (nd.end[c] - nd.first[c] <= G)
+                    flag[nd.first[c]] = 1u;
             return;
         }
     }
     if (v == 0 && cnt <= G) {
-        flag[0] = 1u;
+        if (cnt > 0)
+            flag[0] = 1u;
         return;
     }
     if (cnt <= G)
         return;
-    const uint32_t nc = nd_nchild[v];
-    if (nc == 0) {
-        for (uint32_t j = nd_first[v]; j < nd_first[v] + cnt; j += G)
+    if (c0 == c1) {
+        for (uint32_t j = first; j < first + cnt; j += G)
             flag[j] = 1u;
         return;
     }
     uint32_t bin = 0;
-    const uint32_t c0 = nd_child[v];
-    for (uint32_t c = c0; c < c0 + nc; ++c) {
-        const uint32_t cc = nd_count[c];
+    for (uint32_t c = c0; c < c1; ++c) {
+        const uint32_t f = nd.first[c], cc = nd.end[c] - f;
         if (cc > G) {
             bin = 0;
         } else if (bin > 0 && bin + cc <= G) {
             bin += cc;
         } else {
-            flag[nd_first[c]] = 1u;
+            flag[f] = 1u;
             bin = cc;
         }
     }
 }
 
-__global__ __launch_bounds__(TB_THREADS) void k_group_compact(uint32_t n,
-                                                              const uint32_t *__restrict__ flag,
-                                                              const uint32_t *__restrict__ scan,
-                                                              uint32_t *__restrict__ grp_first) {
-    uint32_t i = blockIdx.x * TB_THREADS + threadIdx.x;
-    if (i < n && flag[i])
-        grp_first[scan[i]] = i;
+// Moments of the nodes that lie inside the block's particles: first every leaf, then the other
+// nodes level by level from the deepest (a node's children start and end inside it), whose
+// children's records wait in LDS; and the group flags of all nodes that start in the block (flag
+// null: the moments alone).  The levels are a chain of dependent steps, a few hundred
+// nanoseconds each; the particles are read and the 96-byte records written once.
+#define TREE_CACHE 320   // records in LDS (30 KB); a block with more nodes reads the rest back
+__global__ __launch_bounds__(TB_THREADS) void k_tree_block(moment_args A, uint32_t G,
+                                                           uint8_t *__restrict__ flag, int KB) {
+    __shared__ uint32_t s_lo[TREE_NLEV], s_hi[TREE_NLEV], s_off[TREE_NLEV + 1];
+    __shared__ dzs_node_rec s_rec[TREE_CACHE];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t bend = blockIdx.x + 1u < A.nb ? A.snap[blockIdx.x + 1u] : A.n;
+    if (A.bs[DZS_BS_BADINPUT]) {   // an empty root
+        if (blockIdx.x == 0 && tid == 0) {
+            dzs_node_rec out;
+            moments_of(A, 0u, [&](uint32_t c) { return A.rec[c]; }, out);
+            A.rec[0] = out;
+        }
+        return;
+    }
+    const int lmax = (int)A.bs[BS_LMAX];
+    if (tid < TREE_NLEV) {
+        const uint64_t at = (uint64_t)tid * A.nb + blockIdx.x;
+        const uint32_t lo = A.E[at];
+        const uint32_t hi = (int)tid > lmax ? lo
+                            : (blockIdx.x + 1u < A.nb ? A.E[at + 1] : A.bs[BS_LEVEL + tid + 1u]);
+        s_lo[tid] = lo;
+        s_hi[tid] = hi;
+        A.span[at] = hi > lo && A.nd.end[hi - 1u] > bend ? hi - 1u : TREE_NONE;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t off = 0;
+        for (int k = 0; k < TREE_NLEV; ++k) {
+            s_off[k] = off;
+            off += s_hi[k] - s_lo[k];
+        }
+        s_off[TREE_NLEV] = off;
+    }
+    __syncthreads();
+    const uint32_t total = s_off[TREE_NLEV];
+    for (uint32_t q = tid; q < total; q += TB_THREADS) {
+        uint32_t k = 0;
+        while (q >= s_off[k + 1])
+            ++k;
+        const uint32_t v = s_lo[k] + (q - s_off[k]);
+        if (flag)
+            node_groups(v, A.nd, G, flag, KB);
+        if (A.nd.cend[v] == A.nd.child[v] && A.nd.end[v] <= bend) {
+            dzs_node_rec out;
+            moments_of(A, v, [&](uint32_t c) { return A.rec[c]; }, out);
+            A.rec[v] = out;
+            if (q < TREE_CACHE)
+                s_rec[q] = out;
+        }
+    }
+    for (int k = lmax; k >= 0; --k) {
+        const uint32_t lo = s_lo[k], hi = s_hi[k];
+        if (hi == lo)
+            continue;
+        __syncthreads();
+        // children of level-k nodes: level k + 1, at this place of the block's list
+        const uint32_t cshift = k < lmax ? s_off[k + 1] - s_lo[k + 1] : 0u;
+        for (uint32_t v = lo + tid; v < hi; v += TB_THREADS) {
+            if (A.nd.cend[v] == A.nd.child[v] || A.nd.end[v] > bend)
+                continue;
+            dzs_node_rec out;
+            moments_of(A, v,
+                       [&](uint32_t c) {
+                           const uint32_t q = c + cshift;
+                           return q < TREE_CACHE ? s_rec[q] : A.rec[c];
+                       },
+                       out);
+            A.rec[v] = out;
+            const uint32_t q = v - lo + s_off[k];
+            if (q < TREE_CACHE)
+                s_rec[q] = out;
+        }
+    }
+}
+
+// Moments of the nodes that span blocks.  A workgroup joins TREE_TIER blocks (or tiers of `size`
+// blocks), in which at most one node of each level starts in each and ends past
+// it (`in`): the nodes that end inside the tier are done, level by level from the deepest, those
+// that span its end are handed on (`out`).  (One workgroup over all blocks took 287 us at 128^3:
+// a single CU's bandwidth.)
+__global__ __launch_bounds__(TREE_TIER *TREE_NLEV) void k_tree_tier(
+    moment_args A, const uint32_t *__restrict__ in, uint32_t nb_in, uint32_t size,
+    uint32_t *__restrict__ out, uint32_t nb_out) {
+    __shared__ uint32_t s_out[TREE_NLEV];
+    if (A.bs[DZS_BS_BADINPUT])
+        return;
+    const int level = (int)(threadIdx.x / TREE_TIER);
+    const uint32_t b = blockIdx.x * TREE_TIER + threadIdx.x % TREE_TIER;
+    if (threadIdx.x < TREE_NLEV)
+        s_out[threadIdx.x] = TREE_NONE;
+    const uint64_t next = (uint64_t)(blockIdx.x + 1u) * TREE_TIER * size;   // the next tier's block
+    const uint32_t tend = next < A.nb ? A.snap[next] : A.n;
+    const uint32_t v = b < nb_in ? in[(uint64_t)level * nb_in + b] : TREE_NONE;
+    const bool here = v != TREE_NONE && A.nd.end[v] <= tend;
+    __syncthreads();
+    if (v != TREE_NONE && !here)
+        s_out[level] = v;   // the level's last node of the tier
+    for (int k = TREE_NLEV - 1; k >= 0; --k) {
+        const bool mine = here && level == k;
+        if (!__syncthreads_or(mine ? 1 : 0))   // (a barrier after each level that had one)
+            continue;
+        if (mine) {
+            dzs_node_rec rec;
+            moments_of(A, v, [&](uint32_t c) { return A.rec[c]; }, rec);
+            A.rec[v] = rec;
+        }
+        __syncthreads();
+    }
+    if (out && threadIdx.x < TREE_NLEV)
+        out[(uint64_t)threadIdx.x * nb_out + blockIdx.x] = s_out[threadIdx.x];
+}
+
+// Group starts from the flags: per tile of 4096 particles their number, then (after a scan of
+// the numbers) their places.  A thread reads 16 flags at once.
+__global__ __launch_bounds__(TB_THREADS) void k_flag_count(uint32_t n,
+                                                           const uint8_t *__restrict__ flag,
+                                                           uint32_t *__restrict__ cnt) {
+    __shared__ uint32_t s_c[TB_THREADS / 64];
+    const uint64_t i = (uint64_t)blockIdx.x * 4096u + threadIdx.x * 16u;
+    uint32_t c = 0;
+    if (i + 16u <= n) {
+        const uint4 v = *(const uint4 *)(flag + i);
+        c = (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w));
+    } else {
+        for (uint64_t j = i; j < n; ++j)
+            c += flag[j];
+    }
+    c = dzs_wave_last(dzs_wave_scan_add_full(c));
+    if ((threadIdx.x & 63u) == 0u)
+        s_c[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        cnt[blockIdx.x] = s_c[0] + s_c[1] + s_c[2] + s_c[3];
+}
+
+__global__ __launch_bounds__(TB_THREADS) void k_flag_place(uint32_t n,
+                                                           const uint8_t *__restrict__ flag,
+                                                           const uint32_t *__restrict__ scan,
+                                                           const uint32_t *__restrict__ total,
+                                                           uint32_t *__restrict__ grp_first) {
+    __shared__ uint32_t s_c[TB_THREADS / 64];
+    const uint64_t i = (uint64_t)blockIdx.x * 4096u + threadIdx.x * 16u;
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    if (i + 16u <= n) {
+        const uint4 v = *(const uint4 *)(flag + i);
+        w[0] = v.x;
+        w[1] = v.y;
+        w[2] = v.z;
+        w[3] = v.w;
+    } else {
+        for (uint64_t j = i; j < n; ++j)
+            w[(j - i) >> 2] |= (uint32_t)flag[j] << (8u * ((j - i) & 3u));
+    }
+    const uint32_t c = (uint32_t)(__popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]));
+    const uint32_t incl = dzs_wave_scan_add_full(c);
+    if ((threadIdx.x & 63u) == 63u)
+        s_c[threadIdx.x >> 6] = incl;
+    __syncthreads();
+    uint32_t at = scan[blockIdx.x] + incl - c;
+    for (uint32_t k = 0; k < (threadIdx.x >> 6); ++k)
+        at += s_c[k];
+    for (uint32_t k = 0; k < 16u; ++k)
+        if ((w[k >> 2] >> (8u * (k & 3u))) & 1u)
+            grp_first[at++] = (uint32_t)(i + k);
     if (i == 0)
-        grp_first[scan[n - 1] + flag[n - 1]] = n;
+        grp_first[*total] = n;
 }
 
 __global__ __launch_bounds__(TB_THREADS) void k_fill_u32(uint64_t n, uint32_t *a, uint32_t v);
@@ -469,31 +742,41 @@ __global__ __launch_bounds__(TB_THREADS) void k_fill_u32(uint64_t n, uint32_t *a
         a[i] = v;
 }
 
-// KB > 0: a batch whose keys carry the box in their top KB digits; the nodes above level KB
-// always split, the box table supplies each leaf's mass unit and softening.
-//
-// Every level runs whether or not the tree is that deep (an empty frontier makes its kernels
-// return at once): the counts stay on the device and nothing here waits for the host.  The
-// launches of level k are sized for the largest frontier it can have: 8^k nodes, and below
-// the forced levels the internal nodes of more than `leaf` particles, at most n / (leaf + 1).
-// Moments of every level of the last built tree, bottom-up (levels 0 .. ctx->tree_deepest).
+// Moments of every node of the last built tree (and, with G, the group flags).
 static dzs_status tree_moments(dzs_ctx *ctx, const dzs_box *box, uint32_t n, const double *x,
                                const double *y, const double *z, const uint32_t *mult,
-                               const dzs_bbox *boxes, int unwrap, hipStream_t s) {
+                               const dzs_bbox *boxes, int unwrap, uint32_t G, int KB,
+                               hipStream_t s) {
     dzs_timed t(ctx, KC_TREE_MOMENTS, s);
-    for (int k = ctx->tree_deepest; k >= 0; --k) {
-        // at most 8^k nodes on level k, and never more than the particles
-        uint64_t ub = n;
-        if (k < 8 && (1ull << (3 * k)) < ub)
-            ub = 1ull << (3 * k);
-        uint32_t nbk = blocks_for(ub, TB_THREADS);
-        nbk = nbk < 8192u ? nbk : 8192u;   // grid-stride beyond
-        hipLaunchKernelGGL(k_tree_moments, dim3(nbk), dim3(TB_THREADS), 0, s,
-                           (const uint32_t *)ctx->bstate, k, x, y, z, mult, box->m0,
-                           2.8 * box->eps0, ctx->nd_first, ctx->nd_count, ctx->nd_child,
-                           ctx->nd_nchild, ctx->nd_level, ctx->nd_rec,
-                           (const uint64_t *)ctx->key, boxes, box->L, unwrap);
-        DZS_TRY(dzs_check_launch(ctx, "tree_moments"));
+    moment_args A;
+    A.x = x; A.y = y; A.z = z; A.mult = mult;
+    A.m0 = box->m0;
+    A.h0 = 2.8 * box->eps0;
+    A.L = box->L;
+    A.nd = tree_nodes{ctx->nd_first, ctx->nd_end, ctx->nd_child, ctx->nd_cend, ctx->nd_level};
+    A.rec = ctx->nd_rec;
+    A.key = ctx->key;
+    A.boxes = boxes;
+    A.unwrap = unwrap;
+    A.E = ctx->tree_snap_e;
+    A.snap = ctx->tree_snap;
+    A.span = ctx->tree_span;
+    A.bs = ctx->bstate;
+    A.n = n;
+    A.nb = (uint32_t)tree_blocks(n);
+    hipLaunchKernelGGL(k_tree_block, dim3(A.nb), dim3(TB_THREADS), 0, s, A, G,
+                       G ? ctx->grp_flag : nullptr, KB);
+    DZS_TRY(dzs_check_launch(ctx, "tree_block"));
+    uint32_t size = 1;
+    uint32_t *in = A.span;
+    for (uint32_t nb = A.nb; nb > 1; size *= TREE_TIER) {
+        const uint32_t nt = (nb + TREE_TIER - 1) / TREE_TIER;
+        uint32_t *out = in + (uint64_t)TREE_NLEV * nb;
+        hipLaunchKernelGGL(k_tree_tier, dim3(nt), dim3(TREE_TIER * TREE_NLEV), 0, s, A,
+                           (const uint32_t *)in, nb, size, nt > 1 ? out : nullptr, nt);
+        DZS_TRY(dzs_check_launch(ctx, "tree_tier"));
+        in = out;
+        nb = nt;
     }
     return DZS_OK;
 }
@@ -504,7 +787,7 @@ dzs_status dzs_tree_refresh(dzs_ctx *ctx, const dzs_box *box, uint64_t n, const 
     if (!ctx->tree_built || n != ctx->tree_n)
         return dzs_fail(ctx, DZS_EINVAL, "tree refresh: no tree of %llu particles",
                         (unsigned long long)n);
-    return tree_moments(ctx, box, (uint32_t)n, x, y, z, mult, nullptr, 1, s);
+    return tree_moments(ctx, box, (uint32_t)n, x, y, z, mult, nullptr, 1, 0u, 0, s);
 }
 
 dzs_status dzs_tree_build_ex(dzs_ctx *ctx, const dzs_box *box, uint64_t n64, const double *x,
@@ -515,62 +798,36 @@ dzs_status dzs_tree_build_ex(dzs_ctx *ctx, const dzs_box *box, uint64_t n64, con
     ctx->tree_built = false;
     if (n == 0)
         return DZS_OK;
-    const uint32_t leaf = (uint32_t)leaf_size;
-    const uint64_t cap = ctx->cap_nodes;
     uint32_t *bs = ctx->bstate;
-    int deepest = 0;  // the deepest level the build may have created
+    const uint32_t nb = (uint32_t)tree_blocks(n);
+    const uint64_t words = (uint64_t)TREE_NLEV * nb;
     {
         dzs_timed t(ctx, KC_TREE_BUILD, s);
-        hipLaunchKernelGGL(k_tree_root, dim3(1), dim3(1), 0, s, n, ctx->nd_first, ctx->nd_count,
-                           ctx->nd_child, ctx->nd_nchild, ctx->nd_level, ctx->frontier, bs, leaf,
-                           KB);
-        DZS_TRY(dzs_check_launch(ctx, "tree_root"));
-        uint32_t *fr = ctx->frontier, *fr_next = ctx->frontier_next;
-        for (int k = 0; k < DZS_TREE_LEVELS; ++k) {
-            deepest = k + 1;
-            uint64_t ub = k <= KB ? n : n / (leaf + 1) + 1;
-            if (k < 8 && (1ull << (3 * k)) < ub)
-                ub = 1ull << (3 * k);
-            // one wave per frontier node, grid-stride
-            const uint64_t sb = (ub + TB_THREADS / 64 - 1) / (TB_THREADS / 64);
-            hipLaunchKernelGGL(k_tree_split, dim3((uint32_t)(sb < 2048 ? sb : 2048)),
-                               dim3(TB_THREADS), 0,
-                               s, fr, (const uint32_t *)bs, k, ctx->key, ctx->nd_first,
-                               ctx->nd_count, ctx->child_bounds, ctx->fr_nchild,
-                               ctx->fr_ninternal, leaf, KB);
-            DZS_TRY(dzs_check_launch(ctx, "tree_split"));
-            DZS_TRY(dzs_scan2_u32_dev(ctx, ctx->fr_nchild, ctx->fr_child_off, ctx->fr_ninternal,
-                                      ctx->fr_int_off, ub, bs + BS_NF, bs + BS_CHILDREN,
-                                      bs + BS_INTERNAL, s));
-            hipLaunchKernelGGL(k_tree_emit, dim3(blocks_for(ub, TB_THREADS)), dim3(TB_THREADS), 0,
-                               s, fr, (const uint32_t *)bs, k, ctx->child_bounds,
-                               ctx->fr_child_off, ctx->fr_int_off, cap, ctx->nd_first,
-                               ctx->nd_count, ctx->nd_child, ctx->nd_nchild, ctx->nd_level,
-                               fr_next, leaf, KB);
-            DZS_TRY(dzs_check_launch(ctx, "tree_emit"));
-            hipLaunchKernelGGL(k_tree_level, dim3(1), dim3(1), 0, s, bs, k, cap);
-            DZS_TRY(dzs_check_launch(ctx, "tree_level"));
-            uint32_t *tmp = fr;
-            fr = fr_next;
-            fr_next = tmp;
-        }
+        hipLaunchKernelGGL(k_tree_levels, dim3(nb), dim3(TB_THREADS), 0, s, n,
+                           (const uint64_t *)ctx->key, leaf_size, KB, (const uint32_t *)bs,
+                           ctx->tree_sd, ctx->tree_cnt, ctx->grp_flag, ctx->tree_snap);
+        DZS_TRY(dzs_check_launch(ctx, "tree_levels"));
+        DZS_TRY(dzs_scan_u32(ctx, ctx->tree_cnt, ctx->tree_scan, words, ctx->tree_scan + words,
+                             s));
+        hipLaunchKernelGGL(k_tree_emit, dim3(nb), dim3(TB_THREADS), 0, s, n,
+                           (const uint16_t *)ctx->tree_sd, (const uint32_t *)ctx->tree_scan,
+                           ctx->cap_nodes, ctx->nd_first, ctx->nd_end, ctx->nd_child,
+                           ctx->nd_cend, ctx->nd_level, (const uint32_t *)ctx->tree_snap,
+                           ctx->tree_snap_e, bs);
+        DZS_TRY(dzs_check_launch(ctx, "tree_emit"));
     }
-    ctx->tree_deepest = deepest;
-    DZS_TRY(tree_moments(ctx, box, n, x, y, z, mult, boxes, 0, s));
+    DZS_TRY(tree_moments(ctx, box, n, x, y, z, mult, boxes, 0, (uint32_t)group_size, KB, s));
     {
         dzs_timed t(ctx, KC_TREE_GROUPS, s);
-        hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n, TB_THREADS)), dim3(TB_THREADS), 0, s,
-                           (uint64_t)n, ctx->grp_flag, 0u);
-        DZS_TRY(dzs_check_launch(ctx, "group_clear"));
-        hipLaunchKernelGGL(k_tree_groups, dim3(blocks_for(cap, TB_THREADS)), dim3(TB_THREADS), 0,
-                           s, (const uint32_t *)bs, ctx->nd_first, ctx->nd_count, ctx->nd_child,
-                           ctx->nd_nchild, (uint32_t)group_size, ctx->grp_flag, ctx->nd_level,
-                           KB);
-        DZS_TRY(dzs_check_launch(ctx, "tree_groups"));
-        DZS_TRY(dzs_scan_u32(ctx, ctx->grp_flag, ctx->grp_scan, n, bs + BS_GROUPS, s));
-        hipLaunchKernelGGL(k_group_compact, dim3(blocks_for(n, TB_THREADS)), dim3(TB_THREADS), 0, s,
-                           n, ctx->grp_flag, ctx->grp_scan, ctx->grp_first);
-        DZS_TRY(dzs_check_launch(ctx, "group_compact"));
+        const uint32_t tiles = (uint32_t)dzs_tree_flag_tiles(n);
+        hipLaunchKernelGGL(k_flag_count, dim3(tiles), dim3(TB_THREADS), 0, s, n,
+                           (const uint8_t *)ctx->grp_flag, ctx->grp_cnt);
+        DZS_TRY(dzs_check_launch(ctx, "flag_count"));
+        DZS_TRY(dzs_scan_u32(ctx, ctx->grp_cnt, ctx->grp_scan, tiles, bs + BS_GROUPS, s));
+        hipLaunchKernelGGL(k_flag_place, dim3(tiles), dim3(TB_THREADS), 0, s, n,
+                           (const uint8_t *)ctx->grp_flag, (const uint32_t *)ctx->grp_scan,
+                           (const uint32_t *)(bs + BS_GROUPS), ctx->grp_first);
+        DZS_TRY(dzs_check_launch(ctx, "flag_place"));
     }
     ctx->tree_built = true;
     ctx->tree_n = n;
@@ -780,14 +1037,14 @@ __global__ __launch_bounds__(TB_THREADS) void k_cell_clear(uint64_t n, uint32_t 
 // key prefix.  The claimed ranges are disjoint; cells no node claims hold no particle.
 __global__ __launch_bounds__(TB_THREADS) void k_cell_fill(
     const uint32_t *__restrict__ bs, int K, const uint64_t *__restrict__ key,
-    const uint32_t *__restrict__ nd_first, const uint8_t *__restrict__ nd_nchild,
+    const uint32_t *__restrict__ nd_first, const uint32_t *__restrict__ nd_child,
     const uint8_t *__restrict__ nd_level, uint32_t *__restrict__ cell_node,
     uint8_t *__restrict__ cell_dl) {
     const uint32_t node = blockIdx.x * TB_THREADS + threadIdx.x;
     if (node >= bs[BS_LEVEL + K + 1])  // the nodes of levels 0..K
         return;
     const int l = nd_level[node];
-    if (l > K || (l < K && nd_nchild[node] != 0))
+    if (l > K || (l < K && nd_child[node] != 0))   // (no node has the root for a child)
         return;
     const uint64_t P = key[nd_first[node]] >> (3 * (DZS_KEY_BITS - l));
     const int dl = K - l;
@@ -2054,7 +2311,7 @@ dzs_status dzs_tree_walk_ex(dzs_ctx *ctx, const dzs_box *box, uint64_t n, const 
         n_top = n_top < ctx->cap_nodes ? n_top : ctx->cap_nodes;
         hipLaunchKernelGGL(k_cell_fill, dim3(blocks_for(n_top, TB_THREADS)), dim3(TB_THREADS), 0,
                            s, (const uint32_t *)ctx->bstate, K, (const uint64_t *)ctx->key,
-                           ctx->nd_first, ctx->nd_nchild, ctx->nd_level, ctx->cell_node,
+                           ctx->nd_first, ctx->nd_child, ctx->nd_level, ctx->cell_node,
                            ctx->cell_dl);
         DZS_TRY(dzs_check_launch(ctx, "cell_fill"));
     }

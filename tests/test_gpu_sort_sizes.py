@@ -1,0 +1,47 @@
+"""The radix sort at the edges of its forms: one workgroup (up to 8192 keys), tiles of 4096, column
+segments of 64 tiles and several segments.  dzs_sort_state's permutation is the stable order of
+the keys, bit for bit, on scattered, nearly sorted and heavily repeated keys."""
+import numpy as np
+import pytest
+
+import dzs_ics
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dz():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2005_05328_amd as dz
+    return dz
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 1023, 8191, 8192, 8193, 12289, 262144, 262145,
+                               300001, 700003])
+@pytest.mark.parametrize("kind", ["random", "near", "few"])
+def test_sort_sizes(dz, n, kind):
+    import torch
+    L = 64.0
+    ps = dzs_ics.uniform_random(n, L, seed=n)
+    if kind == "few":        # 27 distinct positions: long runs of equal keys
+        for a in (ps.x, ps.y, ps.z):
+            a[:] = np.floor(a / (L / 3)) * (L / 3) + 1.0
+    elif kind == "near":     # key order with one in fifty moved
+        o = np.argsort(oracle.morton_keys(ps.x, ps.y, ps.z, L), kind="stable")
+        moved = dzs_ics.rng(n + 1).random(n) < 0.02
+        for a in (ps.x, ps.y, ps.z):
+            a[:] = a[o]
+        ps.x[moved] = (ps.x[moved] + 0.3) % L
+    box = dz.make_box(L, 1.0, 1.0)
+    ctx = dz.Context(n, 0)
+    st = dz.State.from_host(ps)
+    perm = torch.zeros(n, dtype=torch.int32, device="cuda")
+    ctx.sort_state(box, st, perm=perm)
+    torch.cuda.synchronize()
+    ref = np.argsort(oracle.morton_keys(ps.x, ps.y, ps.z, L), kind="stable")
+    assert np.array_equal(perm.cpu().numpy(), ref)
+    assert np.array_equal(st.id[:n].cpu().numpy(), ref.astype(np.int32))
+    assert np.array_equal(st.px[:n].cpu().numpy(), ps.px[ref])
+    ctx.close()

@@ -700,18 +700,21 @@ extern "C" dzs_status kdk_step(dzs_ctx *ctx, const dzs_box *box, dzs_particles *
     bool aold_ok = relative;
     if (relative)
         DZS_TRY(dzs_launch_gnorm(ctx, st->n, st->gx, st->gy, st->gz, nullptr, ctx->aold, s));
-    DZS_TRY(dzs_launch_kick(ctx, st, prm->K1, s));
-    DZS_TRY(dzs_launch_drift_lc(ctx, box, st, &prm->lc, ring, prm->do_lightcone, 1, s));
     const bool can_merge = prm->do_coarsen &&
                            prm->coarsen.R_lc + prm->coarsen.b < 0.5 * sqrt(3.0) * box->L;
     // the state in key order for the tree: after DZS it already is (the coarsening sorts by
     // (key, id) and a merged particle stays in its cube's slot); only new keys are needed,
     // with a full sort if rounding moved a centre of mass out of its cube
     bool in_order = false;
+    // kick, lightcone, drift and keys in one pass that stages the rows; the sort's order is
+    // gathered from them into the state
+    DZS_TRY(dzs_open_step(ctx, box, st, prm->K1, nullptr, &prm->lc, ring, prm->do_lightcone, s));
     if (can_merge && st->n > 0) {
-        if (prm->coarsen.criterion == DZS_CRIT_DYNAMICAL)  // g is the previous force here
-            DZS_TRY(dzs_coarsen_amin(ctx, box, st, &prm->coarsen, s));
-        DZS_TRY(sort_state(ctx, box, st, 1, 0, s));
+        DZS_TRY(dzs_radix_sort(ctx, st->n, s));
+        DZS_TRY(dzs_fix_ties(ctx, st->n, st->id, s));
+        DZS_TRY(dzs_gather_rows(ctx, st, ctx->idx, s));
+        if (prm->coarsen.criterion == DZS_CRIT_DYNAMICAL)
+            DZS_TRY(dzs_coarsen_amin(ctx, box, st, &prm->coarsen, s, ctx->idx));
         if (aold_ok)
             DZS_TRY(dzs_permute_f32(ctx, ctx->aold, ctx->idx, st->n, s));
         DZS_HIP(ctx, hipMemcpyAsync(ctx->dz_perm, ctx->idx, sizeof(uint32_t) * st->n,
@@ -727,7 +730,12 @@ extern "C" dzs_status kdk_step(dzs_ctx *ctx, const dzs_box *box, dzs_particles *
     }
     if (st->n > 0) {
         if (!in_order) {
-            DZS_TRY(sort_state(ctx, box, st, 0, 0, s, true));
+            if (can_merge) {
+                DZS_TRY(sort_state(ctx, box, st, 0, 0, s, true));
+            } else {
+                DZS_TRY(dzs_radix_sort(ctx, st->n, s, DZS_TREE_FIRST_PASS));
+                DZS_TRY(dzs_gather_rows(ctx, st, ctx->idx, s));
+            }
             if (aold_ok)
                 DZS_TRY(dzs_permute_f32(ctx, ctx->aold, ctx->idx, st->n, s));
         }
@@ -1087,14 +1095,11 @@ extern "C" dzs_status kdk_step_batch(dzs_ctx *ctx, const dzs_batch *batch, dzs_p
     if (st->n == 0)
         return DZS_OK;
 
-    DZS_TRY(dzs_launch_kick(ctx, st, prm->K1, s, K1_dev));
-    DZS_TRY(dzs_launch_drift_lc(ctx, &batch->boxes[0], st, &prm->lc, ring, prm->do_lightcone, 1,
-                                s, true, nb, lc_dev));
     // keys with the box on top, one sort for every box: each box stays in its range
-    DZS_TRY(dzs_launch_keys(ctx, st->x, st->y, st->z, st->n, 1.0, ctx->key, ctx->idx, s, true,
-                            nb));
+    DZS_TRY(dzs_open_step(ctx, &batch->boxes[0], st, prm->K1, K1_dev, &prm->lc, ring,
+                          prm->do_lightcone, s, true, nb, lc_dev));
     DZS_TRY(dzs_radix_sort(ctx, st->n, s, DZS_TREE_FIRST_PASS));
-    DZS_TRY(dzs_permute_state(ctx, st, ctx->idx, 0, s));
+    DZS_TRY(dzs_gather_rows(ctx, st, ctx->idx, s));
     DZS_TRY(dzs_tree_build_ex(ctx, &batch->boxes[0], st->n, st->x, st->y, st->z, st->mult,
                               t.leaf_size, t.group_size, DZS_BATCH_LEVELS, ctx->batch_box, s));
     DZS_TRY(dzs_batch_roots(ctx, ctx->batch_box, s));

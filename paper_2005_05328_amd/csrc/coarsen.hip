@@ -164,7 +164,9 @@ __global__ __launch_bounds__(DZ_THREADS) void k_dz_amin(uint64_t n, const double
                                                        const double *__restrict__ gy,
                                                        const double *__restrict__ gz, double L,
                                                        double xo0, double xo1, double xo2,
-                                                       double Rb, unsigned long long *out) {
+                                                       double Rb,
+                                                       const uint32_t *__restrict__ perm,
+                                                       unsigned long long *out) {
     __shared__ double red[DZ_THREADS];
     double best = __builtin_inf();
     const uint64_t stride = (uint64_t)gridDim.x * DZ_THREADS;
@@ -174,7 +176,8 @@ __global__ __launch_bounds__(DZ_THREADS) void k_dz_amin(uint64_t n, const double
         const double dz = dzs_min_image(z[i] - xo2, L);
         if (!(sqrt(dx * dx + dy * dy + dz * dz) < Rb))
             continue;
-        const double g2 = gx[i] * gx[i] + gy[i] * gy[i] + gz[i] * gz[i];
+        const uint64_t j = perm ? perm[i] : i;
+        const double g2 = gx[j] * gx[j] + gy[j] * gy[j] + gz[j] * gz[j];
         best = g2 < best ? g2 : best;
     }
     red[threadIdx.x] = best;
@@ -191,7 +194,8 @@ __global__ __launch_bounds__(DZ_THREADS) void k_dz_amin(uint64_t n, const double
 }
 
 dzs_status dzs_coarsen_amin(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p,
-                            const dzs_coarsen_params *prm, hipStream_t s) {
+                            const dzs_coarsen_params *prm, hipStream_t s,
+                            const uint32_t *perm) {
     unsigned long long *slot = (unsigned long long *)(ctx->d_small + DZS_SMALL_AMIN);
     hipLaunchKernelGGL(k_dz_amin_init, dim3(1), dim3(1), 0, s, slot);
     DZS_TRY(dzs_check_launch(ctx, "dz_amin_init"));
@@ -203,7 +207,7 @@ dzs_status dzs_coarsen_amin(dzs_ctx *ctx, const dzs_box *box, const dzs_particle
                        (const double *)p->x, (const double *)p->y, (const double *)p->z,
                        (const double *)p->gx, (const double *)p->gy, (const double *)p->gz,
                        box->L, prm->x_obs[0], prm->x_obs[1], prm->x_obs[2], prm->R_lc + prm->b,
-                       slot);
+                       perm, slot);
     return dzs_check_launch(ctx, "dz_amin");
 }
 

@@ -73,6 +73,25 @@ struct lc_args {
     double drift_max, drift_slope, chi_fall;
 };
 
+// the rows of a particle state without the accelerations: x, y, z, px, py, pz, ...
+struct dzs_rows {
+    double *f[6];
+    uint32_t *mult, *id;
+    uint8_t *type;
+};
+
+// the opening of a whole step, done with the drift: kick by g K, keys, staged rows
+struct open_args {
+    const double *gx, *gy, *gz;
+    double K;
+    const double *K_dev;   // (non-null: the factor, in a device block)
+    dzs_rows out;
+    const uint8_t *type;
+    uint64_t *key;
+    uint32_t *idx;
+    double key_scale;
+};
+
 // the factors of one batched step, in a device block (and its pinned host staging): a
 // captured step reads them when it runs
 struct dzs_step_block {
@@ -367,14 +386,21 @@ dzs_status dzs_fix_ties(dzs_ctx *ctx, uint64_t n, const uint32_t *id, hipStream_
 dzs_status dzs_launch_kick(dzs_ctx *ctx, const dzs_particles *p, double K, hipStream_t s,
                            const double *K_dev = nullptr);
 void dzs_make_lc_args(const dzs_lc_params *lc, lc_args *A);
-// batch = true: the box of each particle (its L) from ctx->batch_first / ctx->batch_box (nb boxes)
 dzs_status dzs_launch_drift_lc(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p,
                                const dzs_lc_params *lc, dzs_lc_ring *ring, int do_lc,
-                               int do_drift, hipStream_t s, bool batch = false, uint32_t nb = 0,
-                               const lc_args *A_dev = nullptr);
+                               int do_drift, hipStream_t s);
+// The opening of a step: p + g K, the lightcone test over the drift, the drift, the drifted
+// positions' keys (ctx->key, ctx->idx); the state is left as it is, the kicked and drifted rows
+// are staged.  batch = true: the box of each particle from ctx->batch_first / ctx->batch_box
+// (nb boxes).  dzs_gather_rows then writes the state, row i from staged row perm[i].
+dzs_status dzs_open_step(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p, double K,
+                         const double *K_dev, const dzs_lc_params *lc, dzs_lc_ring *ring,
+                         int do_lc, hipStream_t s, bool batch = false, uint32_t nb = 0,
+                         const lc_args *A_dev = nullptr);
+dzs_status dzs_gather_rows(dzs_ctx *ctx, const dzs_particles *p, const uint32_t *perm,
+                           hipStream_t s);
 dzs_status dzs_launch_keys(dzs_ctx *ctx, const double *x, const double *y, const double *z,
-                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s,
-                           bool batch = false, uint32_t nb = 0);
+                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s);
 dzs_status dzs_permute_state(dzs_ctx *ctx, dzs_particles *p, const uint32_t *perm,
                              int with_g, hipStream_t s);
 dzs_status dzs_gather_f64(dzs_ctx *ctx, const double *src, const uint32_t *perm, double *dst,
@@ -506,10 +532,12 @@ dzs_status dzs_tree_active_targets(dzs_ctx *ctx, uint64_t n, const uint8_t *acti
 // max_i (|px| + |py| + |pz|) |D| (before it), both on the device.
 dzs_status dzs_drift_bound_reset(dzs_ctx *ctx, hipStream_t s);
 dzs_status dzs_drift_bound_add(dzs_ctx *ctx, const dzs_particles *p, double D, hipStream_t s);
-// Reduce the dynamical criterion's a_min^2 over the state (before any reordering that leaves
-// g behind) into d_small[DZS_SMALL_AMIN].
+// Reduce the dynamical criterion's a_min^2 over the state into d_small[DZS_SMALL_AMIN]: g in the
+// order of the positions, or (perm non-null) row i's at perm[i], after a reordering that left g
+// behind.
 dzs_status dzs_coarsen_amin(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p,
-                            const dzs_coarsen_params *prm, hipStream_t s);
+                            const dzs_coarsen_params *prm, hipStream_t s,
+                            const uint32_t *perm = nullptr);
 // Keys of the coarsened state into ctx->key and whether they are still ascending
 // (synchronises the stream).
 dzs_status dzs_coarsen_rekey(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p,

@@ -1,6 +1,8 @@
 // Per-particle streaming kernels: kick, drift with the lightcone crossing test, Morton keys,
 // and the gathers that apply a sort permutation to the structure-of-arrays state.
 // All are HBM-bound: one thread per particle, coalesced loads and stores of each array.
+#include <type_traits>
+
 #include "internal.h"
 
 #define PT_THREADS 256
@@ -217,10 +219,30 @@ __device__ double lc_solve(const lc_args &A, double d0x, double d0y, double d0z,
     return t;
 }
 
+// Morton key of a position: s cells per unit length, 2^21 a side; in a batch the box in the top
+// DZS_BATCH_LEVELS digits and 2^18 cells a side below.
+__device__ __forceinline__ uint64_t batch_key(double x, double y, double z, uint64_t b, double L) {
+    const double sb = DZS_BATCH_SIDE / L;
+    auto cell = [&](double v) -> uint64_t {
+        double t = floor(v * sb);
+        t = t < 0.0 ? 0.0 : (t > DZS_BATCH_SIDE - 1.0 ? DZS_BATCH_SIDE - 1.0 : t);
+        return (uint64_t)t;
+    };
+    return (b << DZS_BATCH_SHIFT) | (dzs_spread3(cell(x)) << 2) | (dzs_spread3(cell(y)) << 1) |
+           dzs_spread3(cell(z));
+}
+
 // PBLOCK: the drift and lightcone parameters come from a device block (*Ap) rather than the
 // kernel arguments, so that a captured launch can be replayed for another step.
 //
-// HBM-bound (48 bytes read, 24 written per particle).  The few particles that cross are not
+// OPEN: the opening of a whole step in one pass: the kick p + g K before the drift, the Morton key
+// of the drifted position and the row's copy (kicked, drifted) to the staging rows, from which
+// the sort's order is gathered back into the state (dzs_gather_rows).  The state itself is only
+// read.  Kick, drift, keys, gather and copy as passes of their own moved 444 bytes per
+// particle, these two 268: 128^3 214 -> 111 us, 256^3 1.7 -> 0.88 ms,
+// 512^3 11.5 -> 7.0 ms.
+//
+// HBM-bound (drift alone: 48 bytes read, 24 written per particle).  The few particles that cross are not
 // solved where they are found, which would hold their whole wave for one or two active lanes:
 // a workgroup of 256 threads takes 1024 particles, queues the crossing ones in LDS and then
 // solves them densely, one atomic on the record count per workgroup.  4,000,037 particles of
@@ -228,14 +250,15 @@ __device__ double lc_solve(const lc_args &A, double d0x, double d0y, double d0z,
 // place by bisection, 121 us so.
 #define LC_ITEMS 4
 #define LC_TILE (PT_THREADS * LC_ITEMS)
-template <bool PBLOCK>
+template <bool PBLOCK, bool OPEN>
 __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
     uint64_t n, double *__restrict__ x, double *__restrict__ y, double *__restrict__ z,
     const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ pz,
     const uint32_t *__restrict__ id, const uint32_t *__restrict__ mult, double L, lc_args A_arg,
     const lc_args *__restrict__ Ap, int do_lc, int do_drift, dzs_lc_record *__restrict__ rec, uint64_t rec_cap,
     unsigned long long *__restrict__ rec_count, uint32_t *__restrict__ overflow,
-    const uint64_t *__restrict__ bfirst, const dzs_bbox *__restrict__ boxes, uint32_t nb) {
+    const uint64_t *__restrict__ bfirst, const dzs_bbox *__restrict__ boxes, uint32_t nb,
+    open_args O) {
     __shared__ uint16_t s_queue[LC_TILE];
     __shared__ uint32_t s_cnt;
     __shared__ unsigned long long s_base;
@@ -245,17 +268,38 @@ __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
     if (tid == 0)
         s_cnt = 0u;
     __syncthreads();
+    const double K = OPEN ? (O.K_dev ? *O.K_dev : O.K) : 0.0;
+    // momentum of particle i during the drift
+    auto mom = [&](const double *p, const double *g, uint64_t i) -> double {
+        return OPEN ? p[i] + g[i] * K : p[i];
+    };
     double nx[LC_ITEMS], ny[LC_ITEMS], nz[LC_ITEMS];
 #pragma unroll
     for (int r = 0; r < LC_ITEMS; ++r) {
         const uint64_t i = base + (uint32_t)r * PT_THREADS + tid;
         bool emit = false;
         if (i < n) {
-            const double Lb = boxes ? boxes[batch_box_of(bfirst, nb, i)].L : L;
+            const uint32_t bi = boxes ? batch_box_of(bfirst, nb, i) : 0u;
+            const double Lb = boxes ? boxes[bi].L : L;
             const double xi = x[i], yi = y[i], zi = z[i];
-            nx[r] = dzs_wrap(xi + px[i] * A.D, Lb);
-            ny[r] = dzs_wrap(yi + py[i] * A.D, Lb);
-            nz[r] = dzs_wrap(zi + pz[i] * A.D, Lb);
+            const double pxi = mom(px, O.gx, i), pyi = mom(py, O.gy, i), pzi = mom(pz, O.gz, i);
+            nx[r] = dzs_wrap(xi + pxi * A.D, Lb);
+            ny[r] = dzs_wrap(yi + pyi * A.D, Lb);
+            nz[r] = dzs_wrap(zi + pzi * A.D, Lb);
+            if (OPEN) {
+                O.out.f[0][i] = nx[r];
+                O.out.f[1][i] = ny[r];
+                O.out.f[2][i] = nz[r];
+                O.out.f[3][i] = pxi;
+                O.out.f[4][i] = pyi;
+                O.out.f[5][i] = pzi;
+                O.out.mult[i] = mult[i];
+                O.out.id[i] = id[i];
+                O.out.type[i] = O.type[i];
+                O.key[i] = boxes ? batch_key(nx[r], ny[r], nz[r], bi, Lb)
+                                 : dzs_morton(nx[r], ny[r], nz[r], O.key_scale);
+                O.idx[i] = (uint32_t)i;
+            }
             if (do_lc) {
                 const double dx = dzs_min_image(xi - A.xo[0], Lb);
                 const double dy = dzs_min_image(yi - A.xo[1], Lb);
@@ -301,7 +345,8 @@ __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
                     continue;
                 }
                 dzs_lc_record out;
-                const double pxi = px[i], pyi = py[i], pzi = pz[i];
+                const double pxi = mom(px, O.gx, i), pyi = mom(py, O.gy, i),
+                             pzi = mom(pz, O.gz, i);
                 const double t = lc_solve(A, dzs_min_image(x[i] - A.xo[0], Lb),
                                           dzs_min_image(y[i] - A.xo[1], Lb),
                                           dzs_min_image(z[i] - A.xo[2], Lb), pxi, pyi, pzi,
@@ -317,7 +362,7 @@ __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
             __syncthreads();   // every queued particle read before any position is written
         }
     }
-    if (do_drift) {
+    if (!OPEN && do_drift) {
 #pragma unroll
         for (int r = 0; r < LC_ITEMS; ++r) {
             const uint64_t i = base + (uint32_t)r * PT_THREADS + tid;
@@ -360,12 +405,11 @@ void dzs_make_lc_args(const dzs_lc_params *lc, lc_args *A) {
     A->chi_fall = chi_min > 0.0 && fall > 0.0 ? chi_min * fall : 0.0;
 }
 
-dzs_status dzs_launch_drift_lc(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p,
+template <bool OPEN>
+static dzs_status launch_drift(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p,
                                const dzs_lc_params *lc, dzs_lc_ring *ring, int do_lc,
                                int do_drift, hipStream_t s, bool batch, uint32_t nb,
-                               const lc_args *A_dev) {
-    if (p->n == 0)
-        return DZS_OK;
+                               const lc_args *A_dev, const open_args &O) {
     lc_args A;
     dzs_make_lc_args(lc, &A);
     dzs_lc_record *rec = nullptr;
@@ -379,23 +423,68 @@ dzs_status dzs_launch_drift_lc(dzs_ctx *ctx, const dzs_box *box, const dzs_parti
         ovf = ring->overflow;
     }
     dzs_timed t(ctx, KC_DRIFT_LC, s);
+    auto launch = [&](auto pblock) {
+        hipLaunchKernelGGL((k_drift_lc<pblock.value, OPEN>), dim3(blocks_for(p->n, LC_TILE)),
+                           dim3(PT_THREADS), 0, s, p->n, p->x, p->y, p->z, (const double *)p->px,
+                           (const double *)p->py, (const double *)p->pz, (const uint32_t *)p->id,
+                           (const uint32_t *)p->mult, box->L, A, A_dev, do_lc, do_drift, rec, cap,
+                           cnt, ovf, (const uint64_t *)ctx->batch_first,
+                           batch ? ctx->batch_box : nullptr, nb, O);
+    };
     if (A_dev)
-        hipLaunchKernelGGL(k_drift_lc<true>, dim3(blocks_for(p->n, LC_TILE)), dim3(PT_THREADS),
-                           0, s, p->n, p->x, p->y, p->z, (const double *)p->px,
-                           (const double *)p->py, (const double *)p->pz,
-                           (const uint32_t *)p->id, (const uint32_t *)p->mult, box->L, A, A_dev,
-                           do_lc, do_drift, rec, cap, cnt, ovf,
-                           (const uint64_t *)ctx->batch_first, batch ? ctx->batch_box : nullptr,
-                           nb);
+        launch(std::true_type());
     else
-        hipLaunchKernelGGL(k_drift_lc<false>, dim3(blocks_for(p->n, LC_TILE)),
-                           dim3(PT_THREADS), 0, s, p->n, p->x, p->y, p->z,
-                           (const double *)p->px, (const double *)p->py,
-                           (const double *)p->pz, (const uint32_t *)p->id,
-                           (const uint32_t *)p->mult, box->L, A, A_dev, do_lc, do_drift, rec,
-                           cap, cnt, ovf, (const uint64_t *)ctx->batch_first,
-                           batch ? ctx->batch_box : nullptr, nb);
+        launch(std::false_type());
     return dzs_check_launch(ctx, "drift_lc");
+}
+
+dzs_status dzs_launch_drift_lc(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p,
+                               const dzs_lc_params *lc, dzs_lc_ring *ring, int do_lc,
+                               int do_drift, hipStream_t s) {
+    if (p->n == 0)
+        return DZS_OK;
+    open_args none;
+    memset(&none, 0, sizeof(none));
+    return launch_drift<false>(ctx, box, p, lc, ring, do_lc, do_drift, s, false, 0, nullptr, none);
+}
+
+// The staging rows: the tree's and the coarsening's arena, which holds nothing between the walk
+// of one step and the build (or coarsening) of the next.
+static dzs_rows staging(dzs_ctx *ctx) {
+    const uint64_t n = ctx->cap_n;
+    dzs_rows r;
+    double *f = (double *)ctx->arena;
+    for (int k = 0; k < 6; ++k)
+        r.f[k] = f + (uint64_t)k * n;
+    r.mult = (uint32_t *)(f + 6 * n);
+    r.id = r.mult + n;
+    r.type = (uint8_t *)(r.id + n);
+    return r;
+}
+
+static dzs_rows rows_of(const dzs_particles *p) {
+    return dzs_rows{{p->x, p->y, p->z, p->px, p->py, p->pz}, p->mult, p->id, p->type};
+}
+
+dzs_status dzs_open_step(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *p, double K,
+                         const double *K_dev, const dzs_lc_params *lc, dzs_lc_ring *ring,
+                         int do_lc, hipStream_t s, bool batch, uint32_t nb,
+                         const lc_args *A_dev) {
+    if (p->n == 0)
+        return DZS_OK;
+    ctx->tree_built = false;
+    open_args O;
+    O.gx = p->gx;
+    O.gy = p->gy;
+    O.gz = p->gz;
+    O.K = K;
+    O.K_dev = K_dev;
+    O.out = staging(ctx);
+    O.type = p->type;
+    O.key = ctx->key;
+    O.idx = ctx->idx;
+    O.key_scale = DZS_KEY_SIDE / box->L;
+    return launch_drift<true>(ctx, box, p, lc, ring, do_lc, 1, s, batch, nb, A_dev, O);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -405,41 +494,23 @@ __global__ __launch_bounds__(PT_THREADS) void k_keys(uint64_t n, const double *_
                                                      const double *__restrict__ y,
                                                      const double *__restrict__ z, double s,
                                                      uint64_t *__restrict__ key,
-                                                     uint32_t *__restrict__ idx,
-                                                     const uint64_t *__restrict__ bfirst,
-                                                     const dzs_bbox *__restrict__ boxes,
-                                                     uint32_t nb) {
+                                                     uint32_t *__restrict__ idx) {
     uint64_t i = (uint64_t)blockIdx.x * PT_THREADS + threadIdx.x;
     if (i >= n)
         return;
-    if (boxes) {
-        // a batch: the box in the top DZS_BATCH_LEVELS digits, 2^18 cells per side below
-        const uint64_t b = batch_box_of(bfirst, nb, i);
-        const double sb = DZS_BATCH_SIDE / boxes[b].L;
-        auto cell = [&](double v) -> uint64_t {
-            double t = floor(v * sb);
-            t = t < 0.0 ? 0.0 : (t > DZS_BATCH_SIDE - 1.0 ? DZS_BATCH_SIDE - 1.0 : t);
-            return (uint64_t)t;
-        };
-        key[i] = (b << DZS_BATCH_SHIFT) | (dzs_spread3(cell(x[i])) << 2) |
-                 (dzs_spread3(cell(y[i])) << 1) | dzs_spread3(cell(z[i]));
-    } else {
-        key[i] = dzs_morton(x[i], y[i], z[i], s);
-    }
+    key[i] = dzs_morton(x[i], y[i], z[i], s);
     if (idx)
         idx[i] = (uint32_t)i;
 }
 
 dzs_status dzs_launch_keys(dzs_ctx *ctx, const double *x, const double *y, const double *z,
-                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s,
-                           bool batch, uint32_t nb) {
+                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s) {
     if (n == 0)
         return DZS_OK;
     const double scale = DZS_KEY_SIDE / L;
     dzs_timed t(ctx, KC_KEYS, s);
     hipLaunchKernelGGL(k_keys, dim3(blocks_for(n, PT_THREADS)), dim3(PT_THREADS), 0, s, n, x, y,
-                       z, scale, key, idx, (const uint64_t *)ctx->batch_first,
-                       batch ? ctx->batch_box : nullptr, nb);
+                       z, scale, key, idx);
     return dzs_check_launch(ctx, "keys");
 }
 
@@ -474,19 +545,58 @@ static dzs_status permute_one(dzs_ctx *ctx, T *arr, const uint32_t *perm, uint64
     return dzs_check_launch(ctx, "copy");
 }
 
+// Row i of dst from row perm[i] of src (perm null: the same row), every array in one pass.
+// HBM-bound: 61 bytes read and 57 written per row.
+__global__ __launch_bounds__(PT_THREADS) void k_gather_rows(uint64_t n, dzs_rows src,
+                                                            const uint32_t *__restrict__ perm,
+                                                            dzs_rows dst) {
+    const uint64_t i = (uint64_t)blockIdx.x * PT_THREADS + threadIdx.x;
+    if (i >= n)
+        return;
+    const uint64_t j = perm ? perm[i] : i;
+    double v[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        v[k] = src.f[k][j];
+    const uint32_t m = src.mult[j], id = src.id[j];
+    const uint8_t t = src.type[j];
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        dst.f[k][i] = v[k];
+    dst.mult[i] = m;
+    dst.id[i] = id;
+    dst.type[i] = t;
+}
+
+static dzs_status gather_rows(dzs_ctx *ctx, uint64_t n, const dzs_rows &src, const uint32_t *perm,
+                              const dzs_rows &dst, hipStream_t s) {
+    hipLaunchKernelGGL(k_gather_rows, dim3(blocks_for(n, PT_THREADS)), dim3(PT_THREADS), 0, s, n,
+                       src, perm, dst);
+    return dzs_check_launch(ctx, "gather_rows");
+}
+
+dzs_status dzs_gather_rows(dzs_ctx *ctx, const dzs_particles *p, const uint32_t *perm,
+                           hipStream_t s) {
+    if (p->n == 0)
+        return DZS_OK;
+    dzs_timed t(ctx, KC_PERMUTE, s);
+    return gather_rows(ctx, p->n, staging(ctx), perm, rows_of(p), s);
+}
+
 dzs_status dzs_permute_state(dzs_ctx *ctx, dzs_particles *p, const uint32_t *perm, int with_g,
                              hipStream_t s) {
     const uint64_t n = p->n;
     if (n == 0)
         return DZS_OK;
+    ctx->tree_built = false;
     dzs_timed t(ctx, KC_PERMUTE, s);
-    double *f64[9] = {p->x, p->y, p->z, p->px, p->py, p->pz, p->gx, p->gy, p->gz};
-    const int nf = with_g ? 9 : 6;
-    for (int k = 0; k < nf; ++k)
-        DZS_TRY(permute_one<double>(ctx, f64[k], perm, n, s));
-    DZS_TRY(permute_one<uint32_t>(ctx, p->mult, perm, n, s));
-    DZS_TRY(permute_one<uint32_t>(ctx, p->id, perm, n, s));
-    DZS_TRY(permute_one<uint8_t>(ctx, p->type, perm, n, s));
+    DZS_TRY(gather_rows(ctx, n, rows_of(p), perm, staging(ctx), s));
+    DZS_TRY(gather_rows(ctx, n, staging(ctx), nullptr, rows_of(p), s));
+    if (with_g) {
+        DZS_TRY(permute_one<double>(ctx, p->gx, perm, n, s));
+        DZS_TRY(permute_one<double>(ctx, p->gy, perm, n, s));
+        DZS_TRY(permute_one<double>(ctx, p->gz, perm, n, s));
+    }
     return DZS_OK;
 }
 

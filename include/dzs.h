@@ -144,24 +144,23 @@ typedef struct {
                             and interpolation in FP32 (rms error ~1e-6 of the force) */
     double r_s;          /* split scale */
     int32_t accumulate;  /* 0: g = g_long, 1: g += g_long */
-    int32_t tile_chunk;  /* particles per workgroup tile of the deposit and of the
-                            interpolation: a power of two in [DZS_PM_CHUNK_MIN,
-                            DZS_PM_CHUNK_MAX]; 0 = the library's default
-                            (DZS_PM_CHUNK_DEFAULT); -1 = no tiles.  A workgroup takes a chunk of
-                            consecutive particles (compact in key order), in pieces.  Deposit:
-                            a piece sums its cloud-in-cell contributions into an LDS tile
-                            spanning its points, up to 4096 of them, and adds each non-zero
-                            point to the mesh once.  Interpolation (only when the particles are
-                            at least half as many as the mesh points): a piece loads the
-                            potential its 4-point stencils read, up to 32 KB of values, into LDS
-                            once.  A piece whose points do not fit (or, in a batch, that spans
-                            two boxes) is halved, down to 128 particles, which read and add
-                            directly.  Mesh and forces are the same bits for every value: the
-                            choice changes speed only. */
+    int32_t tile_chunk;  /* particles per workgroup of the deposit: a power of two in
+                            [DZS_PM_CHUNK_MIN, DZS_PM_CHUNK_MAX]; 0 = chosen by the number of
+                            particles; -1 = no tiles.  A workgroup takes a chunk of consecutive
+                            particles (compact in key order), in runs: a run sums its
+                            cloud-in-cell contributions into an LDS tile spanning its points,
+                            up to 4096 of them, and adds each non-zero point to the mesh once.
+                            A run whose points do not fit (or, in a batch, that spans two
+                            boxes) is halved, down to 64 particles, which add directly.  With 0,
+                            pm_force also brings 131072 or more particles that come in no
+                            order into key order first (in the context's scratch; the
+                            caller's arrays stay as they are).  Mesh and forces are the same
+                            bits for every value: the choice changes speed only. */
 } dzs_pm_params;
 
 #define DZS_PM_CHUNK_MIN 256
 #define DZS_PM_CHUNK_MAX 16384
+/* a middling chunk for callers that fix one (tile_chunk = 0 chooses by the number) */
 #define DZS_PM_CHUNK_DEFAULT 2048
 
 /* Tree (short-range) parameters: g_i = -G sum m_j r_ij g_soft(r_ij, h_ij) S(r_ij/r_s) over

@@ -379,7 +379,8 @@ dzs_status dzs_scan_u32(dzs_ctx *ctx, const uint32_t *in, uint32_t *out, uint64_
                         uint32_t *total_dev, hipStream_t s);
 uint64_t dzs_sort_hist_words(uint64_t n);
 dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s,
-                          int first_pass = 0);  // ctx->key/idx in+out; an even first_pass
+                          int first_pass = 0,   // ctx->key/idx in+out; an even first_pass
+                          const uint32_t *skip = nullptr);  // device: not 0, nothing is done
 dzs_status dzs_fix_ties(dzs_ctx *ctx, uint64_t n, const uint32_t *id, hipStream_t s);
 
 // particles.hip
@@ -400,7 +401,8 @@ dzs_status dzs_open_step(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *
 dzs_status dzs_gather_rows(dzs_ctx *ctx, const dzs_particles *p, const uint32_t *perm,
                            hipStream_t s);
 dzs_status dzs_launch_keys(dzs_ctx *ctx, const double *x, const double *y, const double *z,
-                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s);
+                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s,
+                           const uint32_t *skip = nullptr);  // device: not 0, no keys
 dzs_status dzs_permute_state(dzs_ctx *ctx, dzs_particles *p, const uint32_t *perm,
                              int with_g, hipStream_t s);
 dzs_status dzs_gather_f64(dzs_ctx *ctx, const double *src, const uint32_t *perm, double *dst,

@@ -166,7 +166,10 @@ uint64_t dzs_sort_hist_words(uint64_t n) {
 // The tile's digit counts, row [tile][256].  HBM-bound (8 bytes read per key).
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(const uint64_t *__restrict__ key,
                                                              uint64_t n, int shift,
-                                                             uint32_t *__restrict__ tab) {
+                                                             uint32_t *__restrict__ tab,
+                                                             const uint32_t *skip) {
+    if (skip && *skip)
+        return;
     __shared__ uint32_t s_h[256];
     if (threadIdx.x < 256)
         s_h[threadIdx.x] = 0;
@@ -201,7 +204,10 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(const uint64_t *__r
 // sums of the rows before them, the last segment also writing the columns' totals.  A thread
 // owns a column; rows are read eight at a time.
 __global__ __launch_bounds__(256) void k_col_sum(const uint32_t *__restrict__ tab, uint32_t tiles,
-                                                 uint32_t seg, uint32_t *__restrict__ segsum) {
+                                                 uint32_t seg, uint32_t *__restrict__ segsum,
+                                                 const uint32_t *skip) {
+    if (skip && *skip)
+        return;
     const uint32_t t0 = blockIdx.x * seg, t1 = min(t0 + seg, tiles);
     uint32_t sum = 0;
 #pragma unroll 8
@@ -213,7 +219,10 @@ __global__ __launch_bounds__(256) void k_col_sum(const uint32_t *__restrict__ ta
 __global__ __launch_bounds__(256) void k_col_scan(uint32_t *__restrict__ tab, uint32_t tiles,
                                                   uint32_t seg,
                                                   const uint32_t *__restrict__ segsum,
-                                                  uint32_t *__restrict__ totals) {
+                                                  uint32_t *__restrict__ totals,
+                                                  const uint32_t *skip) {
+    if (skip && *skip)
+        return;
     const uint32_t t0 = blockIdx.x * seg, t1 = min(t0 + seg, tiles);
     uint32_t run = 0;
 #pragma unroll 8
@@ -281,7 +290,9 @@ __device__ __forceinline__ uint32_t excl_scan_256(uint32_t v, uint32_t *s_wave) 
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     const uint64_t *__restrict__ key_in, const uint32_t *__restrict__ idx_in,
     uint64_t *__restrict__ key_out, uint32_t *__restrict__ idx_out, uint64_t n, int shift,
-    const uint32_t *__restrict__ tab, const uint32_t *__restrict__ totals) {
+    const uint32_t *__restrict__ tab, const uint32_t *__restrict__ totals, const uint32_t *skip) {
+    if (skip && *skip)
+        return;
     constexpr int WAVES = SORT_THREADS / 64;
     constexpr int ROUNDS = SORT_ITEMS;  // rounds of 64 keys per wave
     __shared__ uint64_t s_key[SORT_TILE];
@@ -430,7 +441,8 @@ __global__ __launch_bounds__(1024) void k_radix_small(uint64_t *__restrict__ key
     }
 }
 
-dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s, int first_pass) {
+dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s, int first_pass,
+                          const uint32_t *skip) {
     if (n <= 1)
         return DZS_OK;
     if (n > 0xffffffffull)
@@ -441,7 +453,7 @@ dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s, int first_pas
     // One workgroup up to what its LDS holds: 8000 keys, six passes 190 -> 47 us.  Above, 1.1e5
     // keys 265 -> 92 us, 2.1e6 371 -> 190, 1.7e7 1576 -> 956, 1.3e8 11.2 -> 10.6 ms, against a
     // digit-major table scanned as one array and transposed, and four waves a workgroup.
-    if (n <= SORT_SMALL) {
+    if (n <= SORT_SMALL && !skip) {
         hipLaunchKernelGGL(k_radix_small, dim3(1), dim3(1024), 0, s, ctx->key, ctx->idx,
                            (uint32_t)n, first_pass);
         return dzs_check_launch(ctx, "radix_small");
@@ -458,19 +470,19 @@ dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s, int first_pas
     for (int pass = first_pass; pass < 8; ++pass) {
         const int shift = 8 * pass;
         hipLaunchKernelGGL(k_radix_hist, dim3(tiles), dim3(SORT_THREADS), 0, s, kin, n, shift,
-                           tab);
+                           tab, skip);
         DZS_TRY(dzs_check_launch(ctx, "radix_hist"));
         if (nseg > 1) {
             hipLaunchKernelGGL(k_col_sum, dim3(nseg), dim3(256), 0, s, (const uint32_t *)tab,
-                               tiles, seg, segsum);
+                               tiles, seg, segsum, skip);
             DZS_TRY(dzs_check_launch(ctx, "col_sum"));
         }
         hipLaunchKernelGGL(k_col_scan, dim3(nseg), dim3(256), 0, s, tab, tiles, seg,
-                           (const uint32_t *)segsum, totals);
+                           (const uint32_t *)segsum, totals, skip);
         DZS_TRY(dzs_check_launch(ctx, "col_scan"));
         hipLaunchKernelGGL(k_radix_scatter, dim3(tiles), dim3(SORT_THREADS), 0, s, kin, iin,
                            kout, iout, n, shift, (const uint32_t *)tab,
-                           (const uint32_t *)totals);
+                           (const uint32_t *)totals, skip);
         DZS_TRY(dzs_check_launch(ctx, "radix_scatter"));
         uint64_t *tk = kin; kin = kout; kout = tk;
         uint32_t *ti = iin; iin = iout; iout = ti;

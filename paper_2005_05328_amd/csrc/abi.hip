@@ -217,10 +217,12 @@ static dzs_status create(dzs_ctx *c, const dzs_capacity *cap) {
                    o_tn = carve(off_t, 4 * tw),
                    o_tp = carve(off_t, 4 * dzs_tree_span_words(n)), o_gf = carve(off_t, n),
                    o_gc = carve(off_t, 4 * gw), o_gs = carve(off_t, 4 * gw);
-    const uint64_t o_head = carve(off_d, 4 * n), o_flag = carve(off_d, 4 * n),
-                   o_scan = carve(off_d, 4 * n), o_new = carve(off_d, 48 * n),
-                   o_nmult = carve(off_d, 4 * n), o_nid = carve(off_d, 4 * n),
-                   o_perm = carve(off_d, 4 * n);
+    // (the coarsening's buffers follow the staging rows, through which it compacts the state)
+    carve(off_d, DZS_ROW_BYTES * n);
+    const uint64_t o_head = carve(off_d, 4 * n), o_keep = carve(off_d, n),
+                   o_cnt = carve(off_d, 4 * gw), o_scan = carve(off_d, 4 * gw),
+                   o_list = carve(off_d, 4 * (n + 1)), o_rank = carve(off_d, 4 * n),
+                   o_stat = carve(off_d, 4 * DZS_STAT_WORDS);
     DZS_TRY(alloc(c, &c->arena, off_t > off_d ? off_t : off_d));
     c->arena_bytes = off_t > off_d ? off_t : off_d;
     char *A = c->arena;
@@ -239,12 +241,12 @@ static dzs_status create(dzs_ctx *c, const dzs_capacity *cap) {
     c->grp_cnt = (uint32_t *)(A + o_gc);
     c->grp_scan = (uint32_t *)(A + o_gs);
     c->dz_head = (uint32_t *)(A + o_head);
-    c->dz_flag = (uint32_t *)(A + o_flag);
+    c->dz_keep = (uint8_t *)(A + o_keep);
+    c->dz_cnt = (uint32_t *)(A + o_cnt);
     c->dz_scan = (uint32_t *)(A + o_scan);
-    c->dz_new = (double *)(A + o_new);
-    c->dz_newmult = (uint32_t *)(A + o_nmult);
-    c->dz_newid = (uint32_t *)(A + o_nid);
-    c->dz_perm = (uint32_t *)(A + o_perm);
+    c->dz_list = (uint32_t *)(A + o_list);
+    c->dz_rank = (uint32_t *)(A + o_rank);
+    c->dz_stat = (uint32_t *)(A + o_stat);
     DZS_TRY(alloc(c, &c->bstate, 64));
     DZS_HIP(c, hipMemset(c->bstate, 0, 64 * sizeof(uint32_t)));
     DZS_TRY(alloc(c, &c->grp_first, n + 1));
@@ -316,9 +318,10 @@ static dzs_status create(dzs_ctx *c, const dzs_capacity *cap) {
     }
     DZS_TRY(alloc(c, &c->d_small, 64));
     void *h = nullptr;
-    DZS_HIP(c, hipHostMalloc(&h, 64 * sizeof(uint32_t), hipHostMallocDefault));
+    DZS_HIP(c, hipHostMalloc(&h, (64 + DZS_STAT_WORDS) * sizeof(uint32_t),
+                             hipHostMallocDefault));
     c->h_small = (uint32_t *)h;
-    memset(c->h_small, 0, 64 * sizeof(uint32_t));
+    memset(c->h_small, 0, (64 + DZS_STAT_WORDS) * sizeof(uint32_t));
     return DZS_OK;
 }
 
@@ -527,8 +530,6 @@ extern "C" dzs_status dzs_coarsen(dzs_ctx *ctx, const dzs_box *box, dzs_particle
     if (dyn)  // before the sort, which leaves g behind
         DZS_TRY(dzs_coarsen_amin(ctx, box, inout, prm, s));
     DZS_TRY(sort_state(ctx, box, inout, 1, 0, s));
-    DZS_HIP(ctx, hipMemcpyAsync(ctx->dz_perm, ctx->idx, sizeof(uint32_t) * inout->n,
-                                hipMemcpyDeviceToDevice, s));
     return dzs_coarsen_sorted(ctx, box, inout, prm, group_of, report, s);
 }
 
@@ -717,8 +718,6 @@ extern "C" dzs_status kdk_step(dzs_ctx *ctx, const dzs_box *box, dzs_particles *
             DZS_TRY(dzs_coarsen_amin(ctx, box, st, &prm->coarsen, s, ctx->idx));
         if (aold_ok)
             DZS_TRY(dzs_permute_f32(ctx, ctx->aold, ctx->idx, st->n, s));
-        DZS_HIP(ctx, hipMemcpyAsync(ctx->dz_perm, ctx->idx, sizeof(uint32_t) * st->n,
-                                    hipMemcpyDeviceToDevice, s));
         const uint64_t n_in = st->n;
         DZS_TRY(dzs_coarsen_sorted(ctx, box, st, &prm->coarsen, nullptr, report, s));
         if (st->n == n_in) {
@@ -962,8 +961,6 @@ extern "C" dzs_status kdk_step_hier(dzs_ctx *ctx, const dzs_box *box, dzs_partic
         if (prm->coarsen.criterion == DZS_CRIT_DYNAMICAL)
             DZS_TRY(dzs_coarsen_amin(ctx, box, st, &prm->coarsen, s));
         DZS_TRY(sort_state(ctx, box, st, 1, 1, s));
-        DZS_HIP(ctx, hipMemcpyAsync(ctx->dz_perm, ctx->idx, sizeof(uint32_t) * st->n,
-                                    hipMemcpyDeviceToDevice, s));
         const uint64_t n_in = st->n;
         DZS_TRY(dzs_coarsen_sorted(ctx, box, st, &prm->coarsen, nullptr, report, s));
         if (st->n != n_in && st->n > 0) {

@@ -2,12 +2,13 @@
 //
 // The paper walks the tree from the root and replaces every node that meets the merging
 // criterion by one particle, without descending further.  Equivalently, every particle joins
-// its shallowest qualifying ancestor.  On the GPU the levels are processed from k_min down
-// to the finest: at level k the first particle of each level-k cube (a contiguous run of the
-// (key, id)-sorted state) sums its cube's members in order — mult, mult*x and mult*p with
-// Neumaier compensation — tests the criterion, and if it holds stamps the cube's members
-// with its own index.  Particles stamped at a shallower level are skipped.  A compaction then
-// writes survivors and one new particle per stamped cube, in sorted order.
+// its shallowest qualifying ancestor.  On the GPU the levels go from k_min down: at level
+// k the first particle of each level-k cube (a contiguous run of the (key, id)-sorted state)
+// that holds two or more stands for its cube.  Its members are summed in order — mult, mult*x
+// and mult*p with Neumaier compensation —, the criterion is tested, and if it holds the members
+// are stamped with the first one's index and the sum takes the first one's row.  Particles
+// stamped at a shallower level are skipped.  A compaction then keeps the rows of survivors and
+// of first members, in sorted order.
 //
 // The node sums, the centre of mass, the minimum-image distance and the threshold comparison
 // use the exact operation sequence of the definition (no contraction), so the grouping is
@@ -28,12 +29,12 @@ struct neumaier {
     double sum, comp;
 };
 
+// (the larger of sum and v first, by selects: a branch here costs more than the sum)
 __device__ __forceinline__ void nm_add(neumaier &a, double v) {
     const double t = a.sum + v;
-    if (fabs(a.sum) >= fabs(v))
-        a.comp += (a.sum - t) + v;
-    else
-        a.comp += (v - t) + a.sum;
+    const bool big = fabs(a.sum) >= fabs(v);
+    const double hi = big ? a.sum : v, lo = big ? v : a.sum;
+    a.comp += (hi - t) + lo;
     a.sum = t;
 }
 
@@ -41,113 +42,335 @@ __device__ __forceinline__ double nm_value(const neumaier &a) { return a.sum + a
 
 struct dz_level_args {
     uint64_t n;
-    int k, crit;
-    double L, T2;
-    double Gm0, lk2, Rb, alpha;       // dynamical criterion
+    int k0, k1, crit;                 // the levels of this launch
+    double L, iL;                     // box side, 1 / L
+    double T2[DZS_KEY_BITS + 1], T2_max;   // levels whose threshold exceeds T2_max merge nothing
+    double Gm0, Rb, alpha;            // dynamical criterion
     const unsigned long long *amin2;  // bits of min g.g inside the lightcone (device)
     double xo[3];
     const uint64_t *key;
-    const double *x, *y, *z, *px, *py, *pz;
-    const uint32_t *mult, *id;
+    double *f[6];                     // x, y, z, px, py, pz
+    uint32_t *mult, *id;
+    uint8_t *type;
     uint32_t *head;
-    double *nx, *ny, *nz, *npx, *npy, *npz;
-    uint32_t *nmult, *nid;
+    uint8_t *keep;                    // 0: a member of a group, not its first
+    int fresh;                        // no row is a member of a group yet
+    uint32_t *stat;                   // groups made, over DZ_STATS words a cache line apart
 };
 
 // Largest minimum-image |x - x_obs| along one axis over the cube [a, a + l), widened by a
 // margin far above the rounding of the keys and of the centre of mass.
-__device__ __forceinline__ double dz_axis_far(double a, double l, double xo, double L) {
+// (iL = 1/L: its rounding is far below the margin too.)
+__device__ __forceinline__ double dz_axis_far(double a, double l, double xo, double L, double iL) {
     const double m = 1e-9 * L;
     const double u = a - m - xo, v = a + l + m - xo;
     // the farthest offset, L/2 (mod L), lies inside [u, v]
-    if (ceil((u - 0.5 * L) / L) <= floor((v - 0.5 * L) / L))
+    if (ceil((u - 0.5 * L) * iL) <= floor((v - 0.5 * L) * iL))
         return 0.5 * L;
-    const double wu = u - L * floor(u / L + 0.5), wv = v - L * floor(v / L + 0.5);
+    const double wu = u - L * floor(u * iL + 0.5), wv = v - L * floor(v * iL + 0.5);
     return fmax(fabs(wu), fabs(wv));
 }
 
-__global__ __launch_bounds__(DZ_THREADS) void k_dz_level(dz_level_args A) {
-    const uint64_t i = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
-    if (i >= A.n || A.head[i] != DZ_NONE)
-        return;
-    const int sh = 3 * (DZS_KEY_BITS - A.k);
-    const uint64_t pk = A.key[i] >> sh;
-    if (i > 0 && (A.key[i - 1] >> sh) == pk)
-        return;  // not the first member of its level-k cube
-    {
-        // A cube whose every point is too close to merge is skipped before its members are
-        // visited: this bound never excludes a cube the criterion would merge.
-        const double l = ldexp(A.L, -A.k);
-        const double fx = dz_axis_far((double)dzs_compact3(pk >> 2) * l, l, A.xo[0], A.L);
-        const double fy = dz_axis_far((double)dzs_compact3(pk >> 1) * l, l, A.xo[1], A.L);
-        const double fz = dz_axis_far((double)dzs_compact3(pk) * l, l, A.xo[2], A.L);
-        const double far2 = fx * fx + fy * fy + fz * fz;
-        if (A.crit == DZS_CRIT_GEOMETRIC) {
-            if (far2 * (1.0 + 1e-12) <= A.T2)
-                return;
-        } else {
-            const double Dmax = sqrt(far2) * (1.0 + 1e-12) - A.Rb;
-            if (!(Dmax > 0.0))
-                return;
-            const double amin = sqrt(__longlong_as_double((long long)*A.amin2));
-            const double D2 = Dmax * Dmax;
-            if ((A.Gm0 * 2.0) * A.lk2 >= (A.alpha * amin) * (D2 * D2) * (1.0 + 1e-9))
-                return;
+#define DZ_TILE 256          // particles of a workgroup, whose cubes it owns
+#define DZ_LT 128            // threads: 16 cubes at a time
+#define DZ_WINDOW 336        // rows held in LDS: the tile and what its last cube has past it
+#define DZ_UNROLL 4          // members loaded together
+#define DZ_ONE 256           // particles a cube from which a level takes its own launch
+#define DZ_STATS 16          // counters of groups, a cache line apart
+
+// Rows t0 .. t0 + len - 1 of the state, keys one more on either side (where there are any), and
+// which rows are members of a group already.  Rows behind are read from memory.
+struct dz_window {
+    double f[6][DZ_WINDOW + 1];
+    uint64_t key[DZ_WINDOW + 2];   // key[1] is row t0's
+    uint32_t mult[DZ_WINDOW], id[DZ_WINDOW];
+    uint8_t done[DZ_WINDOW];
+};
+
+struct dz_sum {
+    neumaier S;
+    uint64_t K;
+    uint32_t min_id;
+};
+
+// One lane's sum over members 0 .. n - 1, in their order.  (Past the last, zeros: they change
+// neither the sum nor its compensation, which are never -0.)
+__device__ __forceinline__ void dz_members(uint32_t n, const double *src, const uint32_t *mult,
+                                           const uint32_t *id, dz_sum &a) {
+    for (uint32_t r = 0; r < n; r += DZ_UNROLL) {
+        double v[DZ_UNROLL];
+        uint32_t mu[DZ_UNROLL], ids[DZ_UNROLL];
+#pragma unroll
+        for (uint32_t q = 0; q < DZ_UNROLL; ++q) {
+            const uint32_t j = min(r + q, n - 1);
+            v[q] = src[j];
+            mu[q] = mult[j];
+            ids[q] = id[j];
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < DZ_UNROLL; ++q) {
+            const bool in = r + q < n;
+            const uint32_t m = in ? mu[q] : 0u;
+            a.K += m;
+            a.min_id = min(a.min_id, ids[q]);
+            nm_add(a.S, in ? (double)m * v[q] : 0.0);
         }
     }
-    uint64_t e = i + 1;
-    while (e < A.n && (A.key[e] >> sh) == pk)
-        ++e;
-    if (e - i < 2)
-        return;
-    neumaier S[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-    neumaier P[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-    uint64_t K = 0;
-    uint32_t min_id = 0xffffffffu;
-    for (uint64_t r = i; r < e; ++r) {
-        const uint32_t mu = A.mult[r];
-        const double m = (double)mu;
-        K += mu;
-        nm_add(S[0], m * A.x[r]);
-        nm_add(S[1], m * A.y[r]);
-        nm_add(S[2], m * A.z[r]);
-        nm_add(P[0], m * A.px[r]);
-        nm_add(P[1], m * A.py[r]);
-        nm_add(P[2], m * A.pz[r]);
-        const uint32_t idr = A.id[r];
-        min_id = idr < min_id ? idr : min_id;
+}
+
+// Largest squared distance from the observer over the level-k cube of key prefix pk.
+__device__ __forceinline__ double dz_far2(const dz_level_args &A, int k, uint64_t pk) {
+    const double l = ldexp(A.L, -k);
+    const double fx = dz_axis_far((double)dzs_compact3(pk >> 2) * l, l, A.xo[0], A.L, A.iL);
+    const double fy = dz_axis_far((double)dzs_compact3(pk >> 1) * l, l, A.xo[1], A.L, A.iL);
+    const double fz = dz_axis_far((double)dzs_compact3(pk) * l, l, A.xo[2], A.L, A.iL);
+    return fx * fx + fy * fy + fz * fz;
+}
+
+// True where no level-k cube whose points all lie within far2 can merge: such cubes are skipped
+// before their members are visited.
+__device__ __forceinline__ bool dz_near(const dz_level_args &A, int k, double far2) {
+    if (A.crit == DZS_CRIT_GEOMETRIC)
+        return far2 * (1.0 + 1e-12) <= A.T2[k];
+    const double Dmax = sqrt(far2) * (1.0 + 1e-12) - A.Rb;
+    if (!(Dmax > 0.0))
+        return true;
+    const double l = ldexp(A.L, -k);
+    const double amin = sqrt(__longlong_as_double((long long)*A.amin2));
+    const double D2 = Dmax * Dmax;
+    return (A.Gm0 * 2.0) * (l * l) >= (A.alpha * amin) * (D2 * D2) * (1.0 + 1e-9);
+}
+
+// Key of row i >= t0 - 1.
+__device__ __forceinline__ uint64_t dz_key(const dz_level_args &A, const dz_window &W, uint64_t t0,
+                                           uint64_t i) {
+    const uint64_t o = i + 1 - t0;
+    return o < DZ_WINDOW + 2 ? W.key[o] : A.key[i];
+}
+
+// One cube at level k whose first member is i, worked on by 8 lanes: each of the six sums, the
+// multiplicity and the lowest id is one lane's, in the members' order.
+__device__ __forceinline__ void dz_cube(const dz_level_args &A, int k, uint64_t i, dz_window &W,
+                                        uint64_t t0, uint32_t len, uint32_t *s_groups) {
+    const uint32_t lane = threadIdx.x & 7u, shift = threadIdx.x & 56u;
+    const int sh = 3 * (DZS_KEY_BITS - k);
+    const uint64_t pk = dz_key(A, W, t0, i) >> sh;
+    const double l = ldexp(A.L, -k), lk2 = l * l;
+    // the last member: strides of 8, then longer while they stay inside, then shorter
+    uint64_t e = i;
+    for (uint64_t stride = 8;;) {
+        const uint64_t r = e + stride * (lane + 1u);
+        const bool in = r < A.n && (dz_key(A, W, t0, r) >> sh) == pk;
+        const uint32_t m = (uint32_t)__popc((uint32_t)(__ballot(in) >> shift) & 0xffu);
+        e += stride * m;
+        if (m == 8u) {
+            stride *= 8;
+        } else {
+            if (stride == 1)
+                break;
+            stride /= 8;
+        }
     }
+    ++e;
+    const uint32_t ax = lane < 6u ? lane : 5u;
+    dz_sum a = {{0.0, 0.0}, 0, 0xffffffffu};
+    if (e - t0 <= len)
+        dz_members((uint32_t)(e - i), W.f[ax] + (i - t0), W.mult + (i - t0), W.id + (i - t0), a);
+    else
+        dz_members((uint32_t)(e - i), A.f[ax] + i, A.mult + i, A.id + i, a);
+    const uint64_t K = a.K;
     const double Kd = (double)K;
-    const double X = dzs_wrap(nm_value(S[0]) / Kd, A.L);
-    const double Y = dzs_wrap(nm_value(S[1]) / Kd, A.L);
-    const double Z = dzs_wrap(nm_value(S[2]) / Kd, A.L);
-    const double dx = dzs_min_image(X - A.xo[0], A.L);
-    const double dy = dzs_min_image(Y - A.xo[1], A.L);
-    const double dz = dzs_min_image(Z - A.xo[2], A.L);
+    double val = nm_value(a.S) / Kd;
+    if (lane < 3u)
+        val = dzs_wrap(val, A.L);
+    const double dd = dzs_min_image(
+        val - (lane == 0u ? A.xo[0] : lane == 1u ? A.xo[1] : A.xo[2]), A.L);
+    const double dx = __shfl(dd, 0, 8), dy = __shfl(dd, 1, 8), dz = __shfl(dd, 2, 8);
     const double d2 = dx * dx + dy * dy + dz * dz;
     if (A.crit == DZS_CRIT_GEOMETRIC) {
-        if (!(d2 > A.T2))
+        if (!(d2 > A.T2[k]))
             return;
     } else {
         const double D = sqrt(d2) - A.Rb;
         if (!(D > 0.0))
             return;
         const double amin = sqrt(__longlong_as_double((long long)*A.amin2));
-        const double lhs = (A.Gm0 * Kd) * A.lk2;
+        const double lhs = (A.Gm0 * Kd) * lk2;
         const double rhs = (A.alpha * amin) * ((D * D) * (D * D));
         if (!(lhs < rhs))
             return;
     }
-    for (uint64_t r = i; r < e; ++r)
+    for (uint64_t r = i + lane; r < e; r += 8) {
         A.head[r] = (uint32_t)i;
-    A.nx[i] = X;
-    A.ny[i] = Y;
-    A.nz[i] = Z;
-    A.npx[i] = nm_value(P[0]) / Kd;
-    A.npy[i] = nm_value(P[1]) / Kd;
-    A.npz[i] = nm_value(P[2]) / Kd;
-    A.nmult[i] = (uint32_t)K;
-    A.nid[i] = min_id;
+        A.keep[r] = r == i;
+        if (r - t0 < len)
+            W.done[r - t0] = 1u;
+    }
+    if (lane < 6u) {
+        A.f[lane][i] = val;
+    } else if (lane == 6u) {
+        A.mult[i] = (uint32_t)K;
+        A.type[i] = 1u;
+    } else {
+        A.id[i] = a.min_id;
+        atomicAdd(s_groups, 1u);
+    }
+}
+
+// Levels k0 .. k1.  A workgroup owns the level-k0 cubes that begin in its tile of DZ_TILE
+// particles (to the end of the last, which may lie past the tile), and with them every cube of
+// the deeper levels inside: the levels follow each other without another launch.  At each level
+// the first members of cubes of two or more are queued in LDS and worked on densely, 8 lanes a
+// cube; the levels end with the deepest that two neighbouring keys share.
+//
+// Bound by latency: finding the cubes, their distances, the rows and the sums (in the members'
+// order) follow each other, and 14 waves a CU hide a third of it.  Small workgroups, so that
+// many are at different places: 256 particles by 128 threads 67 us on 884736 particles (27 a
+// cube at k_min) and 150 us on 128^3, 512 by 256 79 and 172, 1024 by 256 85 and 185; rows from
+// memory instead of LDS 75 and 163.  One thread a cube, every lane between two first members
+// idle, and a launch a level took 282 us (17 levels) and 700 us (21).
+__global__ __launch_bounds__(DZ_LT, 4) void k_dz_levels(dz_level_args A) {
+    __shared__ dz_window W;
+    __shared__ uint16_t s_queue[DZ_TILE], s_work[DZ_TILE / 2];
+    __shared__ uint32_t s_cnt, s_n, s_groups, s_first, s_last, s_live;
+    __shared__ int s_deep;
+    __shared__ unsigned long long s_far;
+    const uint32_t tid = threadIdx.x;
+    const uint64_t t0 = (uint64_t)blockIdx.x * DZ_TILE;
+    const uint64_t t1 = t0 + DZ_TILE < A.n ? t0 + DZ_TILE : A.n;
+    const uint32_t wlen = (uint32_t)(A.n - t0 < DZ_WINDOW ? A.n - t0 : DZ_WINDOW);
+    const int sh0 = 3 * (DZS_KEY_BITS - A.k0);
+    const bool multi = A.k1 > A.k0;
+    if (tid == 0) {
+        s_groups = 0u;
+        s_first = s_last = 0xffffffffu;
+        s_deep = 0;
+        s_far = 0ull;
+    }
+    for (uint32_t o = tid; o < wlen + 2; o += DZ_LT)
+        if (t0 + o >= 1 && t0 + o - 1 < A.n)
+            W.key[o] = A.key[t0 + o - 1];
+    for (uint32_t o = tid; o < wlen; o += DZ_LT)
+        W.done[o] = A.fresh ? 0u : A.head[t0 + o] != DZ_NONE;
+    __syncthreads();
+    const auto key = [&](uint64_t i) { return dz_key(A, W, t0, i); };
+    uint64_t s0 = t0, s1 = t1;
+    if (multi) {
+        // from the first level-k0 cube that begins in the tile to the first that begins after it
+        for (uint32_t o = tid; o < (uint32_t)(t1 - t0); o += DZ_LT)
+            if (t0 + o == 0 || (W.key[o] ^ W.key[o + 1]) >> sh0) {
+                atomicMin(&s_first, o);
+                break;
+            }
+        __syncthreads();
+        if (s_first == 0xffffffffu)
+            return;
+        s0 = t0 + s_first;
+        const uint64_t last = key(t1 - 1) >> sh0;
+        while (s1 < A.n) {
+            const uint64_t i = s1 + tid;
+            if (i >= A.n || (key(i) >> sh0) != last)
+                atomicMin(&s_last, tid);
+            __syncthreads();
+            const uint32_t f = s_last;
+            __syncthreads();   // read by all before the next round writes it
+            s1 += f == 0xffffffffu ? DZ_LT : f;
+            if (f != 0xffffffffu)
+                break;
+        }
+    }
+    // the deepest level that two neighbours of the range share, and the largest distance of its
+    // level-k0 cubes (every cube of a deeper level lies in one of them): levels at which that is
+    // too close to merge are skipped, all of them inside the lightcone
+    int deep = 0;
+    for (uint64_t b0 = s0; b0 < s1; b0 += DZ_TILE) {
+        if (tid == 0)
+            s_cnt = 0u;
+        __syncthreads();
+        const uint32_t len = (uint32_t)(s1 - b0 < DZ_TILE ? s1 - b0 : DZ_TILE);
+        for (uint32_t o = tid; o < len; o += DZ_LT) {
+            const uint64_t i = b0 + o, ki = key(i);
+            if (i + 1 < A.n) {
+                const uint64_t x = ki ^ key(i + 1);
+                deep = max(deep, x ? DZS_KEY_BITS - 1 - (63 - (int)__clzll((long long)x)) / 3
+                                   : DZS_KEY_BITS);
+            }
+            if (i == 0 || (key(i - 1) ^ ki) >> sh0)
+                s_queue[atomicAdd(&s_cnt, 1u)] = (uint16_t)o;
+        }
+        __syncthreads();
+        const uint32_t cnt = s_cnt;
+        double far2 = 0.0;
+        for (uint32_t c = tid; c < cnt; c += DZ_LT)
+            far2 = fmax(far2, dz_far2(A, A.k0, key(b0 + s_queue[c]) >> sh0));
+        if (far2 > 0.0)
+            atomicMax(&s_far, (unsigned long long)__double_as_longlong(far2));
+        __syncthreads();
+    }
+    if (deep)
+        atomicMax(&s_deep, deep);
+    __syncthreads();
+    const int k1 = min(A.k1, s_deep);
+    const double range_far2 = __longlong_as_double((long long)s_far) * (1.0 + 1e-9);
+    const auto skipped = [&](int k) {
+        return (A.crit == DZS_CRIT_GEOMETRIC && A.T2[k] > A.T2_max) || dz_near(A, k, range_far2);
+    };
+    int k = A.k0;
+    while (k <= k1 && skipped(k))
+        ++k;
+    if (k > k1)
+        return;   // no two particles share a cube that could merge
+    for (uint32_t o = tid; o < wlen; o += DZ_LT) {
+#pragma unroll
+        for (int f = 0; f < 6; ++f)
+            W.f[f][o] = A.f[f][t0 + o];
+        W.mult[o] = A.mult[t0 + o];
+        W.id[o] = A.id[t0 + o];
+    }
+    for (; k <= k1; ++k) {
+        if (skipped(k))
+            continue;
+        const int sh = 3 * (DZS_KEY_BITS - k);
+        if (tid == 0)
+            s_live = 0u;
+        bool live = false;   // a particle was in no group before this level
+        for (uint64_t b0 = s0; b0 < s1; b0 += DZ_TILE) {
+            const uint32_t len = (uint32_t)(s1 - b0 < DZ_TILE ? s1 - b0 : DZ_TILE);
+            __syncthreads();   // the stamps and the queue of the cubes before
+            if (tid == 0)
+                s_cnt = s_n = 0u;
+            __syncthreads();
+            for (uint32_t o = tid; o < len; o += DZ_LT) {
+                const uint64_t i = b0 + o;
+                if (i - t0 < wlen ? W.done[i - t0] != 0u : A.head[i] != DZ_NONE)
+                    continue;
+                live = true;
+                if (i + 1 >= A.n)
+                    continue;
+                const uint64_t pk = key(i) >> sh;
+                if ((key(i + 1) >> sh) == pk && (i == 0 || (key(i - 1) >> sh) != pk))
+                    s_queue[atomicAdd(&s_cnt, 1u)] = (uint16_t)o;
+            }
+            __syncthreads();
+            const uint32_t cnt = s_cnt;
+            for (uint32_t c = tid; c < cnt; c += DZ_LT)
+                if (!dz_near(A, k, dz_far2(A, k, key(b0 + s_queue[c]) >> sh)))
+                    s_work[atomicAdd(&s_n, 1u)] = s_queue[c];
+            __syncthreads();
+            const uint32_t work = s_n;
+            for (uint32_t c = tid >> 3; c < work; c += DZ_LT / 8)
+                dz_cube(A, k, b0 + s_work[c], W, t0, wlen, &s_groups);
+        }
+        if (live)
+            s_live = 1u;
+        __syncthreads();
+        if (s_live == 0u)
+            break;
+        __syncthreads();   // read before the next level clears it
+    }
+    __syncthreads();
+    if (tid == 0 && s_groups)
+        atomicAdd(&A.stat[(blockIdx.x % DZ_STATS) * 16u], s_groups);
 }
 
 // The smallest g.g among particles strictly inside R_lc + b of the observer (minimum image);
@@ -242,92 +465,39 @@ dzs_status dzs_coarsen_rekey(dzs_ctx *ctx, const dzs_box *box, const dzs_particl
     return DZS_OK;
 }
 
-__global__ __launch_bounds__(DZ_THREADS) void k_dz_init(uint64_t n, uint32_t *head) {
+__global__ __launch_bounds__(DZ_THREADS) void k_dz_init(uint64_t n, uint32_t *head, uint8_t *keep,
+                                                        uint32_t *stat) {
     const uint64_t i = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
-    if (i < n)
+    if (i < n) {
         head[i] = DZ_NONE;
+        keep[i] = 1u;
+    }
+    if (i < DZ_STATS)
+        stat[i * 16u] = 0u;
 }
 
-// survivors and group heads emit one output particle each
-__global__ __launch_bounds__(DZ_THREADS) void k_dz_flags(uint64_t n, const uint32_t *head,
-                                                         uint32_t *flag) {
-    const uint64_t i = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
-    if (i < n)
-        flag[i] = (head[i] == DZ_NONE || head[i] == (uint32_t)i) ? 1u : 0u;
-}
-
-template <typename T>
-__global__ __launch_bounds__(DZ_THREADS) void k_dz_emit(uint64_t n, const uint32_t *head,
-                                                        const uint32_t *scan, const T *old_val,
-                                                        const T *new_val, T *out) {
-    const uint64_t i = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
-    if (i >= n)
-        return;
-    const uint32_t h = head[i];
-    if (h == DZ_NONE)
-        out[scan[i]] = old_val[i];
-    else if (h == (uint32_t)i)
-        out[scan[i]] = new_val[i];
-}
-
-__global__ __launch_bounds__(DZ_THREADS) void k_dz_type(uint64_t n, const uint32_t *head,
-                                                        const uint32_t *scan,
-                                                        const uint8_t *old_type, uint8_t *out) {
-    const uint64_t i = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
-    if (i >= n)
-        return;
-    const uint32_t h = head[i];
-    if (h == DZ_NONE)
-        out[scan[i]] = old_type[i];
-    else if (h == (uint32_t)i)
-        out[scan[i]] = 1u;
+// The place after the compaction of each kept row, then of every entry particle's group.
+__global__ __launch_bounds__(DZ_THREADS) void k_dz_rank(const uint32_t *__restrict__ n_new,
+                                                        const uint32_t *__restrict__ list,
+                                                        uint32_t *__restrict__ rank) {
+    const uint64_t j = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
+    if (j < *n_new)
+        rank[list[j]] = (uint32_t)j;
 }
 
 __global__ __launch_bounds__(DZ_THREADS) void k_dz_groupmap(uint64_t n, const uint32_t *head,
-                                                            const uint32_t *scan,
+                                                            const uint32_t *rank,
                                                             const uint32_t *perm,
                                                             uint32_t *group_of) {
     const uint64_t i = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
     if (i >= n)
         return;
     const uint32_t h = head[i];
-    group_of[perm[i]] = scan[h == DZ_NONE ? (uint32_t)i : h];
+    group_of[perm[i]] = rank[h == DZ_NONE ? (uint32_t)i : h];
 }
 
-__global__ __launch_bounds__(DZ_THREADS) void k_dz_count_heads(uint64_t n, const uint32_t *head,
-                                                               uint32_t *count) {
-    const uint64_t i = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
-    const bool is_head = i < n && head[i] == (uint32_t)i;
-    const uint64_t m = __ballot(is_head);
-    if ((threadIdx.x & 63) == 0 && m)
-        atomicAdd(count, (uint32_t)__popcll(m));
-}
-
-template <typename T>
-__global__ __launch_bounds__(DZ_THREADS) void k_dz_copy(uint64_t n, const T *src, T *dst) {
-    const uint64_t i = (uint64_t)blockIdx.x * DZ_THREADS + threadIdx.x;
-    if (i < n)
-        dst[i] = src[i];
-}
-
-template <typename T>
-static dzs_status emit_field(dzs_ctx *ctx, uint64_t n, uint64_t n_new, T *arr, const T *new_val,
-                             hipStream_t s) {
-    T *tmp = (T *)ctx->gather_tmp;
-    hipLaunchKernelGGL(k_dz_emit<T>, dim3(blocks_for(n, DZ_THREADS)), dim3(DZ_THREADS), 0, s, n,
-                       (const uint32_t *)ctx->dz_head, (const uint32_t *)ctx->dz_scan,
-                       (const T *)arr, new_val, tmp);
-    DZS_TRY(dzs_check_launch(ctx, "dz_emit"));
-    if (n_new > 0) {
-        hipLaunchKernelGGL(k_dz_copy<T>, dim3(blocks_for(n_new, DZ_THREADS)), dim3(DZ_THREADS), 0,
-                           s, n_new, (const T *)tmp, arr);
-        DZS_TRY(dzs_check_launch(ctx, "dz_copy"));
-    }
-    return DZS_OK;
-}
-
-// State already sorted by (key, id) with ctx->key holding the sorted keys and ctx->dz_perm
-// the entry index of each sorted slot.
+// State already sorted by (key, id) with ctx->key holding the sorted keys and ctx->idx the
+// entry index of each sorted slot.
 dzs_status dzs_coarsen_sorted(dzs_ctx *ctx, const dzs_box *box, dzs_particles *p,
                               const dzs_coarsen_params *prm, uint32_t *group_of,
                               dzs_coarsen_report *report, hipStream_t s) {
@@ -341,12 +511,14 @@ dzs_status dzs_coarsen_sorted(dzs_ctx *ctx, const dzs_box *box, dzs_particles *p
     }
     if (n == 0)
         return DZS_OK;
-    double T2[DZS_KEY_BITS + 1];
-    dzs_merge_thresholds(box->L, prm->R_lc, prm->b, dyn ? 1.0 : prm->theta, T2);
-    const uint64_t cap = ctx->cap_n;
     dz_level_args A;
+    dzs_merge_thresholds(box->L, prm->R_lc, prm->b, dyn ? 1.0 : prm->theta, A.T2);
+    // geometric: no centre of mass lies beyond sqrt(3)/2 L (minimum image), so a level whose
+    // threshold exceeds it cannot merge anything
+    A.T2_max = 0.75 * box->L * box->L * (1.0 + 1e-9);
     A.n = n;
     A.L = box->L;
+    A.iL = 1.0 / box->L;
     A.crit = dyn ? DZS_CRIT_DYNAMICAL : DZS_CRIT_GEOMETRIC;
     A.Gm0 = box->G * box->m0;
     A.Rb = prm->R_lc + prm->b;
@@ -355,49 +527,63 @@ dzs_status dzs_coarsen_sorted(dzs_ctx *ctx, const dzs_box *box, dzs_particles *p
     for (int d = 0; d < 3; ++d)
         A.xo[d] = prm->x_obs[d];
     A.key = ctx->key;
-    A.x = p->x; A.y = p->y; A.z = p->z; A.px = p->px; A.py = p->py; A.pz = p->pz;
+    double *const f[6] = {p->x, p->y, p->z, p->px, p->py, p->pz};
+    for (int k = 0; k < 6; ++k)
+        A.f[k] = f[k];
     A.mult = p->mult;
     A.id = p->id;
+    A.type = p->type;
     A.head = ctx->dz_head;
-    A.nx = ctx->dz_new; A.ny = ctx->dz_new + cap; A.nz = ctx->dz_new + 2 * cap;
-    A.npx = ctx->dz_new + 3 * cap; A.npy = ctx->dz_new + 4 * cap; A.npz = ctx->dz_new + 5 * cap;
-    A.nmult = ctx->dz_newmult;
-    A.nid = ctx->dz_newid;
+    A.keep = ctx->dz_keep;
+    A.stat = ctx->dz_stat;
+    uint32_t *total = ctx->dz_stat + 16 * DZ_STATS;
     const uint32_t blocks = blocks_for(n, DZ_THREADS);
     {
         dzs_timed t(ctx, KC_DZS_LEVELS, s);
-        hipLaunchKernelGGL(k_dz_init, dim3(blocks), dim3(DZ_THREADS), 0, s, n, ctx->dz_head);
+        hipLaunchKernelGGL(k_dz_init, dim3(blocks), dim3(DZ_THREADS), 0, s, n, ctx->dz_head,
+                           ctx->dz_keep, ctx->dz_stat);
         DZS_TRY(dzs_check_launch(ctx, "dz_init"));
-        for (int k = prm->k_min; k <= DZS_KEY_BITS; ++k) {
-            // geometric: no centre of mass lies beyond sqrt(3)/2 L (minimum image), so a level
-            // whose threshold exceeds it cannot merge anything
-            if (!dyn && T2[k] > 0.75 * box->L * box->L * (1.0 + 1e-9))
+        // The levels whose cubes hold more than DZ_ONE particles on average take a launch each
+        // (a workgroup that owned such a cube would work on everything in it alone); all deeper
+        // ones share one.
+        for (int k = prm->k_min; k <= DZS_KEY_BITS;) {
+            A.k0 = k;
+            A.k1 = (n >> (3 * k)) > DZ_ONE ? k : DZS_KEY_BITS;
+            A.fresh = k == prm->k_min;
+            k = A.k1 + 1;
+            if (!dyn && A.k0 == A.k1 && A.T2[A.k0] > A.T2_max)
                 continue;
-            A.k = k;
-            A.T2 = T2[k];
-            const double lk = ldexp(box->L, -k);
-            A.lk2 = lk * lk;
-            hipLaunchKernelGGL(k_dz_level, dim3(blocks), dim3(DZ_THREADS), 0, s, A);
-            DZS_TRY(dzs_check_launch(ctx, "dz_level"));
+            hipLaunchKernelGGL(k_dz_levels, dim3(blocks_for(n, DZ_TILE)), dim3(DZ_LT), 0, s, A);
+            DZS_TRY(dzs_check_launch(ctx, "dz_levels"));
         }
     }
-    uint64_t n_new, n_heads;
+    uint64_t n_new, n_heads = 0;
     {
         dzs_timed t(ctx, KC_DZS_COMPACT, s);
-        hipLaunchKernelGGL(k_dz_flags, dim3(blocks), dim3(DZ_THREADS), 0, s, n,
-                           (const uint32_t *)ctx->dz_head, ctx->dz_flag);
-        DZS_TRY(dzs_check_launch(ctx, "dz_flags"));
-        DZS_TRY(dzs_scan_u32(ctx, ctx->dz_flag, ctx->dz_scan, n, ctx->d_small + 8, s));
-        DZS_HIP(ctx, hipMemsetAsync(ctx->d_small + 9, 0, sizeof(uint32_t), s));
-        hipLaunchKernelGGL(k_dz_count_heads, dim3(blocks), dim3(DZ_THREADS), 0, s, n,
-                           (const uint32_t *)ctx->dz_head, ctx->d_small + 9);
-        DZS_TRY(dzs_check_launch(ctx, "dz_count_heads"));
-        DZS_HIP(ctx, hipMemcpyAsync(ctx->h_small + 8, ctx->d_small + 8,
-                                    (DZS_SMALL_AMIN + 2 - 8) * sizeof(uint32_t),
+        DZS_TRY(dzs_flag_list(ctx, n, ctx->dz_keep, ctx->dz_cnt, ctx->dz_scan, total, ctx->dz_list,
+                              s));
+        if (group_of) {
+            // (the counters' copy below waits for these as well)
+            hipLaunchKernelGGL(k_dz_rank, dim3(blocks), dim3(DZ_THREADS), 0, s,
+                               (const uint32_t *)total, (const uint32_t *)ctx->dz_list,
+                               ctx->dz_rank);
+            DZS_TRY(dzs_check_launch(ctx, "dz_rank"));
+            hipLaunchKernelGGL(k_dz_groupmap, dim3(blocks), dim3(DZ_THREADS), 0, s, n,
+                               (const uint32_t *)ctx->dz_head, (const uint32_t *)ctx->dz_rank,
+                               (const uint32_t *)ctx->idx, group_of);
+            DZS_TRY(dzs_check_launch(ctx, "dz_groupmap"));
+        }
+        uint32_t *h = ctx->h_small + 64;
+        DZS_HIP(ctx, hipMemcpyAsync(h, ctx->dz_stat, DZS_STAT_WORDS * sizeof(uint32_t),
                                     hipMemcpyDeviceToHost, s));
+        if (dyn)
+            DZS_HIP(ctx, hipMemcpyAsync(ctx->h_small + DZS_SMALL_AMIN,
+                                        ctx->d_small + DZS_SMALL_AMIN, 2 * sizeof(uint32_t),
+                                        hipMemcpyDeviceToHost, s));
         DZS_HIP(ctx, hipStreamSynchronize(s));
-        n_new = ctx->h_small[8];
-        n_heads = ctx->h_small[9];
+        n_new = h[16 * DZ_STATS];
+        for (int k = 0; k < DZ_STATS; ++k)
+            n_heads += h[16 * k];
         if (dyn && report) {
             unsigned long long bits;
             memcpy(&bits, ctx->h_small + DZS_SMALL_AMIN, sizeof(bits));
@@ -405,35 +591,13 @@ dzs_status dzs_coarsen_sorted(dzs_ctx *ctx, const dzs_box *box, dzs_particles *p
             memcpy(&g2, &bits, sizeof(g2));
             report->a_min = sqrt(g2);
         }
-        if (group_of) {
-            hipLaunchKernelGGL(k_dz_groupmap, dim3(blocks), dim3(DZ_THREADS), 0, s, n,
-                               (const uint32_t *)ctx->dz_head, (const uint32_t *)ctx->dz_scan,
-                               (const uint32_t *)ctx->dz_perm, group_of);
-            DZS_TRY(dzs_check_launch(ctx, "dz_groupmap"));
-        }
-        if (n_new != n) {
-            DZS_TRY(emit_field<double>(ctx, n, n_new, p->x, A.nx, s));
-            DZS_TRY(emit_field<double>(ctx, n, n_new, p->y, A.ny, s));
-            DZS_TRY(emit_field<double>(ctx, n, n_new, p->z, A.nz, s));
-            DZS_TRY(emit_field<double>(ctx, n, n_new, p->px, A.npx, s));
-            DZS_TRY(emit_field<double>(ctx, n, n_new, p->py, A.npy, s));
-            DZS_TRY(emit_field<double>(ctx, n, n_new, p->pz, A.npz, s));
-            DZS_TRY(emit_field<uint32_t>(ctx, n, n_new, p->mult, ctx->dz_newmult, s));
-            DZS_TRY(emit_field<uint32_t>(ctx, n, n_new, p->id, ctx->dz_newid, s));
-            uint8_t *tmp = (uint8_t *)ctx->gather_tmp;
-            hipLaunchKernelGGL(k_dz_type, dim3(blocks), dim3(DZ_THREADS), 0, s, n,
-                               (const uint32_t *)ctx->dz_head, (const uint32_t *)ctx->dz_scan,
-                               (const uint8_t *)p->type, tmp);
-            DZS_TRY(dzs_check_launch(ctx, "dz_type"));
-            hipLaunchKernelGGL(k_dz_copy<uint8_t>, dim3(blocks_for(n_new, DZ_THREADS)),
-                               dim3(DZ_THREADS), 0, s, n_new, (const uint8_t *)tmp, p->type);
-            DZS_TRY(dzs_check_launch(ctx, "dz_copy_type"));
-        }
     }
+    p->n = n_new;
+    if (n_new != n)
+        DZS_TRY(dzs_permute_state(ctx, p, ctx->dz_list, 0, s));
     if (report) {
         report->n_after = n_new;
         report->n_groups = n_heads;
     }
-    p->n = n_new;
     return DZS_OK;
 }

@@ -211,14 +211,14 @@ struct dzs_ctx {
 
     // ---- DZS
     uint32_t *dz_head = nullptr;     // group head (sorted index) or 0xffffffff
-    uint32_t *dz_flag = nullptr, *dz_scan = nullptr;
-    double *dz_new = nullptr;        // 6 * cap: merged x,y,z,px,py,pz at the head slot
-    uint32_t *dz_newmult = nullptr, *dz_newid = nullptr;
-    uint32_t *dz_perm = nullptr;     // entry index of each sorted slot
+    uint8_t *dz_keep = nullptr;      // row kept by the compaction
+    uint32_t *dz_cnt = nullptr, *dz_scan = nullptr;   // kept rows by tile
+    uint32_t *dz_list = nullptr, *dz_rank = nullptr;  // the kept rows; a kept row's place
+    uint32_t *dz_stat = nullptr;     // DZS_STAT_WORDS counters
 
     // ---- small device / host scalars
     uint32_t *d_small = nullptr;  // 64 words of device scratch (DZS_SMALL_* slots)
-    uint32_t *h_small = nullptr;  // 64 words of pinned host memory
+    uint32_t *h_small = nullptr;  // 64 + DZS_STAT_WORDS words of pinned host memory
 
     // ---- timing
     bool timing = false;
@@ -437,7 +437,10 @@ dzs_status dzs_gather_u32(dzs_ctx *ctx, const uint32_t *src, const uint32_t *per
 // tree.hip
 uint64_t dzs_tree_scan_words(uint64_t n);   // words of tree_cnt and tree_scan
 uint64_t dzs_tree_span_words(uint64_t n);   // words of tree_span
-uint64_t dzs_tree_flag_tiles(uint64_t n);   // words of grp_cnt and grp_scan
+uint64_t dzs_tree_flag_tiles(uint64_t n);   // words of a flag list's cnt and scan
+// The indices i < n with flag[i] = 1 in order, list[*total] = n behind them (total: device).
+dzs_status dzs_flag_list(dzs_ctx *ctx, uint64_t n, const uint8_t *flag, uint32_t *cnt,
+                         uint32_t *scan, uint32_t *total, uint32_t *list, hipStream_t s);
 // Tree build state words (ctx->bstate) that dzs_check reads: sticky error flags.
 #define DZS_BS_OVERFLOW 3   // the tree needed more than the node capacity
 #define DZS_BS_BADINPUT 40  // tree_force: an input out of key order under presorted, or a
@@ -509,6 +512,8 @@ dzs_status dzs_pm_run_batch(dzs_ctx *ctx, const dzs_particles *p, int precision,
 // coarsen.hip
 // d_small word slots: 8 the coarsening survivor count, 9 its head count, 16..17 the bits of
 // the dynamical criterion's min g.g (8-byte aligned).
+#define DZS_ROW_BYTES 57        // a staged row: six doubles, mult, id, type
+#define DZS_STAT_WORDS 272      // dz_stat: 16 counters of groups, 16 words apart, and the kept rows
 #define DZS_SMALL_AMIN 16
 // d_small word 20: set when the keys of a coarsened state are out of order
 #define DZS_SMALL_UNSORTED 20

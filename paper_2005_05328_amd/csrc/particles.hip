@@ -448,8 +448,8 @@ dzs_status dzs_launch_drift_lc(dzs_ctx *ctx, const dzs_box *box, const dzs_parti
     return launch_drift<false>(ctx, box, p, lc, ring, do_lc, do_drift, s, false, 0, nullptr, none);
 }
 
-// The staging rows: the tree's and the coarsening's arena, which holds nothing between the walk
-// of one step and the build (or coarsening) of the next.
+// The staging rows (DZS_ROW_BYTES a row): the arena's first bytes, which hold nothing between
+// the walk of one step and the build of the next; the coarsening's buffers lie behind them.
 static dzs_rows staging(dzs_ctx *ctx) {
     const uint64_t n = ctx->cap_n;
     dzs_rows r;

@@ -650,6 +650,17 @@ __global__ __launch_bounds__(TB_THREADS) void k_flag_place(uint32_t n,
         grp_first[*total] = n;
 }
 
+dzs_status dzs_flag_list(dzs_ctx *ctx, uint64_t n, const uint8_t *flag, uint32_t *cnt,
+                         uint32_t *scan, uint32_t *total, uint32_t *list, hipStream_t s) {
+    const uint32_t tiles = (uint32_t)dzs_tree_flag_tiles(n);
+    hipLaunchKernelGGL(k_flag_count, dim3(tiles), dim3(TB_THREADS), 0, s, (uint32_t)n, flag, cnt);
+    DZS_TRY(dzs_check_launch(ctx, "flag_count"));
+    DZS_TRY(dzs_scan_u32(ctx, cnt, scan, tiles, total, s));
+    hipLaunchKernelGGL(k_flag_place, dim3(tiles), dim3(TB_THREADS), 0, s, (uint32_t)n, flag,
+                       (const uint32_t *)scan, (const uint32_t *)total, list);
+    return dzs_check_launch(ctx, "flag_place");
+}
+
 __global__ __launch_bounds__(TB_THREADS) void k_fill_u32(uint64_t n, uint32_t *a, uint32_t v);
 
 // flag[i] = 1 for a flagged target
@@ -819,15 +830,8 @@ dzs_status dzs_tree_build_ex(dzs_ctx *ctx, const dzs_box *box, uint64_t n64, con
     DZS_TRY(tree_moments(ctx, box, n, x, y, z, mult, boxes, 0, (uint32_t)group_size, KB, s));
     {
         dzs_timed t(ctx, KC_TREE_GROUPS, s);
-        const uint32_t tiles = (uint32_t)dzs_tree_flag_tiles(n);
-        hipLaunchKernelGGL(k_flag_count, dim3(tiles), dim3(TB_THREADS), 0, s, n,
-                           (const uint8_t *)ctx->grp_flag, ctx->grp_cnt);
-        DZS_TRY(dzs_check_launch(ctx, "flag_count"));
-        DZS_TRY(dzs_scan_u32(ctx, ctx->grp_cnt, ctx->grp_scan, tiles, bs + BS_GROUPS, s));
-        hipLaunchKernelGGL(k_flag_place, dim3(tiles), dim3(TB_THREADS), 0, s, n,
-                           (const uint8_t *)ctx->grp_flag, (const uint32_t *)ctx->grp_scan,
-                           (const uint32_t *)(bs + BS_GROUPS), ctx->grp_first);
-        DZS_TRY(dzs_check_launch(ctx, "flag_place"));
+        DZS_TRY(dzs_flag_list(ctx, n, ctx->grp_flag, ctx->grp_cnt, ctx->grp_scan, bs + BS_GROUPS,
+                              ctx->grp_first, s));
     }
     ctx->tree_built = true;
     ctx->tree_n = n;

@@ -20,7 +20,7 @@
 #define SORT_ITEMS 8
 #define SORT_TILE (SORT_THREADS * SORT_ITEMS)
 #define SORT_SEG 64        // tiles of a column segment (more above 512 segments)
-#define SORT_SMALL 8192    // keys one workgroup sorts in LDS
+#define SORT_SMALL 32768   // keys whose places are counted
 
 // ---------------------------------------------------------------------------------------
 // block-wide exclusive scan of one value per thread (256 threads = 4 wave64)
@@ -371,74 +371,76 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     }
 }
 
-// All passes of at most SORT_SMALL keys by one workgroup, the keys in registers and LDS.
-__global__ __launch_bounds__(1024) void k_radix_small(uint64_t *__restrict__ key,
-                                                      uint32_t *__restrict__ idx, uint32_t n,
-                                                      int first_pass) {
-    constexpr int WAVES = 16, ROUNDS = SORT_SMALL / 1024;
-    __shared__ uint64_t s_key[SORT_SMALL];
-    __shared__ uint32_t s_idx[SORT_SMALL];
-    __shared__ uint32_t s_wcnt[WAVES][256];
-    __shared__ uint32_t s_wave[4];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    const uint32_t q0 = wave * (ROUNDS * 64);
-    uint64_t k[ROUNDS];
-    uint32_t id[ROUNDS], pos[ROUNDS];
-#pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        const uint32_t i = q0 + (uint32_t)r * 64u + lane;
-        k[r] = i < n ? key[i] : 0ull;
-        id[r] = i < n ? idx[i] : 0u;
-    }
-    for (int pass = first_pass; pass < 8; ++pass) {
-        const int shift = 8 * pass;
-        for (uint32_t e = tid; e < WAVES * 256u; e += 1024u)
-            (&s_wcnt[0][0])[e] = 0u;
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ROUNDS; ++r)
-            pos[r] = wave_rank((uint32_t)(k[r] >> shift) & 255u,
-                               q0 + (uint32_t)r * 64u + lane < n, lt_mask, s_wcnt[wave]);
-        __syncthreads();
-        uint32_t c = 0;
-        if (tid < 256u)
-            for (int w = 0; w < WAVES; ++w)
-                c += s_wcnt[w][tid];
-        uint32_t run = excl_scan_256(c, s_wave);
-        if (tid < 256u)
-            for (int w = 0; w < WAVES; ++w) {
-                const uint32_t t = s_wcnt[w][tid];
-                s_wcnt[w][tid] = run;
-                run += t;
-            }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ROUNDS; ++r)
-            if (q0 + (uint32_t)r * 64u + lane < n) {
-                const uint32_t at = s_wcnt[wave][(uint32_t)(k[r] >> shift) & 255u] + pos[r];
-                s_key[at] = k[r];
-                s_idx[at] = id[r];
-            }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-            const uint32_t i = q0 + (uint32_t)r * 64u + lane;
-            if (i < n) {
-                k[r] = s_key[i];
-                id[r] = s_idx[i];
-            }
+// At most SORT_SMALL keys: the place of each is counted, against all others, over the whole GPU,
+// and a second launch puts them there.  The passes of a radix sort are a chain of short launches
+// at these sizes (one workgroup for all passes of 8000 keys took 47 us on one CU of 256, from
+// 190 by launches); n^2 comparisons spread evenly.  Bound by latency, then by the comparisons:
+// 4000 keys 16 us, 8000 19, 16384 33, 32768 87, where six passes take as long (40000: 103).
+// Segments of 128 keys are as fast up to 16384 and slower above (116), of 512 slower below (27).
+#define RANK_THREADS 256
+#define RANK_SEG 256       // keys that a workgroup compares its RANK_THREADS keys with
+__global__ __launch_bounds__(RANK_THREADS) void k_rank_count(const uint64_t *__restrict__ key,
+                                                             const uint32_t *__restrict__ idx,
+                                                             uint32_t n, int shift,
+                                                             uint32_t *__restrict__ part,
+                                                             uint64_t *__restrict__ key_in,
+                                                             uint32_t *__restrict__ idx_in) {
+    __shared__ __align__(16) uint64_t s_key[RANK_SEG];
+    const uint32_t i = blockIdx.x * RANK_THREADS + threadIdx.x, j0 = blockIdx.y * RANK_SEG;
+    const uint32_t cnt = min(n - j0, (uint32_t)RANK_SEG);
+    // (keys that fill the segment up are above every other: counted nowhere)
+    for (uint32_t j = threadIdx.x; j < RANK_SEG; j += RANK_THREADS)
+        s_key[j] = j < cnt ? key[j0 + j] >> shift : ~0ull;
+    uint64_t k = 0;
+    if (i < n) {
+        k = key[i];
+        if (blockIdx.y == 0) {
+            key_in[i] = k;
+            idx_in[i] = idx[i];
         }
-        __syncthreads();
+        k >>= shift;
     }
+    __syncthreads();
+    // equal keys keep their order: those of segments before the thread's block come first, those
+    // of segments after it behind
+    uint32_t rank = 0;
+    const uint32_t b0 = blockIdx.x * RANK_THREADS;
+    const auto count = [&](const auto &before) {
+        for (uint32_t j = 0; j < RANK_SEG; j += 16) {
+            ulonglong2 v[8];   // read together, then compared
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        const uint32_t i = q0 + (uint32_t)r * 64u + lane;
-        if (i < n) {
-            key[i] = k[r];
-            idx[i] = id[r];
+            for (int q = 0; q < 8; ++q)
+                v[q] = *(const ulonglong2 *)(s_key + j + 2 * q);
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                rank += (uint32_t)before(v[q].x, j + 2 * q) + (uint32_t)before(v[q].y, j + 2 * q + 1);
         }
-    }
+    };
+    if (j0 + RANK_SEG <= b0)
+        count([&](uint64_t v, uint32_t) { return v <= k; });
+    else if (j0 >= b0 + RANK_THREADS)
+        count([&](uint64_t v, uint32_t) { return v < k; });
+    else
+        count([&](uint64_t v, uint32_t j) { return v < k || (v == k && j0 + j < i); });
+    if (i < n)
+        part[blockIdx.y * n + i] = rank;
+}
+
+__global__ __launch_bounds__(RANK_THREADS) void k_rank_place(const uint64_t *__restrict__ key_in,
+                                                             const uint32_t *__restrict__ idx_in,
+                                                             uint32_t n, uint32_t segs,
+                                                             const uint32_t *__restrict__ part,
+                                                             uint64_t *__restrict__ key,
+                                                             uint32_t *__restrict__ idx) {
+    const uint32_t i = blockIdx.x * RANK_THREADS + threadIdx.x;
+    if (i >= n)
+        return;
+    uint32_t rank = 0;
+#pragma unroll 8
+    for (uint32_t g = 0; g < segs; ++g)
+        rank += part[g * n + i];
+    key[rank] = key_in[i];
+    idx[rank] = idx_in[i];
 }
 
 dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s, int first_pass,
@@ -450,13 +452,25 @@ dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s, int first_pas
     if (first_pass < 0 || first_pass > 6 || (first_pass & 1))
         return dzs_fail(ctx, DZS_EINVAL, "radix sort: first pass %d", first_pass);
     dzs_timed t(ctx, KC_SORT, s);
-    // One workgroup up to what its LDS holds: 8000 keys, six passes 190 -> 47 us.  Above, 1.1e5
+    // By counting up to where that takes as long as the passes (see k_rank_count).  Above, 1.1e5
     // keys 265 -> 92 us, 2.1e6 371 -> 190, 1.7e7 1576 -> 956, 1.3e8 11.2 -> 10.6 ms, against a
     // digit-major table scanned as one array and transposed, and four waves a workgroup.
     if (n <= SORT_SMALL && !skip) {
-        hipLaunchKernelGGL(k_radix_small, dim3(1), dim3(1024), 0, s, ctx->key, ctx->idx,
-                           (uint32_t)n, first_pass);
-        return dzs_check_launch(ctx, "radix_small");
+        // scratch: the walk's stacks, which hold nothing outside the walk
+        const uint32_t segs = (uint32_t)((n + RANK_SEG - 1) / RANK_SEG);
+        uint64_t *key_in = (uint64_t *)ctx->walk_stack;
+        uint32_t *idx_in = (uint32_t *)(key_in + n), *part = idx_in + n;
+        static_assert(SORT_SMALL * (3 + (SORT_SMALL + RANK_SEG - 1) / RANK_SEG) <= 4096 * 8192,
+                      "the keys, their indices and the counts fit the walk's stacks");
+        const dim3 blocks((uint32_t)((n + RANK_THREADS - 1) / RANK_THREADS));
+        hipLaunchKernelGGL(k_rank_count, dim3(blocks.x, segs), dim3(RANK_THREADS), 0, s,
+                           (const uint64_t *)ctx->key, (const uint32_t *)ctx->idx, (uint32_t)n,
+                           8 * first_pass, part, key_in, idx_in);
+        DZS_TRY(dzs_check_launch(ctx, "rank_count"));
+        hipLaunchKernelGGL(k_rank_place, blocks, dim3(RANK_THREADS), 0, s,
+                           (const uint64_t *)key_in, (const uint32_t *)idx_in, (uint32_t)n, segs,
+                           (const uint32_t *)part, ctx->key, ctx->idx);
+        return dzs_check_launch(ctx, "rank_place");
     }
     const uint32_t tiles = (uint32_t)((n + SORT_TILE - 1) / SORT_TILE);
     if (256ull * tiles > ctx->hist_cap)

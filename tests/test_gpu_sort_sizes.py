@@ -1,4 +1,4 @@
-"""The radix sort at the edges of its forms: one workgroup (up to 8192 keys), tiles of 4096, column
+"""The sort at the edges of its forms: by counting (up to 32768 keys), tiles of 4096, column
 segments of 64 tiles and several segments.  dzs_sort_state's permutation is the stable order of
 the keys, bit for bit, on scattered, nearly sorted and heavily repeated keys."""
 import numpy as np
@@ -44,4 +44,26 @@ def test_sort_sizes(dz, n, kind):
     assert np.array_equal(perm.cpu().numpy(), ref)
     assert np.array_equal(st.id[:n].cpu().numpy(), ref.astype(np.int32))
     assert np.array_equal(st.px[:n].cpu().numpy(), ps.px[ref])
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [127, 256, 257, 511, 513, 20000, 32767, 32768, 32769])
+@pytest.mark.parametrize("few", [False, True])
+def test_sort_by_counting_sizes(dz, n, few):
+    """Up to 32768 keys are placed by counting, in segments and blocks of 256: the same stable
+    order."""
+    import torch
+    L = 64.0
+    ps = dzs_ics.uniform_random(n, L, seed=n)
+    if few:                  # one cell in eight of 8, equal keys across every segment
+        for a in (ps.x, ps.y, ps.z):
+            a[:] = np.floor(a / (L / 2)) * (L / 2) + 1.0
+    ctx = dz.Context(n, 0)
+    st = dz.State.from_host(ps)
+    perm = torch.zeros(n, dtype=torch.int32, device="cuda")
+    ctx.sort_state(dz.make_box(L, 1.0, 1.0), st, perm=perm)
+    torch.cuda.synchronize()
+    ref = np.argsort(oracle.morton_keys(ps.x, ps.y, ps.z, L), kind="stable")
+    assert np.array_equal(perm.cpu().numpy(), ref)
+    assert np.array_equal(st.id[:n].cpu().numpy(), ref.astype(np.int32))
     ctx.close()

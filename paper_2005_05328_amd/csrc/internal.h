@@ -401,8 +401,7 @@ dzs_status dzs_open_step(dzs_ctx *ctx, const dzs_box *box, const dzs_particles *
 dzs_status dzs_gather_rows(dzs_ctx *ctx, const dzs_particles *p, const uint32_t *perm,
                            hipStream_t s);
 dzs_status dzs_launch_keys(dzs_ctx *ctx, const double *x, const double *y, const double *z,
-                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s,
-                           const uint32_t *skip = nullptr);  // device: not 0, no keys
+                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s);
 dzs_status dzs_permute_state(dzs_ctx *ctx, dzs_particles *p, const uint32_t *perm,
                              int with_g, hipStream_t s);
 dzs_status dzs_gather_f64(dzs_ctx *ctx, const double *src, const uint32_t *perm, double *dst,

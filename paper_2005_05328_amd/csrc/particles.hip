@@ -494,10 +494,9 @@ __global__ __launch_bounds__(PT_THREADS) void k_keys(uint64_t n, const double *_
                                                      const double *__restrict__ y,
                                                      const double *__restrict__ z, double s,
                                                      uint64_t *__restrict__ key,
-                                                     uint32_t *__restrict__ idx,
-                                                     const uint32_t *skip) {
+                                                     uint32_t *__restrict__ idx) {
     uint64_t i = (uint64_t)blockIdx.x * PT_THREADS + threadIdx.x;
-    if (i >= n || (skip && *skip))
+    if (i >= n)
         return;
     key[i] = dzs_morton(x[i], y[i], z[i], s);
     if (idx)
@@ -505,14 +504,13 @@ __global__ __launch_bounds__(PT_THREADS) void k_keys(uint64_t n, const double *_
 }
 
 dzs_status dzs_launch_keys(dzs_ctx *ctx, const double *x, const double *y, const double *z,
-                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s,
-                           const uint32_t *skip) {
+                           uint64_t n, double L, uint64_t *key, uint32_t *idx, hipStream_t s) {
     if (n == 0)
         return DZS_OK;
     const double scale = DZS_KEY_SIDE / L;
     dzs_timed t(ctx, KC_KEYS, s);
     hipLaunchKernelGGL(k_keys, dim3(blocks_for(n, PT_THREADS)), dim3(PT_THREADS), 0, s, n, x, y,
-                       z, scale, key, idx, skip);
+                       z, scale, key, idx);
     return dzs_check_launch(ctx, "keys");
 }
 

@@ -48,8 +48,14 @@ struct pm_batch {
 
 // Particles that the caller passed in no order, put in key order (copies in the context's
 // arena): used when *ordered, which a kernel sets, is 0.  ordered == nullptr: none.
+struct __align__(32) pm_row {
+    double v[3];
+    uint32_t mult, pad;
+};
+
 struct pm_sorted {
     const uint32_t *ordered;
+    pm_row *out;                 // their forces, in the caller's order (accelerations in v)
     const double *x, *y, *z;
     const uint32_t *mult, *perm;
     __device__ __forceinline__ bool used() const { return ordered && *ordered == 0u; }
@@ -818,10 +824,8 @@ template <> struct value_pair<float> {
 // loads and tiles), 128^3 on 256^3 in FP64 128 against 202 with single loads.
 template <typename Rt>
 __device__ __forceinline__ void interp_direct(double x, double y, double z,
-                                              const Rt *__restrict__ phi, uint64_t p, double delta,
-                                              int ng, double *__restrict__ gx,
-                                              double *__restrict__ gy, double *__restrict__ gz,
-                                              int accumulate) {
+                                              const Rt *__restrict__ phi, double delta, int ng,
+                                              Rt &sx, Rt &sy, Rt &sz) {
     double wx[2], wy[2], wz[2];
     const int i = wrap_index(cic_base(x, delta, wx[0], wx[1]), ng);
     const int j = wrap_index(cic_base(y, delta, wy[0], wy[1]), ng);
@@ -848,9 +852,7 @@ __device__ __forceinline__ void interp_direct(double x, double y, double z,
             d[1] = phi[o + (uint32_t)wrap_near(k + c + 1, ng)];
         });
     }
-    Rt sx, sy, sz;
     cic_gradient<Rt>(v, wx, wy, wz, sx, sy, sz);
-    interp_store<Rt>(p, delta, sx, sy, sz, gx, gy, gz, accumulate);
 }
 
 template <typename Rt>
@@ -862,15 +864,47 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm_interp(
     if (p >= n)
         return;
     const uint32_t *mult;
-    const uint64_t out = S.select(x, y, z, mult) ? S.perm[p] : p;
+    const bool sorted = S.select(x, y, z, mult);
     if (B.boxes) {
         const dzs_bbox &bx = B.boxes[B.key[p] >> DZS_BATCH_SHIFT];
         delta = bx.delta;
         ng = bx.ng;
         phi += bx.mesh_off;
     }
-    interp_direct<Rt>(x[p], y[p], z[p], phi, out, delta, ng, gx, gy, gz, accumulate);
+    Rt sx, sy, sz;
+    interp_direct<Rt>(x[p], y[p], z[p], phi, delta, ng, sx, sy, sz);
+    if (sorted) {
+        // one row instead of a line of each of three arrays
+        const double s = -1.0 / delta;
+        pm_row &r = S.out[S.perm[p]];
+        r.v[0] = s * (double)sx;
+        r.v[1] = s * (double)sy;
+        r.v[2] = s * (double)sz;
+    } else {
+        interp_store<Rt>(p, delta, sx, sy, sz, gx, gy, gz, accumulate);
+    }
 }
+
+// The forces of sorted particles to (or onto) the caller's arrays.
+__global__ __launch_bounds__(PM_THREADS) void k_pm_out(uint64_t n, pm_sorted S,
+                                                       double *__restrict__ gx,
+                                                       double *__restrict__ gy,
+                                                       double *__restrict__ gz, int accumulate) {
+    const uint64_t p = (uint64_t)blockIdx.x * PM_THREADS + threadIdx.x;
+    if (p >= n || !S.used())
+        return;
+    const pm_row r = S.out[p];
+    if (accumulate) {
+        gx[p] += r.v[0];
+        gy[p] += r.v[1];
+        gz[p] += r.v[2];
+    } else {
+        gx[p] = r.v[0];
+        gy[p] = r.v[1];
+        gz[p] = r.v[2];
+    }
+}
+
 
 // ---------------------------------------------------------------------------------------
 // host side
@@ -1037,10 +1071,27 @@ __global__ __launch_bounds__(PM_ORDER_SAMPLES) void k_pm_order(uint64_t n, const
         *ordered = 4u * s_near >= 3u * PM_ORDER_SAMPLES;
 }
 
-__global__ __launch_bounds__(PM_THREADS) void k_pm_gather(uint64_t n, const double *__restrict__ x,
-                                                          const double *__restrict__ y,
-                                                          const double *__restrict__ z,
-                                                          const uint32_t *__restrict__ mult,
+// Keys, and the particles as rows, so that each is gathered from one line instead of four.
+__global__ __launch_bounds__(PM_THREADS) void k_pm_rows(uint64_t n, const double *__restrict__ x,
+                                                        const double *__restrict__ y,
+                                                        const double *__restrict__ z,
+                                                        const uint32_t *__restrict__ mult,
+                                                        double scale,
+                                                        const uint32_t *__restrict__ ordered,
+                                                        uint64_t *__restrict__ key,
+                                                        uint32_t *__restrict__ idx,
+                                                        pm_row *__restrict__ row) {
+    const uint64_t i = (uint64_t)blockIdx.x * PM_THREADS + threadIdx.x;
+    if (i >= n || *ordered)
+        return;
+    const pm_row r = {{x[i], y[i], z[i]}, mult[i], 0u};
+    key[i] = dzs_morton(r.v[0], r.v[1], r.v[2], scale);
+    idx[i] = (uint32_t)i;
+    row[i] = r;
+}
+
+__global__ __launch_bounds__(PM_THREADS) void k_pm_gather(uint64_t n,
+                                                          const pm_row *__restrict__ row,
                                                           const uint32_t *__restrict__ perm,
                                                           const uint32_t *__restrict__ ordered,
                                                           double *__restrict__ sx,
@@ -1050,48 +1101,56 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm_gather(uint64_t n, const doub
     const uint64_t i = (uint64_t)blockIdx.x * PM_THREADS + threadIdx.x;
     if (i >= n || *ordered)
         return;
-    const uint32_t p = perm[i];
-    sx[i] = x[p];
-    sy[i] = y[p];
-    sz[i] = z[p];
-    smult[i] = mult[p];
+    const pm_row r = row[perm[i]];
+    sx[i] = r.v[0];
+    sy[i] = r.v[1];
+    sz[i] = r.v[2];
+    smult[i] = r.mult;
 }
 
 // Particles in no order: sorted by the top 15 bits of their Morton keys, two passes (32 cells a
 // side; on finer meshes than 256 points four passes, 1290 cells a side), so that neighbours
 // in memory share mesh lines.  As they come, every one of a particle's 8 atomics and 28 loads
 // is a mesh line of its own, and the atomics of a clump queue on the same points.  Deposit and
-// interpolation with the sort against without: 1e6 clustered particles on 192^3 367 against
-// 708 us, 2e6 clustered on 64^3 384 against 2170, 8e6 uniform on 384^3 3.04 against 6.10 ms.
-// From where it starts to pay: 1.4e5 particles on 64^3 clustered 97 against 129 us, on 32^3
-// uniform 90 against 81; 7e4 on 64^3 97 against 76.  Not on meshes of more than 32 points a
+// interpolation with the sort against without: 1e6 clustered particles on 192^3 312 against
+// 708 us, 2e6 clustered on 64^3 318 against 2170, 8e6 uniform on 384^3 2.43 against 6.10 ms.
+// From where it starts to pay: 1.4e5 particles on 64^3 clustered 98 against 129 us, on 32^3
+// uniform 89 against 81; 7e4 on 64^3 97 against 76.  Not on meshes of more than 32 points a
 // particle, where neighbours share few lines in any order: 1.4e5 on 192^3 161 against 126.
+// Positions go to their place and forces back as rows of 32 bytes, one line each: gathered from
+// four arrays and scattered to three, 1e6 took 66 instead of 25 us and 110 instead of 89, 8e6
+// 0.61 instead of 0.20 ms and 1.17 instead of 0.91.
 #define PM_SORT_MIN 131072
-static const pm_sorted NO_SORT{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+static const pm_sorted NO_SORT{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
 static dzs_status pm_sort(dzs_ctx *ctx, const dzs_particles *p, double L, int ng, pm_sorted *S,
                           hipStream_t s) {
     const uint64_t n = p->n;
     // (a context shell without scratch of its own passes the particles as they are)
     if (n < PM_SORT_MIN || n > 0xffffffffull || (uint64_t)ng * ng * ng > 32 * n || !ctx->arena ||
-        ctx->arena_bytes < 28 * n + 64)
+        ctx->arena_bytes < 60 * n + 64)
         return DZS_OK;
-    double *sx = (double *)ctx->arena, *sy = sx + n, *sz = sy + n;
+    // (the rows are free again once gathered: the forces' rows take their place)
+    pm_row *row = (pm_row *)ctx->arena;
+    double *sx = (double *)(row + n), *sy = sx + n, *sz = sy + n;
     uint32_t *sm = (uint32_t *)(sz + n), *ordered = sm + n;
     {
         dzs_timed t(ctx, KC_KEYS, s);
         hipLaunchKernelGGL(k_pm_order, dim3(1), dim3(PM_ORDER_SAMPLES), 0, s, n, (const double *)p->x,
                            (const double *)p->y, (const double *)p->z, L / 16.0, ordered);
         DZS_TRY(dzs_check_launch(ctx, "pm_order"));
+        hipLaunchKernelGGL(k_pm_rows, dim3(blocks_for(n, PM_THREADS)), dim3(PM_THREADS), 0, s, n,
+                           (const double *)p->x, (const double *)p->y, (const double *)p->z,
+                           (const uint32_t *)p->mult, DZS_KEY_SIDE / L,
+                           (const uint32_t *)ordered, ctx->key, ctx->idx, row);
+        DZS_TRY(dzs_check_launch(ctx, "pm_rows"));
     }
-    DZS_TRY(dzs_launch_keys(ctx, p->x, p->y, p->z, n, L, ctx->key, ctx->idx, s, ordered));
     DZS_TRY(dzs_radix_sort(ctx, n, s, ng > 256 ? 4 : 6, ordered));
     dzs_timed t(ctx, KC_PERMUTE, s);
     hipLaunchKernelGGL(k_pm_gather, dim3(blocks_for(n, PM_THREADS)), dim3(PM_THREADS), 0, s, n,
-                       (const double *)p->x, (const double *)p->y, (const double *)p->z,
-                       (const uint32_t *)p->mult, (const uint32_t *)ctx->idx,
+                       (const pm_row *)row, (const uint32_t *)ctx->idx,
                        (const uint32_t *)ordered, sx, sy, sz, sm);
     DZS_TRY(dzs_check_launch(ctx, "pm_gather"));
-    *S = pm_sorted{ordered, sx, sy, sz, sm, ctx->idx};
+    *S = pm_sorted{ordered, row, sx, sy, sz, sm, ctx->idx};
     return DZS_OK;
 }
 
@@ -1105,7 +1164,12 @@ static dzs_status pm_interp(dzs_ctx *ctx, const dzs_particles *p, int accumulate
                        s, p->n, (const double *)p->x, (const double *)p->y, (const double *)p->z,
                        (const Rt *)ctx->mesh_phi, delta, ng, p->gx, p->gy, p->gz, accumulate, B,
                        S);
-    return dzs_check_launch(ctx, "pm_interp");
+    DZS_TRY(dzs_check_launch(ctx, "pm_interp"));
+    if (!S.ordered)
+        return DZS_OK;
+    hipLaunchKernelGGL(k_pm_out, dim3(blocks_for(p->n, PM_THREADS)), dim3(PM_THREADS), 0, s, p->n,
+                       S, p->gx, p->gy, p->gz, accumulate);
+    return dzs_check_launch(ctx, "pm_out");
 }
 
 // zero fill by a kernel (a memset node in a captured graph is avoided)

@@ -272,6 +272,14 @@ struct dzs_timed {
 // ---------------------------------------------------------------------------------------
 
 // minimum image of one separation component: into [-L/2, L/2)
+// The block that a workgroup works on: each of the 8 XCDs (workgroups go to them in turn) takes
+// one contiguous part of the blocks, so that the lines that neighbouring blocks share, written by
+// one a few bytes at a time and by the next the others, meet in one L2.
+__device__ __forceinline__ uint32_t dzs_xcd_block() {
+    const uint32_t nb = gridDim.x, x = blockIdx.x & 7u, per = nb >> 3, rem = nb & 7u;
+    return x * per + (x < rem ? x : rem) + (blockIdx.x >> 3);
+}
+
 __device__ __forceinline__ double dzs_min_image(double d, double L) {
     if (d >= 0.5 * L)
         d -= L;

@@ -286,13 +286,16 @@ __device__ __forceinline__ uint32_t excl_scan_256(uint32_t v, uint32_t *s_wave) 
 // Each wave ranks its own contiguous part of the tile (rounds of 64 keys, in input order); the
 // waves' counts become offsets (wave 0's keys of a digit first); equal digits keep their order.
 // Bound by the LDS traffic of the ranks and the staging (two workgroups of eight waves a CU)
-// and by HBM: 24 bytes per key and pass.
+// and by HBM: 24 bytes per key and pass.  Neighbouring tiles write neighbouring parts of each
+// digit's run, so an XCD takes tiles that follow each other: six passes of 1.7e7 keys 968 -> 742
+// us (2e6 keys, which the caches hold, 193 either way).
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     const uint64_t *__restrict__ key_in, const uint32_t *__restrict__ idx_in,
     uint64_t *__restrict__ key_out, uint32_t *__restrict__ idx_out, uint64_t n, int shift,
     const uint32_t *__restrict__ tab, const uint32_t *__restrict__ totals, const uint32_t *skip) {
     if (skip && *skip)
         return;
+    const uint32_t blk = dzs_xcd_block();
     constexpr int WAVES = SORT_THREADS / 64;
     constexpr int ROUNDS = SORT_ITEMS;  // rounds of 64 keys per wave
     __shared__ uint64_t s_key[SORT_TILE];
@@ -302,7 +305,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     __shared__ uint32_t s_wave[4];
 
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint64_t base = (uint64_t)blockIdx.x * SORT_TILE;
+    const uint64_t base = (uint64_t)blk * SORT_TILE;
     const uint32_t cnt = (uint32_t)((n - base) < SORT_TILE ? (n - base) : SORT_TILE);
     const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const uint32_t q0 = wave * (ROUNDS * 64);
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
         id[r] = local < cnt ? idx_in[base + local] : 0u;
     }
     // the tile's global start of each digit: the digits below it, and its keys in earlier tiles
-    const uint32_t before = tid < 256u ? tab[(uint64_t)blockIdx.x * 256u + tid] : 0u;
+    const uint32_t before = tid < 256u ? tab[(uint64_t)blk * 256u + tid] : 0u;
     const uint32_t total = tid < 256u ? totals[tid] : 0u;
     for (uint32_t e = tid; e < WAVES * 256u; e += SORT_THREADS)
         (&s_wcnt[0][0])[e] = 0u;
@@ -453,7 +456,7 @@ dzs_status dzs_radix_sort(dzs_ctx *ctx, uint64_t n, hipStream_t s, int first_pas
         return dzs_fail(ctx, DZS_EINVAL, "radix sort: first pass %d", first_pass);
     dzs_timed t(ctx, KC_SORT, s);
     // By counting up to where that takes as long as the passes (see k_rank_count).  Above, 1.1e5
-    // keys 265 -> 92 us, 2.1e6 371 -> 190, 1.7e7 1576 -> 956, 1.3e8 11.2 -> 10.6 ms, against a
+    // keys 265 -> 92 us, 2.1e6 371 -> 190, 1.7e7 1576 -> 742, against a
     // digit-major table scanned as one array and transposed, and four waves a workgroup.
     if (n <= SORT_SMALL && !skip) {
         // scratch: the walk's stacks, which hold nothing outside the walk

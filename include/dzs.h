@@ -288,7 +288,8 @@ typedef struct {
 
 /* Create a context on HIP device `device` and allocate all its scratch for `cap`: about
  * 106 bytes per particle (keys and sort indices 24; one arena of 72 shared by the tree, with
- * node capacity max_particles/2 + 4096, and the DZS coarsening buffers; group starts 4; the
+ * node capacity max_particles/2 + 4096, the rows of a reordering, the DZS coarsening buffers
+ * and pm_force's particles in key order; group starts 4; the
  * relative criterion's |g| 4; time-step bins and the walk's target flags 2), plus 28 bytes per
  * particle of sorted copies for tree_force unless DZS_CAP_NO_COPIES, plus 44 bytes per
  * particle with DZS_CAP_HIER_SPLIT, plus the meshes (32 bytes per cell, 12 with

@@ -1129,6 +1129,7 @@ static dzs_status pm_sort(dzs_ctx *ctx, const dzs_particles *p, double L, int ng
     if (n < PM_SORT_MIN || n > 0xffffffffull || (uint64_t)ng * ng * ng > 32 * n || !ctx->arena ||
         ctx->arena_bytes < 60 * n + 64)
         return DZS_OK;
+    ctx->tree_built = false;   // the arena is the tree's
     // (the rows are free again once gathered: the forces' rows take their place)
     pm_row *row = (pm_row *)ctx->arena;
     double *sx = (double *)(row + n), *sy = sx + n, *sz = sy + n;

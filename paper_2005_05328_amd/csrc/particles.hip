@@ -244,13 +244,11 @@ __device__ __forceinline__ uint64_t batch_key(double x, double y, double z, uint
 //
 // HBM-bound (drift alone: 48 bytes read, 24 written per particle).  The few particles that cross are not
 // solved where they are found, which would hold their whole wave for one or two active lanes:
-// a workgroup of 256 threads takes 1024 particles, queues the crossing ones in LDS and then
-// solves them densely, one atomic on the record count per workgroup.  4,000,037 particles of
+// a workgroup of 256 threads takes 1024 (or 2048) particles, queues the crossing ones in LDS and
+// then solves them densely, one atomic on the record count per workgroup.  4,000,037 particles of
 // which 57,853 cross, emitted and their records copied into a catalogue: 1255 us solving in
-// place by bisection, 121 us so.
-#define LC_ITEMS 4
-#define LC_TILE (PT_THREADS * LC_ITEMS)
-template <bool PBLOCK, bool OPEN>
+// place by bisection, 121 us so, 104 us by 2048.
+template <bool PBLOCK, bool OPEN, int LC_ITEMS>
 __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
     uint64_t n, double *__restrict__ x, double *__restrict__ y, double *__restrict__ z,
     const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ pz,
@@ -259,6 +257,7 @@ __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
     unsigned long long *__restrict__ rec_count, uint32_t *__restrict__ overflow,
     const uint64_t *__restrict__ bfirst, const dzs_bbox *__restrict__ boxes, uint32_t nb,
     open_args O) {
+    constexpr uint32_t LC_TILE = PT_THREADS * LC_ITEMS;
     __shared__ uint16_t s_queue[LC_TILE];
     __shared__ uint32_t s_cnt;
     __shared__ unsigned long long s_base;
@@ -423,18 +422,29 @@ static dzs_status launch_drift(dzs_ctx *ctx, const dzs_box *box, const dzs_parti
         ovf = ring->overflow;
     }
     dzs_timed t(ctx, KC_DRIFT_LC, s);
-    auto launch = [&](auto pblock) {
-        hipLaunchKernelGGL((k_drift_lc<pblock.value, OPEN>), dim3(blocks_for(p->n, LC_TILE)),
-                           dim3(PT_THREADS), 0, s, p->n, p->x, p->y, p->z, (const double *)p->px,
+    auto launch = [&](auto pblock, auto items) {
+        hipLaunchKernelGGL((k_drift_lc<pblock.value, OPEN, items.value>),
+                           dim3(blocks_for(p->n, PT_THREADS * items.value)), dim3(PT_THREADS), 0,
+                           s, p->n, p->x, p->y, p->z, (const double *)p->px,
                            (const double *)p->py, (const double *)p->pz, (const uint32_t *)p->id,
                            (const uint32_t *)p->mult, box->L, A, A_dev, do_lc, do_drift, rec, cap,
                            cnt, ovf, (const uint64_t *)ctx->batch_first,
                            batch ? ctx->batch_box : nullptr, nb, O);
     };
+    // Eight particles a thread queue twice the crossings for a workgroup's dense solves: with
+    // 1.4% crossing, 4e6 particles 103 -> 82 us, 2e6 69 -> 50, 1e6 44 -> 45, 4e5 34 -> 37 (fewer
+    // workgroups than the GPU holds); a step's opening, which also stages rows, loses by it
+    // (256^3 493 -> 509 us).  Sixteen: 93 us.
+    const std::integral_constant<int, 4> four;
+    const std::integral_constant<int, 8> eight;
     if (A_dev)
-        launch(std::true_type());
+        launch(std::true_type(), four);
+    else if constexpr (OPEN)
+        launch(std::false_type(), four);
+    else if (p->n >= 1u << 20)
+        launch(std::false_type(), eight);
     else
-        launch(std::false_type());
+        launch(std::false_type(), four);
     return dzs_check_launch(ctx, "drift_lc");
 }
 

@@ -352,3 +352,33 @@ def test_crossing_queue_edges_and_both_solvers(dz, n, fast):
         # on the sphere, unless the drifted particle left it only through the periodic image
         if np.linalg.norm(d0[:, i[k]] + p * lc.D) > chi1 * (1 + 1e-9):
             assert abs(np.linalg.norm(rec["d"][k]) - oracle.chi(a)) <= 1e-10 * chi0
+
+
+@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 20) + 2047, (1 << 20) + 2049])
+def test_records_of_large_calls_equal_those_of_parts(dz, n):
+    """From 2^20 particles on a workgroup takes 2048 particles instead of 1024: the records of one
+    call are those of two calls over the halves, bit for bit (each particle is solved alone)."""
+    L = 1000.0
+    lc = dz.step_factors(0.90, 0.91, 0.3).lc
+    for d in range(3):
+        lc.x_obs[d] = 0.5 * L
+    ps = dzs_ics.uniform_random(n, L, seed=n % 1000, vel=500.0)
+    ps.id = np.arange(n, dtype=np.uint32)
+    box = dz.make_box(L, 1.0, 1.0)
+    ctx = dz.Context(n, 0)
+    out = []
+    for cuts in ([0, n], [0, n // 2, n]):
+        ring = dz.LCRing(n)
+        ring.reset()
+        for a, b in zip(cuts[:-1], cuts[1:]):
+            part = dzs_ics.uniform_random(b - a, L, seed=1)
+            for k in ("x", "y", "z", "px", "py", "pz", "mult", "id", "type"):
+                setattr(part, k, getattr(ps, k)[a:b])
+            ctx.lightcone_emit(box, dz.State.from_host(part), lc, ring)
+        rec = ring.records()
+        o = np.argsort(rec["id"])
+        out.append({k: rec[k][o] for k in ("id", "mult", "a_cross", "d", "p")})
+        assert rec["overflow"] == 0 and rec["count"] == len(o) > 1000
+    ctx.close()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k

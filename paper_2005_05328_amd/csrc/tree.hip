@@ -923,7 +923,10 @@ dzs_status dzs_check_order(dzs_ctx *ctx, uint64_t n, hipStream_t s) {
 // w = r^2, one per interval of 1/32 of an octave of w (the interval is the exponent and the top
 // five mantissa bits of w, so finding it takes no square root), over the 16 octaves up to the
 // interval of r_cut^2, i.e. r from r_cut / 256.  The cubic of interval j sits in slot j mod 512,
-// so any w finds a slot with one shift and one mask.  Cubics through the four Chebyshev nodes of the
+// so any w finds a slot with one shift and one mask.  Its variable is the offset from the
+// interval's low end over the power of two below it, y = (w - a) 2^-e, which is the low mantissa
+// bits of w as they are: the coefficients are of the size of F in any unit of length (in powers of
+// w - a the last one is some r^-9, past the FP32 range for r below 5.7e-5).  Cubics through the four Chebyshev nodes of the
 // interval: worst error 2e-8 of F at small w, 1e-8 of the unsplit force near r_cut, before the
 // FP32 rounding of the coefficients (the S table below with r^-3 from the hardware 1/sqrt:
 // 8.5e-8 in S and four more roundings).  The walk's set-up kernel computes it for each call.
@@ -931,6 +934,9 @@ dzs_status dzs_check_order(dzs_ctx *ctx, uint64_t n, hipStream_t s) {
 #define WALK_FT_OCT 16
 #define WALK_FT_N (WALK_FT_OCT << WALK_FT_BITS)
 #define WALK_FT_SHIFT (23 - WALK_FT_BITS)
+// the least interval of the table, w from 2^-83: the coefficients, up to some 4 F, are in the FP32
+// range from there on (closer pairs take S and 1/sqrt)
+#define WALK_FT_LEAST ((uint32_t)(127 - 83) << WALK_FT_BITS)
 // FP32, close pairs (inside a spline support, or below the table of F): S(u) from a table of
 // cubics, one per interval of u = r / r_s on [0, r_cut / r_s]: Hermite interpolation of S and
 // dS/du at both ends of each interval (worst absolute error in S below 1e-7 at 64 intervals,
@@ -967,7 +973,7 @@ struct walk_args {
     float4 stab[WALK_TAB_N + 1];  // FP32 form: the cubics of S(u), coefficients of f^0..f^3
     double stab_scale;            // intervals per unit of u (WALK_TAB_N r_s / r_cut)
     const float4 *ftab;           // FP32 form: the cubics of F(w), [WALK_FT_N] (device)
-    float ft_lo;                  // the low end of the table, in its unit of w
+    float ft_lo;                  // the low end of the table of F (in w = r^2)
     // start cells: the walk of a group begins at the level-K nodes (and shallower leaves) of
     // the cells that meet its bounding box grown by r_cut, instead of at the root
     const uint32_t *cell_node;  // [8^K] node covering each level-K cell (Morton order)
@@ -1245,8 +1251,8 @@ template <> struct pair_eval<float, true> {
     __device__ __forceinline__ float far(float w) const {
         const uint32_t bits = __float_as_uint(w);
         const float4 c = ftab[(bits >> WALK_FT_SHIFT) & (uint32_t)(WALK_FT_N - 1)];
-        const float d = w - __uint_as_float(bits & ~((1u << WALK_FT_SHIFT) - 1u));
-        return __builtin_fmaf(__builtin_fmaf(__builtin_fmaf(c.w, d, c.z), d, c.y), d, c.x);
+        const float y = __uint_as_float((bits & ((1u << WALK_FT_SHIFT) - 1u)) | 0x3f800000u) - 1.0f;
+        return __builtin_fmaf(__builtin_fmaf(__builtin_fmaf(c.w, y, c.z), y, c.y), y, c.x);
     }
     // r2 = 0 (the target itself): any finite factor, its separation is zero
     __device__ __forceinline__ float close(float r2, const float *eh, float hi, float hi2) const {
@@ -2189,9 +2195,9 @@ static double split_table_f32(double ucut, float4 *tab) {
 }
 
 // Before a walk: the work counter to zero and, for the FP32 form (tab non-null), the cubics of
-// F(w) = S(sqrt(w) / r_s) / w^1.5 in d = w - a on each interval [a, b) of 2^-WALK_FT_BITS octave
-// from index base: the polynomial through F at the four Chebyshev nodes (Newton's divided
-// differences), in powers of d.
+// F(w) = S(sqrt(w) / r_s) / w^1.5 on each interval [a, a + h) of 2^-WALK_FT_BITS octave from index
+// base: the polynomial through F at the four Chebyshev nodes (Newton's divided differences), in
+// powers of y = 2^-WALK_FT_BITS (w - a) / h.
 __global__ __launch_bounds__(64) void k_walk_setup(uint32_t *counter, float4 *tab, uint32_t base,
                                                    double r_s) {
     const uint32_t j = blockIdx.x * 64u + threadIdx.x;
@@ -2200,11 +2206,13 @@ __global__ __launch_bounds__(64) void k_walk_setup(uint32_t *counter, float4 *ta
     if (!tab || j >= WALK_FT_N)
         return;
     const double a = (double)__uint_as_float((base + j) << WALK_FT_SHIFT);
-    const double h = (double)__uint_as_float((base + j + 1u) << WALK_FT_SHIFT) - a;
+    // (the octave's power of two: the end of the last one is past the FP32 range)
+    const double h = (double)__uint_as_float((base + j) >> WALK_FT_BITS << 23) /
+                     (double)(1 << WALK_FT_BITS);
     const double node[4] = {0.5 - 0.5 * 0.92387953251128674, 0.5 - 0.5 * 0.38268343236508977,
                             0.5 + 0.5 * 0.38268343236508977, 0.5 + 0.5 * 0.92387953251128674};
     double f[4];
-    for (int k = 0; k < 4; ++k) {   // in units of h: x = d / h in [0, 1)
+    for (int k = 0; k < 4; ++k) {   // in units of h: x = (w - a) / h in [0, 1)
         const double w = a + h * node[k], r = sqrt(w), u = r / r_s;
         f[k] = (erfc(0.5 * u) + u * 0.56418958354775629 * exp(-0.25 * u * u)) / (w * r);
     }
@@ -2217,10 +2225,10 @@ __global__ __launch_bounds__(64) void k_walk_setup(uint32_t *counter, float4 *ta
             c[i] = c[i - 1] - node[k] * c[i];
         c[0] = f[k] - node[k] * c[0];
     }
-    const double hi = 1.0 / h;
+    const double s = (double)(1 << WALK_FT_BITS);   // y = x / s
     tab[(base + j) & (uint32_t)(WALK_FT_N - 1)] =
-        make_float4((float)c[0], (float)(c[1] * hi), (float)(c[2] * hi * hi),
-                         (float)(c[3] * hi * hi * hi));
+        make_float4((float)c[0], (float)(c[1] * s), (float)(c[2] * s * s),
+                    (float)(c[3] * s * s * s));
 }
 
 dzs_status dzs_tree_walk(dzs_ctx *ctx, const dzs_box *box, uint64_t n, const double *x,
@@ -2338,7 +2346,8 @@ dzs_status dzs_tree_walk_ex(dzs_ctx *ctx, const dzs_box *box, uint64_t n, const 
     uint32_t ft_bits;
     memcpy(&ft_bits, &ft_top, sizeof(ft_bits));
     ft_bits >>= WALK_FT_SHIFT;
-    const uint32_t ft_base = ft_bits >= WALK_FT_N ? ft_bits - (WALK_FT_N - 1) : 1u;
+    const uint32_t ft_base = ft_bits >= WALK_FT_LEAST + (WALK_FT_N - 1) ? ft_bits - (WALK_FT_N - 1)
+                                                                        : WALK_FT_LEAST;
     const uint32_t ft_lo_bits = ft_base << WALK_FT_SHIFT;
     memcpy(&A.ft_lo, &ft_lo_bits, sizeof(A.ft_lo));
     A.ftab = (const float4 *)ctx->walk_ftab;

@@ -74,7 +74,11 @@ __device__ __forceinline__ double dz_axis_far(double a, double l, double xo, dou
 #define DZ_TILE 256          // particles of a workgroup, whose cubes it owns
 #define DZ_LT 128            // threads: 16 cubes at a time
 #define DZ_WINDOW 336        // rows held in LDS: the tile and what its last cube has past it
-#define DZ_UNROLL 4          // members loaded together
+#define DZ_UNROLL 4          // members loaded together from LDS
+#define DZ_UNROLL_MEM 16     // and from memory, where a load takes a hundred times as long as a sum
+#define DZ_MARK 512          // every DZ_MARK-th particle is a mark: cubes with two marks are large
+#define DZ_MARKS 32          // marks that a workgroup of k_dz_large looks at
+#define DZ_LARGE 512         // its threads: 64 cubes at a time
 #define DZ_ONE 256           // particles a cube from which a level takes its own launch
 #define DZ_STATS 16          // counters of groups, a cache line apart
 
@@ -95,20 +99,21 @@ struct dz_sum {
 
 // One lane's sum over members 0 .. n - 1, in their order.  (Past the last, zeros: they change
 // neither the sum nor its compensation, which are never -0.)
+template <uint32_t U>
 __device__ __forceinline__ void dz_members(uint32_t n, const double *src, const uint32_t *mult,
                                            const uint32_t *id, dz_sum &a) {
-    for (uint32_t r = 0; r < n; r += DZ_UNROLL) {
-        double v[DZ_UNROLL];
-        uint32_t mu[DZ_UNROLL], ids[DZ_UNROLL];
+    for (uint32_t r = 0; r < n; r += U) {
+        double v[U];
+        uint32_t mu[U], ids[U];
 #pragma unroll
-        for (uint32_t q = 0; q < DZ_UNROLL; ++q) {
+        for (uint32_t q = 0; q < U; ++q) {
             const uint32_t j = min(r + q, n - 1);
             v[q] = src[j];
             mu[q] = mult[j];
             ids[q] = id[j];
         }
 #pragma unroll
-        for (uint32_t q = 0; q < DZ_UNROLL; ++q) {
+        for (uint32_t q = 0; q < U; ++q) {
             const bool in = r + q < n;
             const uint32_t m = in ? mu[q] : 0u;
             a.K += m;
@@ -141,6 +146,12 @@ __device__ __forceinline__ bool dz_near(const dz_level_args &A, int k, double fa
     return (A.Gm0 * 2.0) * (l * l) >= (A.alpha * amin) * (D2 * D2) * (1.0 + 1e-9);
 }
 
+// Octal digits that two keys share.
+__device__ __forceinline__ int dz_common(uint64_t a, uint64_t b) {
+    const uint64_t x = a ^ b;
+    return x ? DZS_KEY_BITS - 1 - (63 - (int)__clzll((long long)x)) / 3 : DZS_KEY_BITS;
+}
+
 // Key of row i >= t0 - 1.
 __device__ __forceinline__ uint64_t dz_key(const dz_level_args &A, const dz_window &W, uint64_t t0,
                                            uint64_t i) {
@@ -149,18 +160,21 @@ __device__ __forceinline__ uint64_t dz_key(const dz_level_args &A, const dz_wind
 }
 
 // One cube at level k whose first member is i, worked on by 8 lanes: each of the six sums, the
-// multiplicity and the lowest id is one lane's, in the members' order.
-__device__ __forceinline__ void dz_cube(const dz_level_args &A, int k, uint64_t i, dz_window &W,
+// multiplicity and the lowest id is one lane's, in the members' order.  WINDOW: rows t0 ..
+// t0 + len - 1 are in W.
+template <bool WINDOW>
+__device__ __forceinline__ void dz_cube(const dz_level_args &A, int k, uint64_t i, dz_window *W,
                                         uint64_t t0, uint32_t len, uint32_t *s_groups) {
     const uint32_t lane = threadIdx.x & 7u, shift = threadIdx.x & 56u;
     const int sh = 3 * (DZS_KEY_BITS - k);
-    const uint64_t pk = dz_key(A, W, t0, i) >> sh;
+    const auto key = [&](uint64_t r) { return WINDOW ? dz_key(A, *W, t0, r) : A.key[r]; };
+    const uint64_t pk = key(i) >> sh;
     const double l = ldexp(A.L, -k), lk2 = l * l;
     // the last member: strides of 8, then longer while they stay inside, then shorter
     uint64_t e = i;
     for (uint64_t stride = 8;;) {
         const uint64_t r = e + stride * (lane + 1u);
-        const bool in = r < A.n && (dz_key(A, W, t0, r) >> sh) == pk;
+        const bool in = r < A.n && (key(r) >> sh) == pk;
         const uint32_t m = (uint32_t)__popc((uint32_t)(__ballot(in) >> shift) & 0xffu);
         e += stride * m;
         if (m == 8u) {
@@ -174,10 +188,13 @@ __device__ __forceinline__ void dz_cube(const dz_level_args &A, int k, uint64_t 
     ++e;
     const uint32_t ax = lane < 6u ? lane : 5u;
     dz_sum a = {{0.0, 0.0}, 0, 0xffffffffu};
-    if (e - t0 <= len)
-        dz_members((uint32_t)(e - i), W.f[ax] + (i - t0), W.mult + (i - t0), W.id + (i - t0), a);
+    if (!WINDOW)
+        dz_members<DZ_UNROLL_MEM>((uint32_t)(e - i), A.f[ax] + i, A.mult + i, A.id + i, a);
+    else if (e - t0 <= len)
+        dz_members<DZ_UNROLL>((uint32_t)(e - i), W->f[ax] + (i - t0), W->mult + (i - t0),
+                              W->id + (i - t0), a);
     else
-        dz_members((uint32_t)(e - i), A.f[ax] + i, A.mult + i, A.id + i, a);
+        dz_members<DZ_UNROLL>((uint32_t)(e - i), A.f[ax] + i, A.mult + i, A.id + i, a);
     const uint64_t K = a.K;
     const double Kd = (double)K;
     double val = nm_value(a.S) / Kd;
@@ -203,8 +220,8 @@ __device__ __forceinline__ void dz_cube(const dz_level_args &A, int k, uint64_t 
     for (uint64_t r = i + lane; r < e; r += 8) {
         A.head[r] = (uint32_t)i;
         A.keep[r] = r == i;
-        if (r - t0 < len)
-            W.done[r - t0] = 1u;
+        if (WINDOW && r - t0 < len)
+            W->done[r - t0] = 1u;
     }
     if (lane < 6u) {
         A.f[lane][i] = val;
@@ -217,9 +234,91 @@ __device__ __forceinline__ void dz_cube(const dz_level_args &A, int k, uint64_t 
     }
 }
 
-// Levels k0 .. k1.  A workgroup owns the level-k0 cubes that begin in its tile of DZ_TILE
-// particles (to the end of the last, which may lie past the tile), and with them every cube of
-// the deeper levels inside: the levels follow each other without another launch.  At each level
+// The large cubes of levels k0 .. k1: those that hold two marks (and so every cube of 1024
+// particles or more, and none below 514).  k_dz_levels works on the others, a workgroup on all
+// levels of what begins in its tile; a clump's cubes would keep one workgroup for themselves.  The
+// level-k0 cube of the first mark inside belongs to a workgroup here, with all large cubes in it:
+// their first marks follow from the marks' keys alone, level by level, so it visits particles only
+// where a cube may merge.  Bound by the loads of the longest sum (one cube's members in their
+// order).  1e6 particles, most of them in 8 clumps of scale L/40, that merge at levels well below
+// k0: 2.34 -> 0.71 ms against the clumps in k_dz_levels (1.62 with a thread a cube and a launch a
+// level); 9e5 of 1e6 in a clump of L/200 that is too near to merge 7.0 -> 0.67 (1.0).
+__global__ __launch_bounds__(DZ_LARGE) void k_dz_large(dz_level_args A) {
+    __shared__ uint32_t s_own[DZ_MARKS], s_work[DZ_LARGE];
+    __shared__ uint32_t s_n, s_cnt, s_groups;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t marks = (uint32_t)((A.n + DZ_MARK - 1) / DZ_MARK);
+    const auto mark = [&](uint32_t j) { return A.key[(uint64_t)j * DZ_MARK]; };
+    const auto common = [&](uint32_t a, uint32_t b) { return dz_common(mark(a), mark(b)); };
+    if (tid == 0)
+        s_n = s_groups = 0u;
+    __syncthreads();
+    if (tid < DZ_MARKS) {
+        const uint32_t m = blockIdx.x * DZ_MARKS + tid;
+        if (m + 1 < marks && common(m, m + 1) >= A.k0 && (m == 0 || common(m - 1, m) < A.k0))
+            s_own[atomicAdd(&s_n, 1u)] = m;
+    }
+    __syncthreads();
+    const uint32_t owned = s_n;
+    for (uint32_t w = 0; w < owned; ++w) {
+        const uint32_t m = s_own[w];
+        uint32_t in = m + 1, end = marks;   // the last mark inside, the first behind
+        while (end - in > 1) {
+            const uint32_t mid = in + (end - in) / 2;
+            if (common(m, mid) >= A.k0)
+                in = mid;
+            else
+                end = mid;
+        }
+        for (int k = A.k0; k <= A.k1; ++k) {
+            if (A.crit == DZS_CRIT_GEOMETRIC && A.T2[k] > A.T2_max)
+                continue;
+            const int sh = 3 * (DZS_KEY_BITS - k);
+            bool live = false;   // a large cube of this level that is in no group
+            for (uint32_t b = m; b < end; b += DZ_LARGE) {
+                __syncthreads();   // the stamps and the queue of the cubes before
+                if (tid == 0)
+                    s_cnt = 0u;
+                __syncthreads();
+                const uint32_t j = b + tid;
+                if (j + 1 < end && common(j, j + 1) >= k &&
+                    A.head[(uint64_t)j * DZ_MARK] == DZ_NONE) {
+                    live = true;
+                    if ((j == m || common(j - 1, j) < k) &&
+                        !dz_near(A, k, dz_far2(A, k, mark(j) >> sh)))
+                        s_work[atomicAdd(&s_cnt, 1u)] = j;
+                }
+                __syncthreads();
+                const uint32_t cnt = s_cnt;
+                for (uint32_t c = tid >> 3; c < cnt; c += DZ_LARGE / 8) {
+                    const uint32_t q = s_work[c];
+                    // the first member: after the mark before (outside), at most this one
+                    const uint64_t pk = mark(q) >> sh;
+                    int64_t out = q ? (int64_t)(q - 1) * DZ_MARK : -1, i = (int64_t)q * DZ_MARK;
+                    while (i - out > 1) {
+                        const int64_t mid = out + (i - out) / 2;
+                        if ((A.key[mid] >> sh) == pk)
+                            i = mid;
+                        else
+                            out = mid;
+                    }
+                    dz_cube<false>(A, k, (uint64_t)i, nullptr, 0, 0, &s_groups);
+                }
+            }
+            if (!__syncthreads_or(live ? 1 : 0))
+                break;
+        }
+    }
+    __syncthreads();
+    if (tid == 0 && s_groups)
+        atomicAdd(&A.stat[(blockIdx.x % DZ_STATS) * 16u], s_groups);
+}
+
+// Levels k0 .. k1 (k1 > k0: without the large cubes of k_dz_large, which ran before).  A workgroup
+// owns the cubes that begin in its tile of DZ_TILE particles, each from the first level on, k0 or
+// deeper, at which it is not large, to the end of the last (less than two marks, so less than 1024
+// particles, past the tile), and with them every cube of the deeper levels inside: the levels
+// follow each other without another launch.  At each level
 // the first members of cubes of two or more are queued in LDS and worked on densely, 8 lanes a
 // cube; the levels end with the deepest that two neighbouring keys share.
 //
@@ -232,44 +331,85 @@ __device__ __forceinline__ void dz_cube(const dz_level_args &A, int k, uint64_t 
 __global__ __launch_bounds__(DZ_LT, 4) void k_dz_levels(dz_level_args A) {
     __shared__ dz_window W;
     __shared__ uint16_t s_queue[DZ_TILE], s_work[DZ_TILE / 2];
+    __shared__ uint8_t s_own[DZ_TILE];
     __shared__ uint32_t s_cnt, s_n, s_groups, s_first, s_last, s_live;
-    __shared__ int s_deep;
+    __shared__ int s_deep, s_top;
     __shared__ unsigned long long s_far;
     const uint32_t tid = threadIdx.x;
     const uint64_t t0 = (uint64_t)blockIdx.x * DZ_TILE;
     const uint64_t t1 = t0 + DZ_TILE < A.n ? t0 + DZ_TILE : A.n;
     const uint32_t wlen = (uint32_t)(A.n - t0 < DZ_WINDOW ? A.n - t0 : DZ_WINDOW);
-    const int sh0 = 3 * (DZS_KEY_BITS - A.k0);
     const bool multi = A.k1 > A.k0;
+    static_assert(DZ_MARK % DZ_TILE == 0, "no mark inside a tile but its first particle");
+    // digits shared by the mark at or before the tile and the next, the one before, and of the
+    // next two: a particle's cube of level k is large where k digits are shared by one of these
+    // pairs and by the particle
+    int big0 = -1, big1 = -1, big2 = -1;
+    uint64_t mark0 = 0, mark1 = 0;
+    if (multi) {
+        const uint64_t q = t0 / DZ_MARK * DZ_MARK;
+        mark0 = A.key[q];
+        if (q)
+            big0 = dz_common(A.key[q - DZ_MARK], mark0);
+        if (q + DZ_MARK < A.n) {
+            mark1 = A.key[q + DZ_MARK];
+            big1 = dz_common(mark0, mark1);
+            if (q + 2 * DZ_MARK < A.n)
+                big2 = dz_common(mark1, A.key[q + 2 * DZ_MARK]);
+        }
+    }
+    const bool large = multi && max(big0, max(big1, big2)) >= A.k0;
     if (tid == 0) {
         s_groups = 0u;
         s_first = s_last = 0xffffffffu;
         s_deep = 0;
+        s_top = A.k0;
         s_far = 0ull;
     }
     for (uint32_t o = tid; o < wlen + 2; o += DZ_LT)
         if (t0 + o >= 1 && t0 + o - 1 < A.n)
             W.key[o] = A.key[t0 + o - 1];
     for (uint32_t o = tid; o < wlen; o += DZ_LT)
-        W.done[o] = A.fresh ? 0u : A.head[t0 + o] != DZ_NONE;
+        W.done[o] = A.fresh && !large ? 0u : A.head[t0 + o] != DZ_NONE;
     __syncthreads();
     const auto key = [&](uint64_t i) { return dz_key(A, W, t0, i); };
+    // first level of the tile's particle o (DZS_KEY_BITS + 1: none, its cubes are all large)
+    const auto own = [&](uint32_t o) -> int {
+        if (!large)
+            return A.k0;
+        const uint64_t ki = W.key[o + 1];
+        return max(A.k0, 1 + max(big1, max(min(big0, dz_common(mark0, ki)),
+                                           min(big2, dz_common(mark1, ki)))));
+    };
     uint64_t s0 = t0, s1 = t1;
+    int last_own = A.k0;
     if (multi) {
-        // from the first level-k0 cube that begins in the tile to the first that begins after it
-        for (uint32_t o = tid; o < (uint32_t)(t1 - t0); o += DZ_LT)
-            if (t0 + o == 0 || (W.key[o] ^ W.key[o + 1]) >> sh0) {
+        // from the first cube that begins in the tile to the first that begins after it
+        if (large && tid == 0)
+            s_top = DZS_KEY_BITS + 1;
+        if (large)
+            __syncthreads();
+        for (uint32_t o = tid; o < (uint32_t)(t1 - t0); o += DZ_LT) {
+            const int ow = own(o);
+            if (large)
+                s_own[o] = (uint8_t)ow;
+            if (ow <= DZS_KEY_BITS && (t0 + o == 0 || dz_common(W.key[o], W.key[o + 1]) < ow)) {
                 atomicMin(&s_first, o);
-                break;
+                if (!large)
+                    break;
+                atomicMin(&s_top, ow);
             }
+        }
         __syncthreads();
         if (s_first == 0xffffffffu)
             return;
         s0 = t0 + s_first;
-        const uint64_t last = key(t1 - 1) >> sh0;
-        while (s1 < A.n) {
+        last_own = own((uint32_t)(t1 - t0) - 1u);
+        const int shl = 3 * (DZS_KEY_BITS - last_own);
+        while (last_own <= DZS_KEY_BITS && s1 < A.n) {
+            const uint64_t last = key(t1 - 1) >> shl;
             const uint64_t i = s1 + tid;
-            if (i >= A.n || (key(i) >> sh0) != last)
+            if (i >= A.n || (key(i) >> shl) != last)
                 atomicMin(&s_last, tid);
             __syncthreads();
             const uint32_t f = s_last;
@@ -279,8 +419,12 @@ __global__ __launch_bounds__(DZ_LT, 4) void k_dz_levels(dz_level_args A) {
                 break;
         }
     }
-    // the deepest level that two neighbours of the range share, and the largest distance of its
-    // level-k0 cubes (every cube of a deeper level lies in one of them): levels at which that is
+    // first level of particle i of the range (those past the tile are in the last cube)
+    const auto own_at = [&](uint64_t i) -> int {
+        return !large ? A.k0 : (i < t1 ? (int)s_own[i - t0] : last_own);
+    };
+    // the deepest level that two neighbours of the range share, and the largest distance of the
+    // owned cubes (every cube of a deeper level lies in one of them): levels at which that is
     // too close to merge are skipped, all of them inside the lightcone
     int deep = 0;
     for (uint64_t b0 = s0; b0 < s1; b0 += DZ_TILE) {
@@ -290,19 +434,20 @@ __global__ __launch_bounds__(DZ_LT, 4) void k_dz_levels(dz_level_args A) {
         const uint32_t len = (uint32_t)(s1 - b0 < DZ_TILE ? s1 - b0 : DZ_TILE);
         for (uint32_t o = tid; o < len; o += DZ_LT) {
             const uint64_t i = b0 + o, ki = key(i);
-            if (i + 1 < A.n) {
-                const uint64_t x = ki ^ key(i + 1);
-                deep = max(deep, x ? DZS_KEY_BITS - 1 - (63 - (int)__clzll((long long)x)) / 3
-                                   : DZS_KEY_BITS);
-            }
-            if (i == 0 || (key(i - 1) ^ ki) >> sh0)
+            if (i + 1 < A.n)
+                deep = max(deep, dz_common(ki, key(i + 1)));
+            const int ow = own_at(i);
+            if (i < t1 && ow <= DZS_KEY_BITS && (i == 0 || dz_common(key(i - 1), ki) < ow))
                 s_queue[atomicAdd(&s_cnt, 1u)] = (uint16_t)o;
         }
         __syncthreads();
         const uint32_t cnt = s_cnt;
         double far2 = 0.0;
-        for (uint32_t c = tid; c < cnt; c += DZ_LT)
-            far2 = fmax(far2, dz_far2(A, A.k0, key(b0 + s_queue[c]) >> sh0));
+        for (uint32_t c = tid; c < cnt; c += DZ_LT) {
+            const uint64_t i = b0 + s_queue[c];
+            const int ow = own_at(i);
+            far2 = fmax(far2, dz_far2(A, ow, key(i) >> (3 * (DZS_KEY_BITS - ow))));
+        }
         if (far2 > 0.0)
             atomicMax(&s_far, (unsigned long long)__double_as_longlong(far2));
         __syncthreads();
@@ -315,7 +460,7 @@ __global__ __launch_bounds__(DZ_LT, 4) void k_dz_levels(dz_level_args A) {
     const auto skipped = [&](int k) {
         return (A.crit == DZS_CRIT_GEOMETRIC && A.T2[k] > A.T2_max) || dz_near(A, k, range_far2);
     };
-    int k = A.k0;
+    int k = s_top;
     while (k <= k1 && skipped(k))
         ++k;
     if (k > k1)
@@ -344,8 +489,11 @@ __global__ __launch_bounds__(DZ_LT, 4) void k_dz_levels(dz_level_args A) {
                 const uint64_t i = b0 + o;
                 if (i - t0 < wlen ? W.done[i - t0] != 0u : A.head[i] != DZ_NONE)
                     continue;
+                const int ow = own_at(i);
+                if (ow > DZS_KEY_BITS)
+                    continue;
                 live = true;
-                if (i + 1 >= A.n)
+                if (i + 1 >= A.n || k < ow)
                     continue;
                 const uint64_t pk = key(i) >> sh;
                 if ((key(i + 1) >> sh) == pk && (i == 0 || (key(i - 1) >> sh) != pk))
@@ -359,7 +507,7 @@ __global__ __launch_bounds__(DZ_LT, 4) void k_dz_levels(dz_level_args A) {
             __syncthreads();
             const uint32_t work = s_n;
             for (uint32_t c = tid >> 3; c < work; c += DZ_LT / 8)
-                dz_cube(A, k, b0 + s_work[c], W, t0, wlen, &s_groups);
+                dz_cube<true>(A, k, b0 + s_work[c], &W, t0, wlen, &s_groups);
         }
         if (live)
             s_live = 1u;
@@ -553,6 +701,11 @@ dzs_status dzs_coarsen_sorted(dzs_ctx *ctx, const dzs_box *box, dzs_particles *p
             k = A.k1 + 1;
             if (!dyn && A.k0 == A.k1 && A.T2[A.k0] > A.T2_max)
                 continue;
+            if (A.k1 > A.k0 && n > DZ_MARK) {
+                hipLaunchKernelGGL(k_dz_large, dim3(blocks_for(n, DZ_MARK * DZ_MARKS)),
+                                   dim3(DZ_LARGE), 0, s, A);
+                DZS_TRY(dzs_check_launch(ctx, "dz_large"));
+            }
             hipLaunchKernelGGL(k_dz_levels, dim3(blocks_for(n, DZ_TILE)), dim3(DZ_LT), 0, s, A);
             DZS_TRY(dzs_check_launch(ctx, "dz_levels"));
         }

@@ -1049,26 +1049,39 @@ static int32_t default_chunk(uint64_t n) {
     return c;
 }
 
-// Order of the particles as they come: of neighbours in memory, sampled evenly, are three in
-// four less than a sixteenth of the box apart on every axis?  Key order and lattice order are;
-// of particles in no order, one pair in 500.
-#define PM_ORDER_SAMPLES 1024
+// Order of the particles as they come, from neighbours in memory at 256 places: for three in four
+// of them, is the neighbour less than a quarter as far as another sample, from anywhere?  (Pairs
+// of pairs at equal separations, coincident particles, say nothing.)  In key order it is for 19 in
+// 20, in lattice order for 9 in 10.  Without an order the two separations are alike whatever the
+// set, so it is for half at the most: one dense clump, whose random pairs are all close, as well as
+// a uniform set.  (Separations measured against L / 16 instead took a shuffled set with nine in
+// ten in a clump of L / 200 for ordered: 131,072 on 64^3 4.09 ms.)
+#define PM_ORDER_SAMPLES 256
 __global__ __launch_bounds__(PM_ORDER_SAMPLES) void k_pm_order(uint64_t n, const double *__restrict__ x,
                                                    const double *__restrict__ y,
-                                                   const double *__restrict__ z, double reach,
+                                                   const double *__restrict__ z,
                                                    uint32_t *__restrict__ ordered) {
-    __shared__ uint32_t s_near;
+    __shared__ double s_p[3][PM_ORDER_SAMPLES];
+    __shared__ uint32_t s_near, s_cnt;
     if (threadIdx.x == 0)
-        s_near = 0u;
+        s_near = s_cnt = 0u;
+    // (multiples of the golden ratio: even steps would meet the row ends of a lattice of 2^k a side)
+    const uint64_t p = ((uint64_t)(threadIdx.x * 2654435769u) * (n - 1)) >> 32;
+    const double px = s_p[0][threadIdx.x] = x[p], py = s_p[1][threadIdx.x] = y[p],
+                 pz = s_p[2][threadIdx.x] = z[p];
+    const double next = fmax(fabs(x[p + 1] - px), fmax(fabs(y[p + 1] - py), fabs(z[p + 1] - pz)));
     __syncthreads();
-    const uint64_t p = (n - 1) * threadIdx.x / PM_ORDER_SAMPLES;
-    const double dx = x[p + 1] - x[p], dy = y[p + 1] - y[p], dz = z[p + 1] - z[p];
-    const uint64_t near = __ballot(fabs(dx) < reach && fabs(dy) < reach && fabs(dz) < reach);
-    if ((threadIdx.x & 63u) == 0u)
+    const uint32_t o = (threadIdx.x * 101u + 53u) % PM_ORDER_SAMPLES;   // (never the sample itself)
+    const double other =
+        fmax(fabs(s_p[0][o] - px), fmax(fabs(s_p[1][o] - py), fabs(s_p[2][o] - pz)));
+    const uint64_t near = __ballot(4.0 * next < other), cnt = __ballot(next != other);
+    if ((threadIdx.x & 63u) == 0u) {
         atomicAdd(&s_near, (uint32_t)__popcll(near));
+        atomicAdd(&s_cnt, (uint32_t)__popcll(cnt));
+    }
     __syncthreads();
     if (threadIdx.x == 0)
-        *ordered = 4u * s_near >= 3u * PM_ORDER_SAMPLES;
+        *ordered = 4u * s_near >= 3u * s_cnt;
 }
 
 // Keys, and the particles as rows, so that each is gathered from one line instead of four.
@@ -1120,6 +1133,9 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm_gather(uint64_t n,
 // Positions go to their place and forces back as rows of 32 bytes, one line each: gathered from
 // four arrays and scattered to three, 1e6 took 66 instead of 25 us and 110 instead of 89, 8e6
 // 0.61 instead of 0.20 ms and 1.17 instead of 0.91.
+// Particles in order pay for the look and a dozen kernels that exit at once: 131,072 on 64^3 90 us
+// against 68 with a chunk given (which never sorts), 2e6 on 128^3 240 against 212, 1.7e7 on 256^3
+// 1.36 ms against 1.32.  Nine in ten of 131,072 in a clump of L / 200, shuffled: 4.09 -> 0.12 ms.
 #define PM_SORT_MIN 131072
 static const pm_sorted NO_SORT{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
 static dzs_status pm_sort(dzs_ctx *ctx, const dzs_particles *p, double L, int ng, pm_sorted *S,
@@ -1137,7 +1153,7 @@ static dzs_status pm_sort(dzs_ctx *ctx, const dzs_particles *p, double L, int ng
     {
         dzs_timed t(ctx, KC_KEYS, s);
         hipLaunchKernelGGL(k_pm_order, dim3(1), dim3(PM_ORDER_SAMPLES), 0, s, n, (const double *)p->x,
-                           (const double *)p->y, (const double *)p->z, L / 16.0, ordered);
+                           (const double *)p->y, (const double *)p->z, ordered);
         DZS_TRY(dzs_check_launch(ctx, "pm_order"));
         hipLaunchKernelGGL(k_pm_rows, dim3(blocks_for(n, PM_THREADS)), dim3(PM_THREADS), 0, s, n,
                            (const double *)p->x, (const double *)p->y, (const double *)p->z,

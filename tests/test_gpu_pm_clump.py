@@ -5,7 +5,8 @@ so closeness alone does not show one; taken as they come, a clump's atomics queu
 points (forty times the time of the same set in key order).  The shuffled set must take no more
 than four times the time of the ordered one: the sort costs about as much as the force itself.
 The forces are the same bits, particle by particle, as without sort and tiles (tile_chunk = -1),
-for sets in no order, in key order and at few points.
+for sets in no order, in key order and at few points.  Where nothing is sorted (few particles, fine
+meshes) the lanes of a wave that share a mesh cell add their integers up first.
 """
 import time
 
@@ -45,8 +46,9 @@ def _key_order(x):
     return x[np.argsort(key, kind="stable")]
 
 
-@pytest.mark.parametrize("n,ng,size", [(131072, 64, 0.5), (300001, 64, 5.0), (131072, 64, 0.0)])
-def test_a_shuffled_clump_is_sorted(dz, n, ng, size):
+def _compare(dz, n, ng, size):
+    """The forces of the set in key order and shuffled, each with the bits of the direct kernels,
+    and the shuffled one's time against the ordered one's."""
     import torch
     rng = np.random.default_rng(n + ng)
     x = rng.uniform(0, L, (n, 3))
@@ -77,3 +79,16 @@ def test_a_shuffled_clump_is_sorted(dz, n, ng, size):
     print(f"{n} on {ng}^3, clump {size}: ordered {took[0]:.0f} us, shuffled {took[1]:.0f} us",
           flush=True)
     assert took[1] <= 4 * took[0]
+
+
+@pytest.mark.parametrize("n,ng,size", [(131072, 64, 0.5), (300001, 64, 5.0), (131072, 64, 0.0)])
+def test_a_shuffled_clump_is_sorted(dz, n, ng, size):
+    _compare(dz, n, ng, size)
+
+
+# too few particles for the sort, or too fine a mesh; waves of 64 alone and four to a workgroup, a
+# last one of 1 and of 33 lanes
+@pytest.mark.parametrize("n,ng,size", [(4097, 32, 0.5), (60001, 64, 0.5), (70049, 64, 0.0),
+                                       (131072, 162, 0.5)])
+def test_a_shuffled_clump_adds_up_before_its_atomics(dz, n, ng, size):
+    _compare(dz, n, ng, size)

@@ -251,8 +251,8 @@ __device__ __forceinline__ uint64_t batch_key(double x, double y, double z, uint
            dzs_spread3(cell(z));
 }
 
-// PBLOCK: the drift and lightcone parameters come from a device block (*Ap) rather than the
-// kernel arguments, so that a captured launch can be replayed for another step.
+// PBLOCK (OPEN only): the drift and lightcone parameters come from a device block (*Ap) rather than
+// the kernel arguments, so that a captured launch can be replayed for another step.
 //
 // OPEN: the opening of a whole step in one pass: the kick p + g K before the drift, the Morton key
 // of the drifted position and the row's copy (kicked, drifted) to the staging rows, from which
@@ -280,6 +280,8 @@ __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
     __shared__ uint16_t s_queue[LC_TILE];
     __shared__ uint32_t s_cnt;
     __shared__ unsigned long long s_base;
+    static_assert(OPEN || !PBLOCK, "only a step's opening is captured");
+    const bool batch = OPEN && boxes;
     const lc_args &A = PBLOCK ? *Ap : A_arg;
     const uint64_t base = (uint64_t)blockIdx.x * LC_TILE;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -297,8 +299,8 @@ __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
         const uint64_t i = base + (uint32_t)r * PT_THREADS + tid;
         bool emit = false;
         if (i < n) {
-            const uint32_t bi = boxes ? batch_box_of(bfirst, nb, i) : 0u;
-            const double Lb = boxes ? boxes[bi].L : L;
+            const uint32_t bi = batch ? batch_box_of(bfirst, nb, i) : 0u;
+            const double Lb = batch ? boxes[bi].L : L;
             const double xi = x[i], yi = y[i], zi = z[i];
             const double pxi = mom(px, O.gx, i), pyi = mom(py, O.gy, i), pzi = mom(pz, O.gz, i);
             nx[r] = dzs_wrap(xi + pxi * A.D, Lb);
@@ -314,7 +316,7 @@ __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
                 O.out.mult[i] = mult[i];
                 O.out.id[i] = id[i];
                 O.out.type[i] = O.type[i];
-                O.key[i] = boxes ? batch_key(nx[r], ny[r], nz[r], bi, Lb)
+                O.key[i] = batch ? batch_key(nx[r], ny[r], nz[r], bi, Lb)
                                  : dzs_morton(nx[r], ny[r], nz[r], O.key_scale);
                 O.idx[i] = (uint32_t)i;
             }
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(PT_THREADS) void k_drift_lc(
             __syncthreads();
             for (uint32_t e = tid; e < cnt; e += PT_THREADS) {
                 const uint64_t i = base + s_queue[e];
-                const double Lb = boxes ? boxes[batch_box_of(bfirst, nb, i)].L : L;
+                const double Lb = batch ? boxes[batch_box_of(bfirst, nb, i)].L : L;
                 const unsigned long long slot = s_base + e;
                 if (slot >= rec_cap) {
                     *overflow = 1u;
@@ -456,14 +458,16 @@ static dzs_status launch_drift(dzs_ctx *ctx, const dzs_box *box, const dzs_parti
     // (256^3 493 -> 509 us).  Sixteen: 93 us.
     const std::integral_constant<int, 4> four;
     const std::integral_constant<int, 8> eight;
-    if (A_dev)
-        launch(std::true_type(), four);
-    else if constexpr (OPEN)
-        launch(std::false_type(), four);
-    else if (p->n >= 1u << 20)
+    if constexpr (OPEN) {
+        if (A_dev)
+            launch(std::true_type(), four);
+        else
+            launch(std::false_type(), four);
+    } else if (p->n >= 1u << 20) {
         launch(std::false_type(), eight);
-    else
+    } else {
         launch(std::false_type(), four);
+    }
     return dzs_check_launch(ctx, "drift_lc");
 }
 

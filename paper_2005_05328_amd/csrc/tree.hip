@@ -1590,7 +1590,6 @@ __global__ __launch_bounds__(64 * (TEAM > 1 ? TEAM : walk_waves<T>::N), 4) void 
             // pairs below the table of F are close pairs too (a few ulps above its low end)
             hg2 = wmax(hg2, 1.000001f * A.ft_lo);
         }
-        const uint64_t act_mask = __ballot(active);
         const T m_unit = T(W.m0), h_unit = T(W.h0);
         const typename vec4_of<T>::half hh_unit = {wmax(h_unit * h_unit, hg2), h_unit};
         // A dense FP32 group is evaluated as two halves, A (its targets 0 .. G/2-1) and B
@@ -2369,13 +2368,13 @@ dzs_status dzs_tree_walk_ex(dzs_ctx *ctx, const dzs_box *box, uint64_t n, const 
         const std::integral_constant<int, 2> two;
         const std::integral_constant<int, 4> four;
         auto pick = [&](auto cells, auto batch) {
-            if (fp32 && !ft)
-                launch(cells, batch, one, no, 0.0f);
-            else if (!fp32)
+            if (!fp32)
                 team == 1 ? launch(cells, batch, one, no, 0.0)
                           : (team == 2 ? launch(cells, batch, two, no, 0.0)
                                        : launch(cells, batch, four, no, 0.0));
-            else if constexpr (!batch.value)
+            else if constexpr (batch.value)
+                launch(cells, batch, one, no, 0.0f);
+            else
                 team == 1 ? launch(cells, batch, one, yes, 0.0f)
                           : (team == 2 ? launch(cells, batch, two, yes, 0.0f)
                                        : launch(cells, batch, four, yes, 0.0f));

@@ -739,9 +739,9 @@ extern "C" dzs_status kdk_step(dzs_ctx *ctx, const dzs_box *box, dzs_particles *
                 DZS_TRY(dzs_permute_f32(ctx, ctx->aold, ctx->idx, st->n, s));
         }
         // the mesh solve (deposit, FFTs) runs on the context's second stream while this one
-        // builds the tree (many small launches and a few host read-backs that leave most of
-        // the GPU idle); the walk starts after both, alone on the GPU (overlapping it with the
-        // FFTs slowed the 512^3 walk by 7%)
+        // builds the tree (launches that depend on each other and leave part of the GPU idle);
+        // the walk starts after both, alone on the GPU (overlapping it with the FFTs slowed the
+        // 512^3 walk by 7%)
         DZS_TRY(ensure_pm_stream(ctx));
         DZS_HIP(ctx, hipEventRecord(ctx->ev_fork, s));
         DZS_HIP(ctx, hipStreamWaitEvent(ctx->pm_stream, ctx->ev_fork, 0));

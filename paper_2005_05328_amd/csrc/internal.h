@@ -271,7 +271,6 @@ struct dzs_timed {
 // device helpers shared by the kernels of this library
 // ---------------------------------------------------------------------------------------
 
-// minimum image of one separation component: into [-L/2, L/2)
 // The block that a workgroup works on: each of the 8 XCDs (workgroups go to them in turn) takes
 // one contiguous part of the blocks, so that the lines that neighbouring blocks share, written by
 // one a few bytes at a time and by the next the others, meet in one L2.
@@ -280,6 +279,7 @@ __device__ __forceinline__ uint32_t dzs_xcd_block() {
     return x * per + (x < rem ? x : rem) + (blockIdx.x >> 3);
 }
 
+// minimum image of one separation component: into [-L/2, L/2)
 __device__ __forceinline__ double dzs_min_image(double d, double L) {
     if (d >= 0.5 * L)
         d -= L;
@@ -517,10 +517,9 @@ dzs_status dzs_pm_run_batch(dzs_ctx *ctx, const dzs_particles *p, int precision,
                             int32_t tile_chunk, const dzs_bbox *db, double G, hipStream_t s);
 
 // coarsen.hip
-// d_small word slots: 8 the coarsening survivor count, 9 its head count, 16..17 the bits of
-// the dynamical criterion's min g.g (8-byte aligned).
 #define DZS_ROW_BYTES 57        // a staged row: six doubles, mult, id, type
 #define DZS_STAT_WORDS 272      // dz_stat: 16 counters of groups, 16 words apart, and the kept rows
+// d_small words 16..17: the bits of the dynamical criterion's min g.g (8-byte aligned)
 #define DZS_SMALL_AMIN 16
 // d_small word 20: set when the keys of a coarsened state are out of order
 #define DZS_SMALL_UNSORTED 20

@@ -453,9 +453,9 @@ static dzs_status launch_drift(dzs_ctx *ctx, const dzs_box *box, const dzs_parti
                            batch ? ctx->batch_box : nullptr, nb, O);
     };
     // Eight particles a thread queue twice the crossings for a workgroup's dense solves: with
-    // 1.4% crossing, 4e6 particles 103 -> 82 us, 2e6 69 -> 50, 1e6 44 -> 45, 4e5 34 -> 37 (fewer
-    // workgroups than the GPU holds); a step's opening, which also stages rows, loses by it
-    // (256^3 493 -> 509 us).  Sixteen: 93 us.
+    // 1.4% crossing, 4e6 particles 97 -> 70 us, 2e6 59 -> 39, 1e6 33 -> 29, 4e5 23 -> 24 (fewer
+    // workgroups than the GPU holds: the line is where there surely are enough); a step's opening,
+    // which also stages rows, loses by it (256^3 493 -> 509 us).
     const std::integral_constant<int, 4> four;
     const std::integral_constant<int, 8> eight;
     if constexpr (OPEN) {

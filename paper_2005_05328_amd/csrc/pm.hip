@@ -224,9 +224,8 @@ __device__ __forceinline__ int wrap_index(int i, int ng) {
 }
 
 // The same for an index within one period of the mesh, -ng <= i < 2 ng, by compares instead
-// of a division: a stencil point i0 + d (|d| <= 3 < ng), or a tile point (the base indices of
-// positions in [0, L) lie in [0, ng], a tile reaches at most ng + 2 points past its lowest and
-// starts at most 2 before it; meshes have at least 8 points per side).
+// of a division: a stencil point i0 + d (|d| <= 3 < ng), or a point of a deposit tile (base
+// indices in [0, ng] and the points after them; meshes have at least 8 points per side).
 __device__ __forceinline__ int wrap_near(int i, int ng) {
     return i < 0 ? i + ng : (i >= ng ? i - ng : i);
 }

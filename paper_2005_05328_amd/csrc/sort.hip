@@ -9,7 +9,7 @@
 // by wave-level digit matching through eight ballots, then the waves' counts become offsets —
 // stages the tile in LDS in local digit order and writes it out so that consecutive lanes write
 // consecutive addresses of the same digit run.  Three launches of a pass up to 64 tiles, four
-// above.  At most 8192 keys: one workgroup makes all passes in LDS, in one launch.
+// above.  At most 32768 keys: each key's place is counted against all others, in two launches.
 #include "internal.h"
 
 #define SCAN_THREADS 256

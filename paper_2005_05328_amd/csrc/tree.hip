@@ -967,7 +967,7 @@ struct walk_args {
     int G_lanes;  // targets per wave (64 / phases)
     uint32_t *stack;
     uint32_t depth;
-    uint32_t *counter;  // [0] next group, [1] overflow flag
+    uint32_t *counter;  // [0] next group, [2] overflow flag
     unsigned long long *pair_count;
     double q[WALK_QN];
     float4 stab[WALK_TAB_N + 1];  // FP32 form: the cubics of S(u), coefficients of f^0..f^3
@@ -1405,7 +1405,10 @@ __device__ __forceinline__ void pair_dense(const pair_eval<float, true> &ev, flo
     np_wave += (uint32_t)__builtin_amdgcn_readfirstlane((int)cnt);
 }
 
-// 4 waves per SIMD (128 VGPRs).
+// 4 waves per SIMD (128 VGPRs), at the price of spills around the pair loops: 10 to 18 VGPRs in
+// FP64 with start cells or in a batch, 12 to 22 in FP32 (3 waves without them: 256^3 FP32 28.1 ms
+// against 23.1 at the time).  The FP32 teams of two get 3: every two waves hold the tables (23.7
+// KB a workgroup), so the LDS allows no more and the compiler takes 155 to 166 VGPRs.
 //
 // TEAM > 1: the workgroup's TEAM waves take every group together.  Each walks the tree and fills
 // its own list (the same one), evaluates every TEAM-th of its entries, and the first adds the
@@ -2329,8 +2332,8 @@ dzs_status dzs_tree_walk_ex(dzs_ctx *ctx, const dzs_box *box, uint64_t n, const 
     // persistent waves: each takes groups until the counter passes the device group count
     const bool ft = fp32 && !boxes;
     // Waves per group, by n / group_size, the least number of groups (the tree cuts about 1.5
-    // times as many).  With 4096 resident waves a launch of few groups lasts as long as its
-    // heaviest one: FP64, 110,592 clustered particles in groups of 32 (3456) 1.16 ms alone, 0.98
+    // times as many).  With 4096 resident waves (3072 in FP32 teams of two) a launch of few groups
+    // lasts as long as its heaviest one: FP64, 110,592 clustered particles in groups of 32 (3456) 1.16 ms alone, 0.98
     // in twos, 1.01 in fours; 20^3 (250) 78, 63 and 58 us; FP32 in groups of 64, 100,000
     // clustered (1562) 1.42, 0.96 and 0.74 ms, near-uniform 32^3 (512) 286, 195 and 181 us, 48^3
     // (1728) 436, 446 and 489 us.  Where every wave has several groups the repeated walks only

@@ -26,8 +26,8 @@ def dz():
     return dz
 
 
-def _force(dz, k, n, group):
-    """The FP32 short-range force in a box of 100 2^k, in units of the force at k = 0."""
+def _force(dz, k, n, group, ng=64, eps_frac=4e4, mass=1.0):
+    """The FP32 short-range force in a box of 100 2^k, in units of the force at k = 0, mass = 1."""
     s = 2.0 ** k
     ps = dzs_ics.merged_state(dzs_ics.clustered_random(n, L0, seed=n, r_clump=L0 / 50), seed=3,
                               max_mult=16)
@@ -38,15 +38,16 @@ def _force(dz, k, n, group):
         v[m] = v[m + 1] + rng.standard_normal(len(m)) * 10.0 ** rng.uniform(-4, -1, len(m))
         v[:] = np.mod(v, L0) * s
     ps.L = L0 * s
-    r_s = 1.25 * ps.L / 64
-    box = dz.make_box(ps.L, dzs_ics.particle_mass(L0, n), ps.L / round(n ** (1 / 3)) / 4e4)
+    r_s = 1.25 * ps.L / ng
+    box = dz.make_box(ps.L, dzs_ics.particle_mass(L0, n) * mass,
+                      ps.L / round(n ** (1 / 3)) / eps_frac)
     ctx = dz.Context(n, 0)
     st = dz.State.from_host(ps)
     ctx.tree_force(box, st, dz.TreeParams(r_s, 4.5 * r_s, 0.0, 8, group, dz.DZS_FP32, 0))
     ctx.check()
     g = np.stack([getattr(st, a)[:n].cpu().numpy() for a in ("gx", "gy", "gz")])
     ctx.close()
-    return g * s * s
+    return g * s * s / mass
 
 
 # teams of four waves, groups on few lanes (the masked loop at 4), one wave a group
@@ -59,3 +60,14 @@ def test_fp32_force_scales_with_the_unit_of_length(dz, n, group):
         print(f"n {n} group {group} box {L0 * 2.0 ** k:.3g}: {(~np.isfinite(g)).sum()} not finite, "
               f"largest difference {np.abs(g - one).max() / np.abs(one).max():.1e}", flush=True)
         assert np.array_equal(g, one), f"box {L0 * 2.0 ** k:.3g}"
+
+
+def test_fp32_force_where_the_table_begins_later(dz):
+    """r_cut^2 = 2^-67.7: the table of far pairs begins at 2^-83, above r_cut^2 / 2^16, so that its
+    coefficients are in range.  The pairs below lie inside the softening here (h from r_cut / 18,
+    the table from r_cut / 200), whose force is the same arithmetic at every scale: the same bits.
+    A mass unit of 2^-60 keeps mass over h^3 in range."""
+    one = _force(dz, 0, 3000, 16, ng=16, eps_frac=10.0)
+    g = _force(dz, -39, 3000, 16, ng=16, eps_frac=10.0, mass=2.0 ** -60)
+    print(f"largest difference {np.abs(g - one).max() / np.abs(one).max():.1e}", flush=True)
+    assert np.isfinite(one).all() and np.array_equal(g, one)
